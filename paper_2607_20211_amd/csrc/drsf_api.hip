@@ -49,6 +49,12 @@ constexpr int CREATE_DEEP_LOG = 16;
 enum Phase { PH_VALIDATE, PH_UPDATE, PH_ROOT, PH_ORPH_LIST, PH_ORPH_SCAN, PH_SWEEP, PH_SWEEP_DELTA,
              PH_REPL, PH_ROOTING, PH_FINISH, PH_N };
 
+// The inserted-edge list is merged into the base store every delta_capacity
+// inserts, or kept when at most an eighth of that many of its entries are
+// live; so it can hold that many more.
+constexpr int64_t LIST_KEEP = 8;
+int64_t list_capacity(int64_t dcap) { return dcap + dcap / LIST_KEEP; }
+
 int ceil_log2(int64_t x) {
     int r = 0;
     while (((int64_t)1 << r) < x) r++;
@@ -60,11 +66,12 @@ int ceil_log2(int64_t x) {
 struct drsf_snapshot {
     drsf_opts opts{};  // allocator hooks of the context it was taken from
     int32_t n = 0;
-    int64_t eb = 0, dcap = 0, ndelta_bound = 0, m_live = 0, rebuilds = 0;
+    int64_t eb = 0, dcap = 0, m_live = 0, rebuilds = 0;
+    int64_t ndelta_bound = 0, nd = 0, nfree = 0, hash_used = 0, ntomb = 0;  // as in drsf_ctx
     uint64_t dhmask = 0;
-    unsigned long long ndelta = 0;
     std::vector<int64_t> gm;
-    int32_t *parent = nullptr, *label = nullptr, *bcol = nullptr, *lcol = nullptr, *dhpos = nullptr;
+    int32_t *parent = nullptr, *label = nullptr, *bcol = nullptr, *lcol = nullptr, *dhpos = nullptr,
+            *dfree = nullptr;
     uint64_t *dkey = nullptr, *dhash = nullptr;
     // small graphs: their key pool, live counts and current buffers
     int64_t pool_keys = 0;
@@ -98,9 +105,18 @@ struct drsf_ctx {
     int64_t ntiles = 0;
     uint64_t *dkey = nullptr;
     int64_t dcap = 0, dtmax = 0;
+    // inserts since the inserted-edge list was last merged (see merge_list),
+    // queued ones included: at most dcap.  The list's length after every
+    // queued update, at most (its arrays hold lcap); its length and free
+    // positions after the last update waited for; slots of its index that may
+    // not be empty; deleted entries of the base store
     int64_t ndelta_bound = 0;
+    int64_t lcap = 0, list_len = 0;
+    int64_t nd_known = 0, nfree_known = 0, hash_used = 0, ntomb = 0;
     uint64_t *dhash = nullptr;
-    int32_t *dhpos = nullptr;
+    int32_t *dhpos = nullptr, *dfree = nullptr;
+    int32_t *adeg = nullptr;
+    bool adeg_on = false;  // adeg differs from the store's row lengths
     uint64_t dhmask = 0;
     // forest
     int32_t *parent = nullptr, *label = nullptr, *rep = nullptr;
@@ -205,6 +221,7 @@ struct drsf_ctx {
         uint64_t seq;
         int kind, op;
         int64_t b;
+        int64_t nins;  // inserts into the edge store
     } pend[2] = {};
     int npend = 0;
     // results of updates that a call of the library waited for on the
@@ -218,7 +235,7 @@ struct drsf_ctx {
     bool multi_last = false;
     std::vector<int64_t> last_bg;  // per-graph batch sizes of the last apply
     std::vector<int8_t> last_opg;  // per-graph op of the last apply
-    int64_t last_b = 0;
+    int64_t last_b = 0, last_nins = 0;
     int last_op = 0;
     int last_rc = DRSF_OK;
     drsf_view view{};
@@ -373,7 +390,9 @@ Dev make_dev(drsf_ctx *c) {
     d.gsum = c->gsum; d.gpre = c->gpre; d.gopre = c->gopre; d.ostage = c->ostage;
     d.zrow = c->zrow; d.zptr = c->zptr; d.nz = c->nz; d.tile_k = c->tile_k; d.ntiles = c->ntiles;
     d.dtmax = c->dtmax;
-    d.dkey = c->dkey; d.dcap = c->dcap; d.dhash = c->dhash; d.dhpos = c->dhpos; d.dhmask = c->dhmask;
+    d.dkey = c->dkey; d.dcap = c->lcap; d.dhash = c->dhash; d.dhpos = c->dhpos; d.dhmask = c->dhmask;
+    d.dfree = c->dfree;
+    d.adeg = c->adeg_on ? c->adeg : nullptr;
     d.parent = c->parent; d.label = c->label; d.rep = c->rep;
     d.obits = c->obits;
     d.tidx = c->tidx; d.owner = c->owner; d.pkeep = c->pkeep; d.prt = c->prt; d.pmin = c->pmin;
@@ -532,13 +551,15 @@ int alloc_state(drsf_ctx *c) {
     if ((rc = dalloc(c, &c->dslot, (int64_t)ds))) return rc;
     c->dcap = c->opts.delta_capacity > 0 ? c->opts.delta_capacity
                                          : std::max<int64_t>({4 * mb, c->eb / 8, 1 << 20});
-    c->dtmax = delta_tiles(c->dcap);
-    if ((rc = dalloc(c, &c->dkey, c->dcap))) return rc;
+    c->lcap = list_capacity(c->dcap);
+    c->dtmax = delta_tiles(c->lcap);
+    if ((rc = dalloc(c, &c->dkey, c->lcap))) return rc;
     uint64_t dh = 16;
     while (dh < (uint64_t)(2 * c->dcap)) dh <<= 1;
     c->dhmask = dh - 1;
     if ((rc = dalloc(c, &c->dhash, (int64_t)dh))) return rc;
     if ((rc = dalloc(c, &c->dhpos, (int64_t)dh))) return rc;
+    if ((rc = dalloc(c, &c->dfree, c->lcap))) return rc;
     if ((rc = alloc_tiles(c))) return rc;
     c->ercap = c->pcap;
     if ((rc = dalloc(c, &c->er, c->ercap))) return rc;
@@ -1005,12 +1026,39 @@ int rebuild_store(drsf_ctx *c) {
     if (c->ntiles > old_tiles && (rc = alloc_tiles(c))) return rc;
     // empty inserted-edge list
     launch_fill_u64(c->cnt + C_NDELTA, 1, 0, s);
+    launch_fill_u64(c->cnt + C_NFREE, 1, 0, s);
     launch_fill_u64(c->dhash, (int64_t)c->dhmask + 1, HASH_EMPTY, s);
-    c->ndelta_bound = 0;
-    c->rebuilds++;
+    c->nd_known = c->nfree_known = c->list_len = c->hash_used = c->ntomb = 0;
+    c->adeg_on = false;
     HIPCHK(c, hipStreamSynchronize(s));
     c->broken = false;
     drop_graphs(c);
+    return DRSF_OK;
+}
+
+// Called before an insert that would be more than dcap since the last merge,
+// with nothing queued.  The list goes into the base store, unless few of its
+// entries are live: deleted positions are reused and deleted base entries
+// revived, so a stream of edges that come and go leaves a short list, which
+// costs every delete less than the rebuild would.  Then only the figure that
+// a merge changes is brought up to date (drsf_view.orphan_slots counts each
+// vertex's edges as of the last merge).  A snapshot from before is refused
+// after either.
+int merge_list(drsf_ctx *c) {
+    int rc;
+    if (c->nd_known - c->nfree_known > c->dcap / LIST_KEEP) {
+        if ((rc = rebuild_store(c))) return rc;
+    } else {
+        if (!c->adeg && (rc = dalloc(c, &c->adeg, c->n))) return rc;
+        launch_count_edges(make_dev(c), c->adeg, c->list_len, c->stream);
+        if (!c->adeg_on) {
+            HIPCHK(c, hipStreamSynchronize(c->stream));
+            drop_graphs(c);  // captured sequences hold the null pointer
+            c->adeg_on = true;
+        }
+    }
+    c->ndelta_bound = 0;
+    c->rebuilds++;
     return DRSF_OK;
 }
 
@@ -1062,7 +1110,7 @@ void enqueue_update(drsf_ctx *c, int kind, bool profile, const Ctl *kc) {
     Dev d = make_dev(c);
     if (kc) {  // launched kernel by kernel: grids sized for this batch and list
         d.lb = std::max<int64_t>(kc->b, 1);
-        d.ltiles = delta_tiles(c->ndelta_bound);
+        d.ltiles = delta_tiles(c->list_len);
     }
     hipStream_t s = c->stream;
     const bool ins = kind & 1, del = kind & 2;
@@ -1170,7 +1218,7 @@ int continue_update(drsf_ctx *c) {
     Dev d = make_dev(c);
     d.gate = 0;  // runs while the update's cleanup holds any update queued behind it
     d.lb = std::max<int64_t>(c->last_b, 1);
-    d.ltiles = delta_tiles(c->ndelta_bound);
+    d.ltiles = delta_tiles(c->list_len);
     hipStream_t s = c->stream;
     unsigned long long *f = c->h_ret + c->ret_words;  // [0] status, [1] rounds done, [2] level active
     auto read_flags = [&](int levels) -> int {
@@ -1310,7 +1358,7 @@ int launch_update(drsf_ctx *c) {
         HIPCHK(c, hipGraphLaunch(c->gexec[c->slot][c->kind], s));
     }
     HIPCHK(c, hipGetLastError());
-    c->pend[c->slot] = drsf_ctx::Pend{c->seq, c->kind, c->last_op, c->last_b};
+    c->pend[c->slot] = drsf_ctx::Pend{c->seq, c->kind, c->last_op, c->last_b, c->last_nins};
     c->last_slot = c->slot;
     c->npend++;
     c->have_phases = prof;
@@ -1342,10 +1390,34 @@ bool can_queue(const drsf_ctx *c) {
            c->opts.reverse_mode == 0 && c->nsg == 0;
 }
 
+// The inserted-edge list's length at most, once every queued update and
+// `more` further inserts have been applied: each insert takes a free position
+// if there is one (deletes still queued can only free more).
+int64_t list_bound(const drsf_ctx *c, int64_t more) {
+    for (int i = 0; i < c->npend; i++)
+        more += c->pend[c->npend == 1 ? c->last_slot : i].nins;
+    return c->nd_known + std::max<int64_t>(0, more - c->nfree_known);
+}
+
+// Counts an update's inserts into the store's list against its index, and
+// first clears deleted keys out of the index if they could come to fill half
+// of it (a clear and one pass over the list; at least an eighth of the table
+// has been used since the last time).
+void reserve_index(drsf_ctx *c, int64_t nins) {
+    const int64_t slots = (int64_t)c->dhmask + 1;
+    int64_t live = c->nd_known - c->nfree_known;  // with every queued insert: at most
+    for (int i = 0; i < c->npend; i++) live += c->pend[c->npend == 1 ? c->last_slot : i].nins;
+    if (nins > 0 && c->hash_used + nins > slots / 2 && c->hash_used - live >= slots / 8) {
+        launch_rehash(make_dev(c), c->list_len, c->stream);
+        c->hash_used = live;
+    }
+    c->hash_used += nins;
+}
+
 // Regions of x0 the first hooking rounds read (see Dev::x0).
 void set_regions(drsf_ctx *c, Ctl &k) {
     k.ibase = c->ntiles + c->dtmax;
-    const int64_t dreg = c->ntiles + delta_tiles(c->ndelta_bound);
+    const int64_t dreg = c->ntiles + delta_tiles(c->list_len);
     if (k.has_ins && k.has_del) {
         k.rlo = 0;
         k.rhi = k.ibase + insert_regions(k.b);
@@ -1620,14 +1692,15 @@ int64_t drsf_footprint(int32_t n, int64_t nnz, const drsf_opts *opts) {
     const int64_t dcap = o.delta_capacity > 0 ? o.delta_capacity : std::max<int64_t>({4 * mb, eb / 8, 1 << 20});
     auto pow2 = [](int64_t x) { int64_t p = 16; while (p < x) p <<= 1; return p; };
     const int64_t bh = pow2(2 * mb), dh = pow2(2 * dcap);
-    const int64_t xcap = (ntiles + (dcap + TILE - 1) / TILE + (mb + BLOCK - 1) / BLOCK) * TILE;
+    const int64_t lcap = list_capacity(dcap);
+    const int64_t xcap = (ntiles + (lcap + TILE - 1) / TILE + (mb + BLOCK - 1) / BLOCK) * TILE;
     int64_t b = 0;
     b += o.inputs_on_device ? 0 : 8 * (N + 1) + 4 * nnz;                 // staged input
     b += 4 * (N + 1) * 3 + 4 * ntiles * TILE + 8 * eb + 4 * (ntiles + 1);  // bptr, lptr, zptr; bcol; lcol, twin
     b += 4 * N * 2;                                                       // zrow, parent
     b += 16 * N + (N + 63) / 64 * 8;                                      // label, rep, tidx, owner; bitmap
     b += 49 * pcap + 40 * pcap + 16 * pcap + 16 * std::max(2 * pcap, N);  // pieces, tour, er, paths
-    b += 37 * mb + 8 * bh + 8 * dcap + 12 * dh;                           // batch, tables, inserted list
+    b += 37 * mb + 8 * bh + 12 * lcap + 12 * dh + 4 * N;                          // batch, tables, inserted list
     b += 32 * xcap + 8 * (xcap / TILE);                                   // cross lists
     b += 24 * nvb + 40 * N + 40 * nvb * BLOCK + 8 * (ntiles + 1) + 4 * (2 * ntiles + 1) +
          24 * ((nvb + BLOCK - 1) / BLOCK);                                // orphan scan
@@ -1706,7 +1779,7 @@ int drsf_apply_async(drsf_ctx *c, const int32_t *edges, int64_t b, int op) {
         if (b > c->dcap)
             return fail(c, DRSF_E_CAPACITY, "batch of %lld inserts exceeds delta_capacity %lld",
                         (long long)b, (long long)c->dcap);
-        if ((rc = rebuild_store(c))) return rc;
+        if ((rc = merge_list(c))) return rc;
     }
     // a device batch is read in place by the first kernel (the stream orders
     // it before later work the caller queues there); a host batch is staged
@@ -1727,7 +1800,15 @@ int drsf_apply_async(drsf_ctx *c, const int32_t *edges, int64_t b, int op) {
     k.lfast = c->bfs_fast;
     k.smode = c->opts.sweep_mode;
     k.nvl = k.nil = k.ntl = -1;
-    if (op == DRSF_INSERT) c->ndelta_bound += b;
+    c->last_nins = op == DRSF_INSERT ? b : 0;
+    // without validation an insert has no other use for the search of its
+    // row; it pays (about 0.07 ns an insert against 3 ns of rebuild that a
+    // place in the list costs in the end) where one insert in sixteen or
+    // more can find its entry
+    k.revive = c->opts.validate_batches || 16 * c->ntomb >= b;
+    reserve_index(c, c->last_nins);
+    c->ndelta_bound += c->last_nins;
+    c->list_len = list_bound(c, c->last_nins);
     set_regions(c, k);
     return launch_update(c);
 }
@@ -1770,7 +1851,7 @@ int drsf_multi_apply_async(drsf_ctx *c, const int32_t *edges, const int64_t *b_o
         if (nins > c->dcap)
             return fail(c, DRSF_E_CAPACITY, "batch of %lld inserts exceeds delta_capacity %lld",
                         (long long)nins, (long long)c->dcap);
-        if ((rc = rebuild_store(c))) return rc;
+        if ((rc = merge_list(c))) return rc;
     }
     c->have_phases = false;
     c->multi_last = true;
@@ -1859,7 +1940,11 @@ int drsf_multi_apply_async(drsf_ctx *c, const int32_t *edges, const int64_t *b_o
     k.nil = nil;
     k.ntl = ntl;
     k.nsmall = nsmall;
+    k.revive = c->opts.validate_batches || 16 * c->ntomb >= nins;
+    c->last_nins = nins;
+    reserve_index(c, nins);
     c->ndelta_bound += nins;
+    c->list_len = list_bound(c, nins);
     set_regions(c, k);
     return launch_update(c);
 }
@@ -1957,26 +2042,38 @@ int wait_oldest(drsf_ctx *c) {
     if (st != 0) {
         c->last_rc = fail(c, DRSF_E_DEVICE, "internal bound exceeded (status %d)", st);
     } else {
+        // the list as this update left it; of its inserts and deletes in the
+        // store, those that did not go through the list changed base entries
+        c->nd_known = (int64_t)k[C_NDELTA];
+        c->nfree_known = (int64_t)k[C_NFREE];
+        c->hash_used -= c->pend[q].nins - (int64_t)k[C_LISTED];
+        c->ntomb += (int64_t)k[C_LISTED] - (int64_t)k[C_FREED];
         c->view.num_key_cross = (int64_t)(k[C_NCROSS] + k[C_SNCROSS]);
         c->view.num_replacement = (int64_t)(k[C_NER] + k[C_SNER]);
         c->view.num_pieces = (int64_t)k[C_NP];
         c->view.num_paths = (int64_t)(k[C_NR] + k[C_SNR]);
         c->view.scan_orphans = (int32_t)k[C_OMODE];
         c->view.num_orphans = (int64_t)k[C_NORPH];
-        c->view.orphan_slots = (int64_t)k[C_OVOL] - (int64_t)OR_PAD * (int64_t)k[C_NORPH];
+        if (c->adeg_on) {
+            c->view.orphan_slots = 0;
+            for (int i = 0; i < OSLOTS; i++) c->view.orphan_slots += (int64_t)k[C_OSLOTS + i];
+        } else {
+            c->view.orphan_slots = (int64_t)k[C_OVOL] - (int64_t)OR_PAD * (int64_t)k[C_NORPH];
+        }
         c->view.jump_rounds = 0;
         for (int r = 0; r < MAX_JUMP; r++) c->view.jump_rounds += k[C_JUMP_ROUND + r] ? 1 : 0;
         c->last_rc = DRSF_OK;
         if (c->multi_last) {
             for (int32_t g = 0; g < c->ngraph; g++) {
                 const int64_t bg = c->last_bg[g];
+                const bool in_store = c->g2s.empty() || c->g2s[g] < 0;
                 if (c->h_gstat[g]) {
-                    const bool in_store = c->g2s.empty() || c->g2s[g] < 0;
                     if (c->last_opg[g] == DRSF_INSERT && in_store) c->ndelta_bound -= bg;
                 } else {
                     const int64_t dm = c->last_opg[g] == DRSF_INSERT ? bg : -bg;
                     c->gm_h[g] += dm;
                     c->m_live += dm;
+                    if (in_store) c->ntomb -= dm;
                 }
             }
         } else if (c->h_gstat[0]) {
@@ -1991,6 +2088,7 @@ int wait_oldest(drsf_ctx *c) {
             const int64_t dm = c->last_op == DRSF_INSERT ? c->last_b : -c->last_b;
             c->m_live += dm;
             c->gm_h[0] += dm;
+            c->ntomb -= dm;
         }
     }
     c->view.parent = c->parent;
@@ -2133,7 +2231,8 @@ int drsf_snapshot_take(drsf_ctx *c, drsf_snapshot **out) {
     if ((rc = check_usable(c))) return rc;
     drsf_snapshot *s = new drsf_snapshot();
     s->n = c->n; s->eb = c->eb; s->dcap = c->dcap; s->dhmask = c->dhmask;
-    s->ndelta_bound = c->ndelta_bound; s->m_live = c->m_live; s->rebuilds = c->rebuilds;
+    s->m_live = c->m_live; s->rebuilds = c->rebuilds;
+    s->ndelta_bound = c->ndelta_bound; s->nd = c->nd_known; s->nfree = c->nfree_known; s->hash_used = c->hash_used; s->ntomb = c->ntomb;
     s->gm = c->gm_h;
     const size_t dh = (size_t)c->dhmask + 1;
     s->opts = c->opts;
@@ -2144,7 +2243,8 @@ int drsf_snapshot_take(drsf_ctx *c, drsf_snapshot **out) {
     const bool ok = get(&s->parent, 4 * (size_t)c->n) && get(&s->label, 4 * (size_t)c->n) &&
                     get(&s->bcol, 4 * (size_t)std::max<int64_t>(c->eb, 1)) &&
                     get(&s->lcol, 4 * (size_t)std::max<int64_t>(c->eb, 1)) &&
-                    get(&s->dkey, 8 * (size_t)c->dcap) && get(&s->dhash, 8 * dh) && get(&s->dhpos, 4 * dh) &&
+                    get(&s->dkey, 8 * (size_t)c->lcap) && get(&s->dhash, 8 * dh) && get(&s->dhpos, 4 * dh) &&
+                    get(&s->dfree, 4 * (size_t)c->lcap) &&
                     (c->nsg == 0 || (get(&s->pool, 4 * (size_t)c->pool_keys) && get(&s->sm, 4 * (size_t)c->nsg) &&
                                      get(&s->sbuf, 4 * (size_t)c->nsg)));
     s->pool_keys = c->pool_keys;
@@ -2158,17 +2258,16 @@ int drsf_snapshot_take(drsf_ctx *c, drsf_snapshot **out) {
     HIPCHK(c, hipMemcpyAsync(s->label, c->label, 4 * (size_t)c->n, hipMemcpyDeviceToDevice, st));
     if (c->eb) HIPCHK(c, hipMemcpyAsync(s->bcol, c->bcol, 4 * (size_t)c->eb, hipMemcpyDeviceToDevice, st));
     if (c->eb) HIPCHK(c, hipMemcpyAsync(s->lcol, c->lcol, 4 * (size_t)c->eb, hipMemcpyDeviceToDevice, st));
-    HIPCHK(c, hipMemcpyAsync(s->dkey, c->dkey, 8 * (size_t)c->dcap, hipMemcpyDeviceToDevice, st));
+    HIPCHK(c, hipMemcpyAsync(s->dkey, c->dkey, 8 * (size_t)c->lcap, hipMemcpyDeviceToDevice, st));
     HIPCHK(c, hipMemcpyAsync(s->dhash, c->dhash, 8 * dh, hipMemcpyDeviceToDevice, st));
     HIPCHK(c, hipMemcpyAsync(s->dhpos, c->dhpos, 4 * dh, hipMemcpyDeviceToDevice, st));
+    HIPCHK(c, hipMemcpyAsync(s->dfree, c->dfree, 4 * (size_t)c->lcap, hipMemcpyDeviceToDevice, st));
     if (c->nsg) {
         HIPCHK(c, hipMemcpyAsync(s->pool, c->pool, 4 * (size_t)c->pool_keys, hipMemcpyDeviceToDevice, st));
         HIPCHK(c, hipMemcpyAsync(s->sm, c->sm, 4 * (size_t)c->nsg, hipMemcpyDeviceToDevice, st));
         HIPCHK(c, hipMemcpyAsync(s->sbuf, c->sbuf, 4 * (size_t)c->nsg, hipMemcpyDeviceToDevice, st));
     }
-    HIPCHK(c, hipMemcpyAsync(c->h_ret, c->cnt + C_NDELTA, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     HIPCHK(c, hipStreamSynchronize(st));
-    s->ndelta = c->h_ret[0];
     *out = s;
     return DRSF_OK;
 }
@@ -2190,18 +2289,25 @@ int drsf_snapshot_restore(drsf_ctx *c, const drsf_snapshot *s) {
     HIPCHK(c, hipMemcpyAsync(c->rep, s->label, 4 * (size_t)c->n, hipMemcpyDeviceToDevice, st));
     if (c->eb) HIPCHK(c, hipMemcpyAsync(c->bcol, s->bcol, 4 * (size_t)c->eb, hipMemcpyDeviceToDevice, st));
     if (c->eb) HIPCHK(c, hipMemcpyAsync(c->lcol, s->lcol, 4 * (size_t)c->eb, hipMemcpyDeviceToDevice, st));
-    HIPCHK(c, hipMemcpyAsync(c->dkey, s->dkey, 8 * (size_t)c->dcap, hipMemcpyDeviceToDevice, st));
+    HIPCHK(c, hipMemcpyAsync(c->dkey, s->dkey, 8 * (size_t)c->lcap, hipMemcpyDeviceToDevice, st));
     HIPCHK(c, hipMemcpyAsync(c->dhash, s->dhash, 8 * dh, hipMemcpyDeviceToDevice, st));
     HIPCHK(c, hipMemcpyAsync(c->dhpos, s->dhpos, 4 * dh, hipMemcpyDeviceToDevice, st));
+    HIPCHK(c, hipMemcpyAsync(c->dfree, s->dfree, 4 * (size_t)c->lcap, hipMemcpyDeviceToDevice, st));
     if (c->nsg) {
         HIPCHK(c, hipMemcpyAsync(c->pool, s->pool, 4 * (size_t)c->pool_keys, hipMemcpyDeviceToDevice, st));
         HIPCHK(c, hipMemcpyAsync(c->sm, s->sm, 4 * (size_t)c->nsg, hipMemcpyDeviceToDevice, st));
         HIPCHK(c, hipMemcpyAsync(c->sbuf, s->sbuf, 4 * (size_t)c->nsg, hipMemcpyDeviceToDevice, st));
     }
-    c->h_ret[0] = s->ndelta;
+    c->h_ret[0] = (unsigned long long)s->nd;
+    c->h_ret[1] = (unsigned long long)s->nfree;
     HIPCHK(c, hipMemcpyAsync(c->cnt + C_NDELTA, c->h_ret, sizeof(unsigned long long), hipMemcpyHostToDevice, st));
+    HIPCHK(c, hipMemcpyAsync(c->cnt + C_NFREE, c->h_ret + 1, sizeof(unsigned long long), hipMemcpyHostToDevice, st));
     HIPCHK(c, hipStreamSynchronize(st));
     c->ndelta_bound = s->ndelta_bound;
+    c->nd_known = c->list_len = s->nd;
+    c->nfree_known = s->nfree;
+    c->hash_used = s->hash_used;
+    c->ntomb = s->ntomb;
     c->m_live = s->m_live;
     c->gm_h = s->gm;
     c->view.num_edges = c->m_live;
@@ -2211,7 +2317,7 @@ int drsf_snapshot_restore(drsf_ctx *c, const drsf_snapshot *s) {
 void drsf_snapshot_free(drsf_snapshot *s) {
     if (!s) return;
     for (void *p : {(void *)s->parent, (void *)s->label, (void *)s->bcol, (void *)s->lcol, (void *)s->dkey,
-                    (void *)s->dhash, (void *)s->dhpos, (void *)s->pool, (void *)s->sm, (void *)s->sbuf})
+                    (void *)s->dhash, (void *)s->dhpos, (void *)s->dfree, (void *)s->pool, (void *)s->sm, (void *)s->sbuf})
         raw_dfree(s->opts, p);
     delete s;
 }

@@ -24,7 +24,7 @@ struct Ctl {
     const int32_t *edges;  // the batch in the caller's device memory, or null: staged copy
     uint64_t seq;          // update number, written to the completion word when done
     int32_t nsmall;        // small graphs with a batch in this update (SmallDev::tasks)
-    int32_t pad;
+    int32_t revive;        // inserts look for their deleted base entry also without validation
 };
 
 // All device pointers one apply needs; passed by value to every kernel.
@@ -63,6 +63,9 @@ struct Dev {
     uint64_t *dhash;         // [dhmask + 1] key -> slot, HASH_TOMB_BIT marks a deleted key
     int32_t *dhpos;          // [dhmask + 1] slot -> index in dkey
     uint64_t dhmask;
+    int32_t *dfree;          // [dcap] positions of deleted list entries, C_NFREE of them
+    const int32_t *adeg;     // [n] each vertex's edges when the inserted edges were last counted
+                             // as merged, or null: its entries in the store
     // lower half of the same store (row v holds u < v, ascending; TOMB kept
     // in step with the upper copy), so that a vertex's whole adjacency is
     // two contiguous runs
@@ -116,7 +119,8 @@ struct Dev {
     int32_t *gstat;          // [ngraph] batch status bits per graph
     int64_t max_b;
     uint64_t *bkey;          // [max_b] normalised key
-    int64_t *bloc;           // [max_b] >= 0: position in bcol; < 0: -(hash slot + 1)
+    int64_t *bloc;           // [max_b] >= 0: position in bcol; < 0: -(hash slot + 1), or -1 for
+                             // an insert without a deleted base entry
     int32_t *bchild;         // [max_b] child endpoint of a deleted tree edge, NONE otherwise
     int32_t *bslot;          // [max_b] slot claimed in the batch duplicate table
     uint64_t *bhash;         // [bhmask + 1] keys claimed by edges whose slot below collided
@@ -243,6 +247,14 @@ constexpr int C_SNR = C_COUNT + 10;
 constexpr int C_LP_DONE = C_COUNT + 11;
 // root finding: some chase took more than DEEP_STEPS steps (the forest is deep)
 constexpr int C_DEEP = C_COUNT + 12;
+// the inserted-edge list: free positions (persistent, like C_NDELTA), and an
+// update's own inserts into the list and deletes from it
+constexpr int C_NFREE = C_COUNT + 13;
+constexpr int C_LISTED = C_COUNT + 14;
+constexpr int C_FREED = C_COUNT + 15;
+// adeg over the orphans, in OSLOTS partial sums (one word would be a hot address)
+constexpr int OSLOTS = 32;
+constexpr int C_OSLOTS = C_COUNT + 16;
 
 // Grid sizes.  Workgroups are dispatched at about 200-270 per microsecond
 // across the chip, so a kernel of many short workgroups is bound by
@@ -284,6 +296,10 @@ void launch_dedupe(const Dev &d, hipStream_t s);  // repeated pairs inside the b
 void launch_prepare(const Dev &d, bool del, hipStream_t s);  // with rep <- parent when del
 void launch_register(const Dev &d, hipStream_t s);
 void launch_insert_emit(const Dev &d, hipStream_t s);
+// adeg: every vertex's live edges in the store and the list
+void launch_count_edges(const Dev &d, int32_t *adeg, int64_t list, hipStream_t s);
+// the list's hash index from its live entries (deleted keys leave it)
+void launch_rehash(const Dev &d, int64_t count, hipStream_t s);
 // pointer-jumping rounds over rep before the chase (deep forests); a round
 // after one that changed nothing exits at once
 void launch_rep_jump(const Dev &d, int rounds, hipStream_t s);

@@ -87,12 +87,15 @@ __device__ int64_t dhash_find(const Dev &d, uint64_t k) {
     return -1;
 }
 
-// insert key k (not live in the index) pointing at list position pos
+// Insert key k (not live in the index) pointing at list position pos, in the
+// first slot of its probe sequence that holds no live key: a deleted key's
+// slot serves any key, so that a list whose entries come and go does not use
+// up the table (HASH_EMPTY has the tombstone bit too).
 __device__ void dhash_insert(const Dev &d, uint64_t k, int32_t pos) {
     uint64_t h = hmix(k) & d.dhmask;
     for (uint64_t probe = 0; probe <= 2 * d.dhmask + 2; probe++) {
         uint64_t s = d.dhash[h];
-        if (s == HASH_EMPTY || s == (k | HASH_TOMB_BIT)) {
+        if (s & HASH_TOMB_BIT) {
             uint64_t old = atomicCAS((unsigned long long *)&d.dhash[h], (unsigned long long)s,
                                      (unsigned long long)k);
             if (old == s) {
@@ -283,12 +286,13 @@ __global__ __launch_bounds__(BLOCK) void k_classify(Dev d, Ctl kc, int from_arg)
     // launch) or with the launch (a kernel-by-kernel one); the first
     // workgroup publishes it for the later kernels, which read the device copy
     int64_t b;
-    int opm;
+    int opm, revive;
     const int32_t *edges;
     if (from_arg) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *d.ctlw = kc;
         b = kc.b;
         opm = kc.op;
+        revive = kc.revive;
         edges = kc.edges;
     } else {
         const Ctl *hc = d.hctl;
@@ -297,6 +301,7 @@ __global__ __launch_bounds__(BLOCK) void k_classify(Dev d, Ctl kc, int from_arg)
                 reinterpret_cast<const uint64_t *>(hc)[threadIdx.x];
         b = hc->b;
         opm = hc->op;
+        revive = hc->revive;
         edges = hc->edges;
     }
     const int32_t *be = edges ? edges : d.bedges;  // caller's device batch, or the staged one
@@ -319,12 +324,15 @@ __global__ __launch_bounds__(BLOCK) void k_classify(Dev d, Ctl kc, int from_arg)
         }
         const uint64_t k = mkkey((uint32_t)u, (uint32_t)v);
         d.bkey[i] = k;
-        if (!d.validate && (opm == 2 ? (int)d.bop[i] : opm) == 0) continue;  // an absent pair, by contract
+        const int opi = opm == 2 ? (int)d.bop[i] : opm;
+        if (!d.validate && opi == 0 && !revive) {  // an absent pair, by contract
+            d.bloc[i] = -1;
+            continue;
+        }
         const int32_t lo = key_lo(k), hi = key_hi(k);
         // loads that do not depend on the probes below, issued first (the
         // parents only where the batch holds deletes)
         const uint32_t ua = d.bptr[lo], ub = d.bptr[lo + 1], la = d.lptr[hi], lb = d.lptr[hi + 1];
-        const int opi = opm == 2 ? (int)d.bop[i] : opm;
         int32_t plo = NONE, phi = NONE;
         if (opm != 0) {
             plo = d.parent[lo];
@@ -342,18 +350,20 @@ __global__ __launch_bounds__(BLOCK) void k_classify(Dev d, Ctl kc, int from_arg)
             const int64_t q = find_in_row(d.lcol, la, lb, lo, &raw);
             pos = q >= 0 ? (int64_t)d.ltwin[q] : -1;
         }
-        int64_t loc;
-        bool present;
+        int64_t loc = -1;
+        bool present = false;
         if (pos >= 0 && raw >= 0) {
             present = true;
             loc = pos;
-        } else {
+        } else if (opi != 0 || d.validate) {
             const int64_t slot = dhash_find(d, k);
             present = slot >= 0;
             loc = -(slot + 1);
         }
         if (opi == 0) {
-            if (present) atomicOr(&d.gstat[g], ST_EXISTS);
+            if (present && d.validate) atomicOr(&d.gstat[g], ST_EXISTS);
+            // an edge of the base store that was deleted comes back in place
+            d.bloc[i] = !present && pos >= 0 ? pos : -1;
         } else {
             if (!present) {
                 atomicOr(&d.gstat[g], ST_MISSING);
@@ -403,6 +413,14 @@ __global__ __launch_bounds__(BLOCK) void k_dedupe(Dev d) {
 
 // ---------------------------- a2 + a3: update the edge store, cut tree edges
 
+// An inserted edge whose deleted entry is still in the base store gets that
+// entry back (one bit in each half); any other takes a free position of the
+// inserted-edge list, or a new one at its end.  So edges that come and go do
+// not lengthen the list, which every delete scans and which costs a rebuild
+// of the whole store when it is full.  Measured on R-MAT 22 in steady service
+// (half of each batch new edges, half edges coming back): a step of 2 x 1e5
+// updates 750 -> 422 us, of 2 x 1e6 4.75 -> 1.37 ms, where the list used to
+// fill every 80 and every 8 steps.
 // Also nominates the trees of F-hat the batch touches: each touched piece
 // root gets owner[root] = (batch index, side) by plain stores; whichever
 // store lands last owns the registration in k_register (no contended atomics
@@ -435,22 +453,22 @@ __global__ __launch_bounds__(BLOCK) void k_prepare(Dev d, int gb) {
         return;
     }
     const int64_t b = d.ctl->b;
+    const bool has_ins = d.ctl->has_ins, has_del = d.ctl->has_del;
+    // free positions and length of the inserted-edge list before this update
+    const int64_t nfree = (int64_t)d.cnt[C_NFREE], nd = (int64_t)d.cnt[C_NDELTA];
     const int64_t stride = (int64_t)gb * BLOCK;
     for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < b; base += stride) {
         const int64_t i = base + threadIdx.x;
         const bool valid = i < b && edge_op(d, i) != 2 && edge_ok(d, i);
         const int op = valid ? edge_op(d, i) : -1;
+        const int64_t loc = valid ? d.bloc[i] : 0;
+        if (op >= 0 && loc >= 0) {  // a base entry: deleted, or back in its place
+            const uint32_t l2 = d.twin[loc];
+            const int32_t c = d.bcol[loc], c2 = d.lcol[l2];
+            d.bcol[loc] = op == 1 ? c | TOMB : c & COLMASK;
+            d.lcol[l2] = op == 1 ? c2 | TOMB : c2 & COLMASK;
+        }
         if (op == 1) {
-            const int64_t loc = d.bloc[i];
-            if (loc >= 0) {
-                d.bcol[loc] = d.bcol[loc] | TOMB;
-                const uint32_t l2 = d.twin[loc];
-                d.lcol[l2] = d.lcol[l2] | TOMB;
-            } else {
-                const int64_t slot = -loc - 1;
-                d.dkey[d.dhpos[slot]] = KEY_DEAD;
-                d.dhash[slot] = d.bkey[i] | HASH_TOMB_BIT;
-            }
             const int32_t c = d.bchild[i];
             if (c != NONE) {
                 d.parent[c] = c;  // Algorithm 1: parent[u] <- u
@@ -459,14 +477,30 @@ __global__ __launch_bounds__(BLOCK) void k_prepare(Dev d, int gb) {
                 d.owner[d.label[c]] = (int32_t)(2 * i + 1);
             }
         }
-        const int64_t pos = block_append(op == 0 ? 1 : 0, &d.cnt[C_NDELTA]);
-        if (op == 0) {
-            const uint64_t k = d.bkey[i];
-            if (pos >= d.dcap) {
-                atomicOr(d.status, ST_CAPACITY);
-            } else {
-                d.dkey[pos] = k;
-                dhash_insert(d, k, (int32_t)pos);
+        if (has_del) {  // uniform over the grid
+            const bool list = op == 1 && loc < 0;
+            const int64_t at = block_append(list ? 1 : 0, &d.cnt[C_FREED]);
+            if (list) {  // its index slot is marked deleted in k_register, after the inserts' probes
+                const int32_t pos = d.dhpos[-loc - 1];
+                d.dkey[pos] = KEY_DEAD;
+                if (nfree + at < d.dcap) d.dfree[nfree + at] = pos;
+                else atomicOr(d.status, ST_CAPACITY);
+            }
+        }
+        if (has_ins) {
+            const bool list = op == 0 && loc < 0;
+            const int64_t at = block_append(list ? 1 : 0, &d.cnt[C_LISTED]);
+            if (op == 0) {
+                const uint64_t k = d.bkey[i];
+                if (list) {
+                    const int64_t pos = at < nfree ? d.dfree[nfree - 1 - at] : nd + (at - nfree);
+                    if (pos >= d.dcap) {
+                        atomicOr(d.status, ST_CAPACITY);
+                    } else {
+                        d.dkey[pos] = k;
+                        dhash_insert(d, k, (int32_t)pos);
+                    }
+                }
                 const int32_t la = d.label[key_lo(k)], lb = d.label[key_hi(k)];
                 if (la != lb) {
                     d.owner[la] = (int32_t)(2 * i);
@@ -474,6 +508,23 @@ __global__ __launch_bounds__(BLOCK) void k_prepare(Dev d, int gb) {
                 }
             }
         }
+    }
+}
+
+// The list's length and free positions after the update (one workgroup):
+// the inserts took free positions from the end of dfree first, the deletes
+// appended theirs behind it; with both, appended ones fill the taken places.
+__device__ void settle_list(const Dev &d) {
+    const int64_t nfree = (int64_t)d.cnt[C_NFREE];
+    const int64_t listed = (int64_t)d.cnt[C_LISTED], freed = (int64_t)d.cnt[C_FREED];
+    const int64_t taken = listed < nfree ? listed : nfree;
+    const int64_t move = taken < freed ? taken : freed;
+    for (int64_t i = threadIdx.x; i < move; i += BLOCK)
+        d.dfree[nfree - taken + i] = d.dfree[nfree + freed - 1 - i];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        d.cnt[C_NFREE] = (unsigned long long)(nfree - taken + freed);
+        d.cnt[C_NDELTA] += (unsigned long long)(listed - taken);
     }
 }
 
@@ -489,6 +540,8 @@ __global__ __launch_bounds__(BLOCK) void k_register(Dev d) {
         if (i < b && edge_op(d, i) != 2 && edge_ok(d, i)) {
             del = edge_op(d, i) == 1;
             if (del) {
+                const int64_t loc = d.bloc[i];
+                if (loc < 0) d.dhash[-loc - 1] = d.bkey[i] | HASH_TOMB_BIT;
                 const int32_t c = d.bchild[i];
                 if (c != NONE) {
                     a = c;
@@ -507,6 +560,43 @@ __global__ __launch_bounds__(BLOCK) void k_register(Dev d) {
         const int64_t ib = ia + (ga ? 1 : 0);
         if (ga) init_piece(d, ia, a, false);
         if (gb) init_piece(d, ib, c2, del);
+    }
+    if (blockIdx.x == 0) settle_list(d);
+}
+
+// Live edges of each vertex: its entries in the store's two halves, less the
+// deleted ones (the mirror of an upper entry holds its row), plus the list's.
+__global__ __launch_bounds__(BLOCK) void k_row_entries(Dev d, int32_t *adeg) {
+    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    for (int64_t v = (int64_t)blockIdx.x * BLOCK + threadIdx.x; v < d.n; v += stride)
+        adeg[v] = (int32_t)(d.bptr[v + 1] - d.bptr[v] + d.lptr[v + 1] - d.lptr[v]);
+}
+__global__ __launch_bounds__(BLOCK) void k_live_edges(Dev d, int32_t *adeg) {
+    const int64_t nd = (int64_t)d.cnt[C_NDELTA];
+    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    for (int64_t j = (int64_t)blockIdx.x * BLOCK + threadIdx.x; j < d.eb; j += stride) {
+        const int32_t c = d.bcol[j];
+        if (c >= 0) continue;
+        atomicSub(&adeg[c & COLMASK], 1);
+        atomicSub(&adeg[d.lcol[d.twin[j]] & COLMASK], 1);
+    }
+    for (int64_t j = (int64_t)blockIdx.x * BLOCK + threadIdx.x; j < nd; j += stride) {
+        const uint64_t k = d.dkey[j];
+        if (k == KEY_DEAD) continue;
+        atomicAdd(&adeg[key_lo(k)], 1);
+        atomicAdd(&adeg[key_hi(k)], 1);
+    }
+}
+
+// The inserted-edge index again from the list's live entries (the table has
+// been cleared): deleted keys' slots lengthen the probes of absent keys, so
+// the host queues this once they could fill half of the table.
+__global__ __launch_bounds__(BLOCK) void k_rehash(Dev d) {
+    const int64_t nd = (int64_t)d.cnt[C_NDELTA];
+    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < nd; i += stride) {
+        const uint64_t k = d.dkey[i];
+        if (k != KEY_DEAD) dhash_insert(d, k, (int32_t)i);
     }
 }
 
@@ -1908,10 +1998,18 @@ __global__ __launch_bounds__(BLOCK) void k_lp_reverse(Dev d, LongPaths b) {
 
 // ------------------------------------------------------------ a9: labels
 
+// A wave's share of the orphans' edges, as they were last counted.
+__device__ __forceinline__ void add_edges(const Dev &d, unsigned long long x) {
+    for (int o = WAVE / 2; o > 0; o >>= 1) x += __shfl_xor(x, o);
+    if (lane_id() == 0 && x)
+        atomicAdd(&d.cnt[C_OSLOTS + (blockIdx.x * (BLOCK / WAVE) + threadIdx.x / WAVE) % OSLOTS], x);
+}
+
 // Deletes: a vertex cut off from its old root takes its new component's
 // label.  Runs before the insert labels (mixed batches).  Restores
 // rep == label for the next update.
 __device__ void label_delete(const Dev &d, int64_t bid, int64_t nblk) {
+    unsigned long long edges = 0;  // of this thread's orphans
     if (d.cnt[C_OMODE]) {
         // the orphan list holds every orphan with its piece (rep and the
         // piece table are unchanged since root finding): relabel them, clear
@@ -1921,6 +2019,7 @@ __device__ void label_delete(const Dev &d, int64_t bid, int64_t nblk) {
         for (int64_t i = bid * BLOCK + threadIdx.x; i < no; i += stride) {
             const int32_t v = d.olist[i].v;
             const int32_t p = d.olist[i].pu;
+            if (d.adeg) edges += (unsigned long long)d.adeg[v];
             if (p >= 0) {
                 const int32_t l = d.newlab[d.comp[p]];
                 d.label[v] = l;
@@ -1932,6 +2031,7 @@ __device__ void label_delete(const Dev &d, int64_t bid, int64_t nblk) {
             d.bvol[v / BLOCK] = 0;
             d.bcnt[v / BLOCK] = 0;
         }
+        if (d.adeg) add_edges(d, edges);
         return;
     }
     const int64_t nb = (d.n + BLOCK - 1) / BLOCK;
@@ -1952,6 +2052,7 @@ __device__ void label_delete(const Dev &d, int64_t bid, int64_t nblk) {
         }
         if (v < d.n && ((w >> (v & 63)) & 1)) {
             const int32_t p = d.tidx[d.rep[v]];
+            if (d.adeg) edges += (unsigned long long)d.adeg[v];
             if (p >= 0) {
                 const int32_t l = d.newlab[d.comp[p]];
                 d.label[v] = l;
@@ -1961,6 +2062,7 @@ __device__ void label_delete(const Dev &d, int64_t bid, int64_t nblk) {
             }
         }
     }
+    if (d.adeg) add_edges(d, edges);
 }
 
 // Inserts: every vertex of a tree that merged into another takes the new
@@ -2287,7 +2389,7 @@ __global__ __launch_bounds__(BLOCK) void k_cleanup(Dev d) {
     if (!fin) return;
     const int t = threadIdx.x;
     for (int u = t; u < C_TOTAL; u += BLOCK)
-        if (u != C_NDELTA) d.cnt[u] = 0;
+        if (u != C_NDELTA && u != C_NFREE) d.cnt[u] = 0;
     for (int64_t g = threadIdx.x; g < d.ctl->ngraph; g += BLOCK) d.gstat[g] = 0;
     if (t == 0) {
         d.status[0] = 0;
@@ -2322,6 +2424,14 @@ void launch_register(const Dev &d, hipStream_t s) {
 }
 void launch_insert_emit(const Dev &d, hipStream_t s) {
     hipLaunchKernelGGL(k_insert_emit, dim3((unsigned)insert_regions(d.lb)), dim3(BLOCK), 0, s, d);
+}
+void launch_count_edges(const Dev &d, int32_t *adeg, int64_t list, hipStream_t s) {
+    hipLaunchKernelGGL(k_row_entries, dim3(grid_for(d.n, BLOCK)), dim3(BLOCK), 0, s, d, adeg);
+    hipLaunchKernelGGL(k_live_edges, dim3(grid_for(std::max(d.eb, list), BLOCK)), dim3(BLOCK), 0, s, d, adeg);
+}
+void launch_rehash(const Dev &d, int64_t count, hipStream_t s) {
+    launch_fill_u64(d.dhash, (int64_t)d.dhmask + 1, HASH_EMPTY, s);
+    hipLaunchKernelGGL(k_rehash, dim3(grid_for(count, BLOCK)), dim3(BLOCK), 0, s, d);
 }
 void launch_rep_jump(const Dev &d, int rounds, hipStream_t s) {
     for (int k = 0; k < std::min(rounds, MAX_JUMP); k++)
