@@ -116,6 +116,7 @@ struct drsf_ctx {
     uint64_t *dhash = nullptr;
     int32_t *dhpos = nullptr, *dfree = nullptr;
     int32_t *adeg = nullptr;
+    unsigned long long *osum = nullptr, *wdeg = nullptr;
     bool adeg_on = false;  // adeg differs from the store's row lengths
     uint64_t dhmask = 0;
     // forest
@@ -139,11 +140,10 @@ struct drsf_ctx {
     uint64_t dsmask = 0;
     // orphan scan
     int64_t nvb = 0;
-    int64_t *bvol = nullptr, *bpre = nullptr;
-    unsigned long long *gsum = nullptr;
+    unsigned long long *wvol = nullptr, *wpre = nullptr, *gsum = nullptr;
     int64_t *gpre = nullptr, *gopre = nullptr;
-    int32_t *bcnt = nullptr, *opre = nullptr, *rstart = nullptr;
-    OrphEnt *olist = nullptr, *ostage = nullptr;
+    int32_t *rstart = nullptr;
+    OrphEnt *olist = nullptr;
     unsigned long long *xcnt = nullptr;
     int32_t *lists = nullptr;      // vlist | ilist | tlist (several graphs)
     int64_t nvblk = 0;
@@ -385,14 +385,16 @@ Dev make_dev(drsf_ctx *c) {
     d.ret_words = c->ret_words;
     d.bptr = c->bptr; d.bcol = c->bcol; d.eb = c->eb;
     d.lptr = c->lptr; d.lcol = c->lcol; d.twin = c->twin; d.ltwin = c->ltwin;
-    d.nvb = c->nvb; d.bvol = c->bvol; d.bcnt = c->bcnt; d.bpre = c->bpre; d.opre = c->opre;
+    d.nvb = c->nvb; d.wvol = c->wvol; d.wpre = c->wpre;
     d.olist = c->olist; d.rstart = c->rstart; d.xcnt = c->xcnt;
-    d.gsum = c->gsum; d.gpre = c->gpre; d.gopre = c->gopre; d.ostage = c->ostage;
+    d.gsum = c->gsum; d.gpre = c->gpre; d.gopre = c->gopre;
     d.zrow = c->zrow; d.zptr = c->zptr; d.nz = c->nz; d.tile_k = c->tile_k; d.ntiles = c->ntiles;
     d.dtmax = c->dtmax;
     d.dkey = c->dkey; d.dcap = c->lcap; d.dhash = c->dhash; d.dhpos = c->dhpos; d.dhmask = c->dhmask;
     d.dfree = c->dfree;
     d.adeg = c->adeg_on ? c->adeg : nullptr;
+    d.osum = c->osum;
+    d.wdeg = c->wdeg;
     d.parent = c->parent; d.label = c->label; d.rep = c->rep;
     d.obits = c->obits;
     d.tidx = c->tidx; d.owner = c->owner; d.pkeep = c->pkeep; d.prt = c->prt; d.pmin = c->pmin;
@@ -593,17 +595,13 @@ int alloc_state(drsf_ctx *c) {
     if ((rc = dalloc(c, &c->ctl, 1))) return rc;
     // orphan scan: per-block figures (zero between updates), list, ranges
     c->nvb = (n + BLOCK - 1) / BLOCK;
-    if ((rc = dalloc(c, &c->bvol, c->nvb))) return rc;
-    if ((rc = dalloc(c, &c->bcnt, c->nvb))) return rc;
-    if ((rc = dalloc(c, &c->bpre, c->nvb))) return rc;
-    if ((rc = dalloc(c, &c->opre, c->nvb))) return rc;
-    if ((rc = dalloc(c, &c->gsum, (c->nvb + BLOCK - 1) / BLOCK))) return rc;
-    if ((rc = dalloc(c, &c->gpre, (c->nvb + BLOCK - 1) / BLOCK))) return rc;
-    if ((rc = dalloc(c, &c->gopre, (c->nvb + BLOCK - 1) / BLOCK))) return rc;
+    if ((rc = dalloc(c, &c->wvol, orphan_words(c->nvb)))) return rc;
+    if ((rc = dalloc(c, &c->wpre, orphan_words(c->nvb)))) return rc;
+    if ((rc = dalloc(c, &c->gsum, orphan_groups(c->nvb)))) return rc;
+    if ((rc = dalloc(c, &c->gpre, orphan_groups(c->nvb)))) return rc;
+    if ((rc = dalloc(c, &c->gopre, orphan_groups(c->nvb)))) return rc;
     if ((rc = dalloc(c, &c->olist, n))) return rc;
-    if ((rc = dalloc(c, &c->ostage, c->nvb * BLOCK))) return rc;
-    launch_fill_u64(reinterpret_cast<uint64_t *>(c->bvol), c->nvb, 0, s);
-    launch_fill_i32(c->bcnt, c->nvb, 0, s);
+    launch_fill_u64(c->wvol, orphan_words(c->nvb), 0, s);
     if ((rc = halloc(c, &c->h_edges, 2 * mb))) return rc;
     if ((rc = halloc(c, &c->h_bop, mb))) return rc;
     if ((rc = halloc(c, &c->h_bgid, mb))) return rc;
@@ -1049,8 +1047,10 @@ int merge_list(drsf_ctx *c) {
     if (c->nd_known - c->nfree_known > c->dcap / LIST_KEEP) {
         if ((rc = rebuild_store(c))) return rc;
     } else {
+        if (!c->osum && (rc = dalloc(c, &c->osum, FINISH_CAP))) return rc;
+        if (!c->wdeg && (rc = dalloc(c, &c->wdeg, c->nvb * (BLOCK / WAVE)))) return rc;
         if (!c->adeg && (rc = dalloc(c, &c->adeg, c->n))) return rc;
-        launch_count_edges(make_dev(c), c->adeg, c->list_len, c->stream);
+        launch_count_edges(make_dev(c), c->adeg, c->wdeg, c->list_len, c->stream);
         if (!c->adeg_on) {
             HIPCHK(c, hipStreamSynchronize(c->stream));
             drop_graphs(c);  // captured sequences hold the null pointer
@@ -1180,7 +1180,7 @@ void enqueue_update(drsf_ctx *c, int kind, bool profile, const Ctl *kc) {
         launch_boruvka(d, 0, c->bor_fast, units, ins, s);
     }
     mark(PH_ROOTING);
-    launch_sf_root(d, s);
+    launch_sf_root(d, c->opts.replacement_mode != 1, s);
     launch_sf_bfs(d, 0, c->bfs_fast, s);
     launch_orient_bfs(d, c->bfs_fast, s);
     if (c->lr_kinds & (1u << kind)) launch_superforest_lr(d, tour_rounds(c), c->bfs_fast, s);
@@ -1266,7 +1266,7 @@ int continue_update(drsf_ctx *c) {
             bad = true;
         }
         if (!bad) {
-            launch_sf_root(d, s);
+            launch_sf_root(d, c->opts.replacement_mode != 1, s);
             launch_sf_bfs(d, 0, c->bfs_fast, s);
             if ((rc = read_flags(lv))) return rc;
             bad = *(int32_t *)f != 0;
@@ -1700,10 +1700,10 @@ int64_t drsf_footprint(int32_t n, int64_t nnz, const drsf_opts *opts) {
     b += 4 * N * 2;                                                       // zrow, parent
     b += 16 * N + (N + 63) / 64 * 8;                                      // label, rep, tidx, owner; bitmap
     b += 49 * pcap + 40 * pcap + 16 * pcap + 16 * std::max(2 * pcap, N);  // pieces, tour, er, paths
-    b += 37 * mb + 8 * bh + 12 * lcap + 12 * dh + 4 * N;                          // batch, tables, inserted list
+    b += 37 * mb + 8 * bh + 12 * lcap + 12 * dh + 5 * N;                          // batch, tables, inserted list
     b += 32 * xcap + 8 * (xcap / TILE);                                   // cross lists
-    b += 24 * nvb + 40 * N + 40 * nvb * BLOCK + 8 * (ntiles + 1) + 4 * (2 * ntiles + 1) +
-         24 * ((nvb + BLOCK - 1) / BLOCK);                                // orphan scan
+    b += 16 * orphan_words(nvb) + 40 * N + 8 * (ntiles + 1) + 4 * (2 * ntiles + 1) +
+         24 * orphan_groups(nvb);                               // orphan scan
     return b + (1 << 20);
 }
 
@@ -2055,8 +2055,7 @@ int wait_oldest(drsf_ctx *c) {
         c->view.scan_orphans = (int32_t)k[C_OMODE];
         c->view.num_orphans = (int64_t)k[C_NORPH];
         if (c->adeg_on) {
-            c->view.orphan_slots = 0;
-            for (int i = 0; i < OSLOTS; i++) c->view.orphan_slots += (int64_t)k[C_OSLOTS + i];
+            c->view.orphan_slots = (int64_t)k[C_OSLOTS];
         } else {
             c->view.orphan_slots = (int64_t)k[C_OVOL] - (int64_t)OR_PAD * (int64_t)k[C_NORPH];
         }

@@ -121,10 +121,11 @@ __device__ __forceinline__ void min_i32(int32_t *addr, int32_t v) {
 
 // Hot-address atomics.  On this part an atomic request to one address is
 // serialised at the memory side (about 12 ns per request, where a request is
-// one wave instruction), so lanes of a wave that target the same address are
-// merged first: up to GROUP_ROUNDS times the lowest pending lane's target is
-// taken, every lane with that target joins the group, and the group issues a
-// single request.  Lanes left over issue their own.
+// one wave instruction), and all together they pass at some 14 per
+// nanosecond, so lanes that target the same address are merged first: up to
+// GROUP_ROUNDS times the lowest pending lane's target is taken, every lane
+// with that target joins the group, and the group issues a single request.
+// Lanes left over issue their own.
 constexpr int GROUP_ROUNDS = 4;
 
 __device__ __forceinline__ void group_min_u64(bool active, int32_t target, uint64_t val,
@@ -147,6 +148,59 @@ __device__ __forceinline__ void group_min_u64(bool active, int32_t target, uint6
     }
     if (active && arr[target] > val) atomicMin((unsigned long long *)&arr[target], (unsigned long long)val);
 }
+
+// The same merge over a workgroup's many (target, value) pairs: minima per
+// target in a small LDS table, then one global atomic per target met.  A
+// pair that finds no place within a few probes goes to memory by itself.
+// clear() once (with a barrier after it), then any number of add(), and
+// flush() by every thread of the workgroup, which leaves the table clear.
+constexpr int MIN_SLOTS = 1024;
+constexpr int MIN_PROBES = 8;
+struct MinTable {
+    int32_t id[MIN_SLOTS];
+    unsigned long long val[MIN_SLOTS];
+    int32_t used;
+    __device__ __forceinline__ void clear() {
+        if (threadIdx.x == 0) used = 0;
+        for (int s = threadIdx.x; s < MIN_SLOTS; s += blockDim.x) {
+            id[s] = -1;
+            val[s] = KEY_INF;
+        }
+    }
+    __device__ __forceinline__ void add(int32_t target, uint64_t v, uint64_t *arr) {
+        static_assert(MIN_SLOTS == 1 << 10, "the hash takes 10 bits");
+        uint32_t h = (uint32_t)target * 2654435769u >> 22;
+        for (int p = 0; p < MIN_PROBES; p++) {
+            const int32_t cur = atomicCAS(&id[h], -1, target);
+            if (cur == -1) atomicAdd(&used, 1);
+            if (cur == -1 || cur == target) {
+                atomicMin(&val[h], (unsigned long long)v);
+                return;
+            }
+            h = (h + 1) & (MIN_SLOTS - 1);
+        }
+        min_key(&arr[target], v);
+    }
+    __device__ __forceinline__ void flush(uint64_t *arr) {
+        __syncthreads();
+        for (int s = threadIdx.x; s < MIN_SLOTS; s += blockDim.x) {
+            const int32_t t = id[s];
+            if (t < 0) continue;
+            min_key(&arr[t], val[s]);
+            id[s] = -1;
+            val[s] = KEY_INF;
+        }
+        if (threadIdx.x == 0) used = 0;
+        __syncthreads();
+    }
+    // flush once the table is half full (every thread calls it)
+    __device__ __forceinline__ void flush_half(uint64_t *arr) {
+        __syncthreads();
+        const bool full = used >= MIN_SLOTS / 2;
+        __syncthreads();  // used is not written before every thread has read it
+        if (full) flush(arr);
+    }
+};
 
 // Push `item` onto the singly linked list headed by head[target]
 // (nxt[item] = previous head).  Grouped lanes are chained among themselves

@@ -64,6 +64,8 @@ struct Dev {
     int32_t *dhpos;          // [dhmask + 1] slot -> index in dkey
     uint64_t dhmask;
     int32_t *dfree;          // [dcap] positions of deleted list entries, C_NFREE of them
+    unsigned long long *osum;  // [FINISH_CAP] adeg over the orphans each label workgroup met
+    const unsigned long long *wdeg;  // [4 nvb] adeg over each wave's 64 vertices of a block
     const int32_t *adeg;     // [n] each vertex's edges when the inserted edges were last counted
                              // as merged, or null: its entries in the store
     // lower half of the same store (row v holds u < v, ascending; TOMB kept
@@ -73,19 +75,16 @@ struct Dev {
     int32_t *lcol;           // [eb]
     const uint32_t *twin;    // [eb] position in lcol of the mirror of each bcol entry
     const uint32_t *ltwin;   // [eb] position in bcol of the mirror of each lcol entry
-    // orphan adjacency scan (delete): per vertex block of BLOCK vertices the
-    // listed orphans and their slots, prefixes, the compacted list and, per
+    // orphan adjacency scan (delete): per word of the orphan bitmap the listed
+    // orphans and their slots, prefixes, the compacted list and, per
     // range of OR_W slots, the list index holding its first slot
     int64_t nvb;             // vertex blocks
-    int64_t *bvol;           // [nvb] slots of the block's orphans (zero between updates)
-    int32_t *bcnt;           // [nvb] listed orphans of the block (zero between updates)
-    int64_t *bpre;           // [nvb] slots before the block within its group of BLOCK blocks
-    int32_t *opre;           // [nvb] orphans before the block within its group
+    unsigned long long *wvol;  // [orphan_words] packed (slots, orphans) per word (zero between updates)
+    unsigned long long *wpre;  // [orphan_words] the same before the word within its group of BLOCK words
     unsigned long long *gsum;  // [ngroups] packed (slots, orphans) per group
     int64_t *gpre;             // [ngroups] slots before the group
     int64_t *gopre;            // [ngroups] orphans before the group
     OrphEnt *olist;          // [n] every orphan, vertex order
-    OrphEnt *ostage;         // [nvb * BLOCK] each block's orphans, compacted at the block's start
     int32_t *rstart;         // [2 ntiles + 1]
     unsigned long long *xcnt;  // [ntiles] cross edges found per range
     // forest.  Between updates rep[v] == label[v]; a delete recomputes rep as
@@ -252,9 +251,7 @@ constexpr int C_DEEP = C_COUNT + 12;
 constexpr int C_NFREE = C_COUNT + 13;
 constexpr int C_LISTED = C_COUNT + 14;
 constexpr int C_FREED = C_COUNT + 15;
-// adeg over the orphans, in OSLOTS partial sums (one word would be a hot address)
-constexpr int OSLOTS = 32;
-constexpr int C_OSLOTS = C_COUNT + 16;
+constexpr int C_OSLOTS = C_COUNT + 16;  // adeg over the orphans
 
 // Grid sizes.  Workgroups are dispatched at about 200-270 per microsecond
 // across the chip, so a kernel of many short workgroups is bound by
@@ -284,6 +281,14 @@ constexpr int COPY_CAP = DRSF_COPY_CAP;      // rep <- parent beside the store u
 #endif
 constexpr int CLEANUP_CAP = DRSF_CLEANUP_CAP;  // cleanup (its workgroups share one arrival counter)
 int grid_for(int64_t items, int64_t per_block, int cap = GRID_CAP);
+// workgroups that set the labels of a delete
+__host__ __device__ inline int64_t label_groups(int64_t n) {
+    const int64_t g = (n + BLOCK - 1) / BLOCK;
+    return g < FINISH_CAP ? g : FINISH_CAP;
+}
+// words of the orphan bitmap (whole vertex blocks), and their groups of BLOCK
+__host__ __device__ inline int64_t orphan_words(int64_t nvb) { return nvb * (BLOCK / WAVE); }
+__host__ __device__ inline int64_t orphan_groups(int64_t nvb) { return (orphan_words(nvb) + BLOCK - 1) / BLOCK; }
 int64_t delta_tiles(int64_t count);
 int64_t insert_regions(int64_t b);
 
@@ -296,8 +301,8 @@ void launch_dedupe(const Dev &d, hipStream_t s);  // repeated pairs inside the b
 void launch_prepare(const Dev &d, bool del, hipStream_t s);  // with rep <- parent when del
 void launch_register(const Dev &d, hipStream_t s);
 void launch_insert_emit(const Dev &d, hipStream_t s);
-// adeg: every vertex's live edges in the store and the list
-void launch_count_edges(const Dev &d, int32_t *adeg, int64_t list, hipStream_t s);
+// adeg: every vertex's live edges in the store and the list; wdeg: over each 64 vertices
+void launch_count_edges(const Dev &d, int32_t *adeg, unsigned long long *wdeg, int64_t list, hipStream_t s);
 // the list's hash index from its live entries (deleted keys leave it)
 void launch_rehash(const Dev &d, int64_t count, hipStream_t s);
 // pointer-jumping rounds over rep before the chase (deep forests); a round
@@ -313,7 +318,8 @@ void launch_sweep_delta(const Dev &d, hipStream_t s);
 // rounds [r0, r1); emit: round 0 also emits the insert cross edges
 // (k_insert_emit not launched)
 void launch_boruvka(const Dev &d, int r0, int r1, int64_t units, bool emit, hipStream_t s);
-void launch_sf_root(const Dev &d, hipStream_t s);
+// count: also the number of cross edges found (the supergraph counts its own)
+void launch_sf_root(const Dev &d, bool count, hipStream_t s);
 void launch_sf_bfs(const Dev &d, int l0, int l1, hipStream_t s);
 void launch_orient_bfs(const Dev &d, int levels, hipStream_t s);
 // the super-forest's Euler tour when the search of `levels` levels did not

@@ -132,8 +132,7 @@ __device__ __forceinline__ void init_piece(const Dev &d, int64_t id, int32_t v, 
     d.pmin[id] = v;
     d.comp[id] = (int32_t)id;
     d.hook[id] = HOOK_NONE;
-    d.best[id] = KEY_INF;
-    d.best[d.pcap + id] = KEY_INF;
+    d.best[id] = d.best[d.pcap + id] = keep ? 0 : KEY_INF;
     d.srkey[id] = KEY_INF;
     d.head[id] = NONE;
     d.newlab[id] = v;
@@ -588,6 +587,16 @@ __global__ __launch_bounds__(BLOCK) void k_live_edges(Dev d, int32_t *adeg) {
     }
 }
 
+// and over every 64 vertices (a word of the orphan bitmap)
+__global__ __launch_bounds__(BLOCK) void k_word_edges(Dev d, const int32_t *adeg, unsigned long long *wdeg) {
+    for (int64_t blk = blockIdx.x; blk < d.nvb; blk += gridDim.x) {
+        const int64_t v = blk * BLOCK + threadIdx.x;
+        unsigned long long x = v < d.n ? (unsigned long long)adeg[v] : 0;
+        for (int o = WAVE / 2; o > 0; o >>= 1) x += __shfl_xor(x, o);
+        if (lane_id() == 0) wdeg[v / WAVE] = x;
+    }
+}
+
 // The inserted-edge index again from the list's live entries (the table has
 // been cleared): deleted keys' slots lengthen the probes of absent keys, so
 // the host queues this once they could fill half of the table.
@@ -644,27 +653,26 @@ __global__ __launch_bounds__(BLOCK) void k_insert_emit(Dev d) {
 
 // rep[v] <- root of v in F-hat.  Each thread chases rep[] upward; entries
 // already finished by other threads are roots, so chains shorten as the
-// sweep proceeds (pointer jumping, Algorithm 1).  A chase longer than a few
-// steps also publishes its progress in rep[v] after every step, so the
+// sweep proceeds (pointer jumping, Algorithm 1).  A chase longer than a
+// step also publishes its progress in rep[v] after every step, so the
 // chases of v's descendants jump over what v has covered: on deep trees
 // (long paths of vertices chased at the same time) a chain then takes
 // about log of its length in steps instead of half of it.  Every value
 // read or published is an ancestor of the vertex, so stale reads only cost
-// extra steps.  A thread
-// can take REP_CH vertex blocks at a time and interleave their chases and
-// the loads that follow (on gfx950 one block at a time measures fastest:
-// the whole grid is resident, so more chains per thread add no overlap).
-// Marks vertices whose root is not their old root (they lie in a
-// piece cut off by the batch), stages each block's such orphans, compacted
-// at the block's start, with their adjacency runs, their piece and their
-// old root's piece for the orphan scan, and lowers each orphan piece's
-// smallest vertex.  (Loading the next block's rep and label before the
-// chase of the current one measured slower.)
-#ifndef DRSF_REP_CH
-#define DRSF_REP_CH 1
-#endif
-constexpr int REP_CH = DRSF_REP_CH;
-constexpr int PUBLISH_AFTER = 4;  // steps before a chase publishes its progress (short chains never do)
+// extra steps.  Bound by those dependent reads, then, where most vertices
+// are orphans, by the atomics on their pieces' smallest vertices (so those
+// are looked at first).  A thread takes CH vertices, their chases and the
+// loads that follow interleaved: one while the grid holds every vertex block
+// at once (n up to 2^20; G(1e6, 4e6), depth 800: 79 us, two 86), two on
+// larger graphs, whose later blocks then start sooner (4096^2 grid, depth
+// 8000 and more: one 477 us, two 352, four 776; R-MAT 22: 30 either way;
+// 256 graphs: 85 and 77).  Also marks vertices whose root is not their old
+// root (they lie in a piece cut off by the batch), counts each bitmap word's
+// such orphans and their adjacency slots for the orphan scan, and lowers each
+// orphan piece's smallest vertex.  (Loading the next block's rep and label
+// before the chase of the current one measured slower.)
+constexpr int PUBLISH_AFTER = 1;  // steps before a chase publishes its progress (the shortest never do)
+constexpr int64_t CHASE_ONE = 4096;  // vertex blocks up to which a thread takes one vertex at a time
 #ifndef DRSF_DEEP_STEPS
 #define DRSF_DEEP_STEPS 1024
 #endif
@@ -696,6 +704,7 @@ __global__ __launch_bounds__(BLOCK) void k_rep_jump(Dev d, int k) {
     }
     if (__ballot(changed) != 0 && lane_id() == 0) d.cnt[C_JUMP_ROUND + k] = 1;
 }
+template <int REP_CH>
 __global__ __launch_bounds__(BLOCK) void k_rep_chase(Dev d) {
     if (stopped(d) || !d.ctl->has_del) return;
     const int64_t nb = (d.n + BLOCK - 1) / BLOCK;
@@ -739,60 +748,39 @@ __global__ __launch_bounds__(BLOCK) void k_rep_chase(Dev d) {
         // wave, and only then): its later deletes queue jumping rounds first
         if (__ballot(steps > DEEP_STEPS) != 0 && lane_id() == 0) d.cnt[C_DEEP] = 1;
         bool orphan[REP_CH];
-        int32_t t[REP_CH], tk[REP_CH];
-        uint32_t us[REP_CH], ls[REP_CH];
-        int32_t du[REP_CH], dl[REP_CH];
+        int32_t t[REP_CH];
+        uint32_t u0[REP_CH], u1[REP_CH], l0[REP_CH], l1[REP_CH];
 #pragma unroll
         for (int k = 0; k < REP_CH; k++) {
             orphan[k] = live[k] && x[k] != lab[k];
             if (live[k]) d.rep[v[k]] = x[k];
-            const uint64_t word = __ballot(orphan[k]);
-            if (lane_id() == 0 && live[k]) d.obits[v[k] >> 6] = word;
-            t[k] = tk[k] = NONE;
-            us[k] = ls[k] = 0;
-            du[k] = dl[k] = 0;
+            t[k] = NONE;
+            u0[k] = u1[k] = l0[k] = l1[k] = 0;
             if (orphan[k]) {
                 t[k] = d.tidx[x[k]];
-                tk[k] = d.tidx[lab[k]];  // the old root: a piece of its own
-                us[k] = d.bptr[v[k]];
-                ls[k] = d.lptr[v[k]];
-                du[k] = (int32_t)d.bptr[v[k] + 1];
-                dl[k] = (int32_t)d.lptr[v[k] + 1];
+                u0[k] = d.bptr[v[k]];
+                u1[k] = d.bptr[v[k] + 1];
+                l0[k] = d.lptr[v[k]];
+                l1[k] = d.lptr[v[k] + 1];
             }
         }
+        int32_t pm[REP_CH];
+#pragma unroll
+        for (int k = 0; k < REP_CH; k++) pm[k] = orphan[k] && t[k] >= 0 ? d.pmin[t[k]] : 0;
 #pragma unroll
         for (int k = 0; k < REP_CH; k++) {
-            if (blk[k] < 0) continue;  // uniform over the block
-            if (orphan[k]) {
-                if (t[k] < 0 || tk[k] < 0) atomicOr(d.status, ST_WALK_BOUND);
-                du[k] -= (int32_t)us[k];
-                dl[k] -= (int32_t)ls[k];
-            }
-            // the block's orphans with their adjacency runs (plus padding)
-            // and the block's totals
-            unsigned long long tot;
-            const unsigned long long off = block_excl_scan64(
-                orphan[k] ? opack((unsigned long long)(du[k] + dl[k] + OR_PAD), 1) : 0, &tot);
-            if (orphan[k]) {
-                OrphEnt o;
-                o.pre = (int64_t)ovol(off);
-                o.ustart = us[k];
-                o.lstart = ls[k];
-                o.v = (int32_t)v[k];
-                o.du = du[k];
-                o.dl = dl[k];
-                o.pu = t[k];
-                o.ru = x[k];
-                o.pk = tk[k];
-                d.ostage[blk[k] * BLOCK + (int64_t)ocnt(off)] = o;
-            }
-            if (threadIdx.x == 0) {
-                d.bvol[blk[k]] = (int64_t)ovol(tot);
-                d.bcnt[blk[k]] = (int32_t)ocnt(tot);
-            }
-            // smallest vertex of each orphan piece; consecutive ids often
-            // share a piece
-            const bool grp = orphan[k] && t[k] >= 0;
+            const uint64_t word = __ballot(orphan[k]);
+            if (lane_id() == 0 && live[k]) d.obits[v[k] >> 6] = word;
+            if (word == 0) continue;  // uniform over the wave
+            if (orphan[k] && t[k] < 0) atomicOr(d.status, ST_WALK_BOUND);
+            // the word's orphans and their adjacency slots (plus padding)
+            unsigned long long vol =
+                orphan[k] ? (unsigned long long)(u1[k] - u0[k]) + (l1[k] - l0[k]) + OR_PAD : 0;
+            for (int o = WAVE / 2; o > 0; o >>= 1) vol += __shfl_xor(vol, o);
+            if (lane_id() == 0) d.wvol[v[k] >> 6] = opack(vol, (unsigned long long)__popcll(word));
+            // smallest vertex of each orphan piece: mostly known already from
+            // a lower id (it only falls); consecutive ids often share a piece
+            const bool grp = orphan[k] && t[k] >= 0 && pm[k] > (int32_t)v[k];
             uint64_t rem = __ballot(grp);
             bool pending = grp;
             for (int round = 0; round < GROUP_ROUNDS && rem; round++) {
@@ -1044,27 +1032,23 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_delta(Dev d) {
 // old root have equal reps), so scanning the whole adjacency of the orphan
 // vertices finds every cross edge of the base store; when the orphans hold
 // few slots this replaces the sweep of the whole store.  Root finding left,
-// per vertex block, the block's orphans and their slots.  Prefixes over the
-// blocks are taken in two levels: within groups of BLOCK blocks here, then
-// over the groups in k_orph_total.
+// per word of the orphan bitmap, the word's orphans and their slots.
+// Prefixes over the words are taken in two levels: within groups of BLOCK
+// words here, then over the groups in k_orph_total.
 __global__ __launch_bounds__(BLOCK) void k_orph_plan(Dev d) {
     if (stopped(d) || !d.ctl->has_del) return;
-    const int64_t b = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-    const unsigned long long x =
-        b < d.nvb ? opack((unsigned long long)d.bvol[b], (unsigned long long)d.bcnt[b]) : 0;
+    const int64_t w = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+    const unsigned long long x = w < orphan_words(d.nvb) ? d.wvol[w] : 0;
     unsigned long long tot;
     const unsigned long long pre = block_excl_scan64(x, &tot);
-    if (b < d.nvb) {
-        d.bpre[b] = (int64_t)ovol(pre);
-        d.opre[b] = (int32_t)ocnt(pre);
-    }
+    if (w < orphan_words(d.nvb)) d.wpre[w] = pre;
     if (threadIdx.x == 0) d.gsum[blockIdx.x] = tot;
 }
 
 // Prefix over the groups, the totals and the choice of scan.
 __global__ __launch_bounds__(BLOCK) void k_orph_total(Dev d) {
     if (stopped(d) || !d.ctl->has_del) return;
-    const int64_t ng = (d.nvb + BLOCK - 1) / BLOCK;
+    const int64_t ng = orphan_groups(d.nvb);
     const int64_t per = (ng + BLOCK - 1) / BLOCK;
     const int64_t g0 = (int64_t)threadIdx.x * per;
     const int64_t g1 = g0 + per < ng ? g0 + per : ng;
@@ -1090,34 +1074,68 @@ __global__ __launch_bounds__(BLOCK) void k_orph_total(Dev d) {
     }
 }
 
-// Compacted list of all orphans in vertex order (copied from the blocks'
-// staging with global prefixes), each orphan's piece in owner[], and for
-// each range of OR_W slots the list index of the orphan holding its first
-// slot.
+// Compacted list of all orphans in vertex order, each orphan's piece in
+// owner[], and for each range of OR_W slots the list index of the orphan
+// holding its first slot.  FILL_LANES lanes take a word's orphans, that many
+// at a time (most words hold few).  Nothing is staged by root finding: where
+// most vertices are orphans the store is swept instead and no list is made
+// (40 bytes a vertex, 0.67 GB of the 16.7e6-vertex grid's root finding).
 __global__ __launch_bounds__(BLOCK) void k_orph_fill(Dev d) {
     if (stopped(d) || !d.ctl->has_del || !d.cnt[C_OMODE]) return;
-    // FILL_LANES lanes per vertex block (blocks hold few orphans), so one
-    // wave covers WAVE / FILL_LANES blocks with all its loads in flight
     constexpr int FILL_LANES = 8;
+    constexpr int WPB = BLOCK / WAVE;  // words per vertex block
     const int64_t per_block = BLOCK / FILL_LANES;
     const int sub = threadIdx.x % FILL_LANES;
     const int64_t nvl_list = d.ctl->nvl;  // read once: stores below may alias it
     for (int64_t j = (int64_t)blockIdx.x * per_block + threadIdx.x / FILL_LANES;;
          j += (int64_t)gridDim.x * per_block) {
-        const int64_t blk = list_block(d.vlist, nvl_list, j, d.nvb);
+        const int64_t blk = list_block(d.vlist, nvl_list, j / WPB, d.nvb);
         if (blk < 0) break;
-        const int32_t nc = d.bcnt[blk];
-        if (nc == 0) continue;
-        const int64_t ob = d.gopre[blk / BLOCK] + d.opre[blk];
-        const int64_t vb = d.gpre[blk / BLOCK] + d.bpre[blk];
-        for (int32_t i = sub; i < nc; i += FILL_LANES) {
-            OrphEnt o = d.ostage[blk * BLOCK + i];
-            const int64_t idx = ob + i;
-            o.pre += vb;
-            d.olist[idx] = o;
-            d.owner[o.v] = o.pu;  // the orphan's piece, for the orphan scan
-            const int64_t end = o.pre + o.du + o.dl + OR_PAD;
-            for (int64_t w = (o.pre + OR_W - 1) / OR_W; w * OR_W < end; w++) d.rstart[w] = (int32_t)idx;
+        const int64_t w = blk * WPB + j % WPB;
+        if (w * WAVE >= d.n) continue;
+        uint64_t bits = d.obits[w];
+        if (bits == 0) continue;
+        const unsigned long long pre = d.wpre[w];
+        int64_t idx = d.gopre[w / BLOCK] + (int64_t)ocnt(pre);
+        int64_t vb = d.gpre[w / BLOCK] + (int64_t)ovol(pre);
+        while (bits) {  // uniform over the lanes of the word
+            uint64_t m = bits;
+            for (int i = 0; i < FILL_LANES; i++) {
+                if (i < sub) m &= m - 1;
+                bits &= bits - 1;
+            }
+            const bool act = m != 0;  // this lane's orphan: the sub-th left
+            OrphEnt o;
+            o.v = act ? (int32_t)(w * WAVE) + __ffsll((unsigned long long)m) - 1 : 0;
+            o.du = o.dl = 0;
+            int64_t size = 0;
+            if (act) {
+                o.ru = d.rep[o.v];
+                const int32_t lab = d.label[o.v];
+                o.ustart = d.bptr[o.v];
+                o.lstart = d.lptr[o.v];
+                o.du = (int32_t)(d.bptr[o.v + 1] - o.ustart);
+                o.dl = (int32_t)(d.lptr[o.v + 1] - o.lstart);
+                o.pu = d.tidx[o.ru];
+                o.pk = d.tidx[lab];  // the old root: a piece of its own
+                if (o.pk < 0) atomicOr(d.status, ST_WALK_BOUND);
+                size = (int64_t)o.du + o.dl + OR_PAD;
+            }
+            int64_t inc = size;
+#pragma unroll
+            for (int s = 1; s < FILL_LANES; s <<= 1) {
+                const int64_t y = __shfl_up(inc, s, FILL_LANES);
+                if (sub >= s) inc += y;
+            }
+            if (act) {
+                o.pre = vb + inc - size;
+                d.olist[idx + sub] = o;
+                d.owner[o.v] = o.pu;  // the orphan's piece, for the orphan scan
+                const int64_t end = o.pre + size;
+                for (int64_t r = (o.pre + OR_W - 1) / OR_W; r * OR_W < end; r++) d.rstart[r] = (int32_t)(idx + sub);
+            }
+            vb += __shfl(inc, FILL_LANES - 1, FILL_LANES);
+            idx += FILL_LANES;  // past the end only after the last
         }
     }
 }
@@ -1372,16 +1390,50 @@ __global__ __launch_bounds__(BLOCK) void k_orph_scan(Dev d) {
 __device__ __forceinline__ uint64_t hook_pack(int r, int32_t other) {
     return ((uint64_t)(uint32_t)r << 32) | (uint32_t)other;
 }
-__device__ int32_t comp_root(const Dev &d, int32_t x, uint32_t r, int64_t np) {
+// Long chains are shortened on the way: an entry passed is made to point two
+// hooks up, with its own tag (any ancestor a concurrent reader sees will do).
+// On a grid, where pieces hook along whole rows, the edges' walks otherwise
+// repeat chains of hundreds of hooks.
+__device__ __forceinline__ int32_t hook_to(uint64_t h) { return (int32_t)(uint32_t)h; }
+__device__ __forceinline__ bool hooked(uint64_t h, uint32_t r) { return (uint32_t)(h >> 32) < r; }
+// N pieces at once, their loads in flight together; entries that are not `on`
+// stay as they are
+template <int N>
+__device__ __forceinline__ void comp_roots(const Dev &d, const bool (&on)[N], int32_t (&x)[N], uint32_t r,
+                                           int64_t np) {
+    uint64_t h[N];
+    bool go[N];
+#pragma unroll
+    for (int k = 0; k < N; k++) h[k] = d.hook[on[k] ? x[k] : 0];
+#pragma unroll
+    for (int k = 0; k < N; k++) go[k] = on[k] && hooked(h[k], r);
     for (int64_t steps = 0;; steps++) {
-        const uint64_t h = d.hook[x];
-        if ((uint32_t)(h >> 32) >= r) return x;  // a root then (HOOK_NONE has the largest tag)
-        x = (int32_t)(uint32_t)h;
+        bool more = false;
+        uint64_t h2[N];
+#pragma unroll
+        for (int k = 0; k < N; k++) h2[k] = d.hook[go[k] ? hook_to(h[k]) : 0];
+#pragma unroll
+        for (int k = 0; k < N; k++) {
+            if (!go[k]) continue;
+            const int32_t y = hook_to(h[k]);
+            go[k] = hooked(h2[k], r);
+            if (go[k]) d.hook[x[k]] = (h[k] & 0xffffffff00000000ull) | (uint32_t)hook_to(h2[k]);
+            x[k] = y;
+            h[k] = h2[k];
+            more |= go[k];
+        }
+        if (!more) return;
         if (steps > np) {
             atomicOr(d.status, ST_WALK_BOUND);
-            return x;
+            return;
         }
     }
+}
+__device__ __forceinline__ int32_t comp_root(const Dev &d, int32_t x, uint32_t r, int64_t np) {
+    const bool on[1] = {true};
+    int32_t c[1] = {x};
+    comp_roots(d, on, c, r, np);
+    return c[0];
 }
 // the buffer of best[] that round r selects into
 __device__ __forceinline__ uint64_t *best_of(const Dev &d, int r) { return d.best + (r & 1) * d.pcap; }
@@ -1391,66 +1443,105 @@ __device__ __forceinline__ uint64_t *best_of(const Dev &d, int r) { return d.bes
 // edge lies inside one old component, whose root piece is unique, so every
 // live edge touches a component without one, which selects; each selected
 // edge is the lowest key leaving its component (cut property), so the
-// chosen set is still the Kruskal one.
-__device__ __forceinline__ void select_edge(const Dev &d, bool live, const Cross &e, int32_t ca,
-                                            int32_t cb, uint64_t *best) {
-    const bool sa = live && !d.pkeep[ca], sb = live && !d.pkeep[cb];
-    group_min_u64(sa, ca, e.key, best);
-    group_min_u64(sb, cb, e.key, best);
+// chosen set is still the Kruskal one.  Such a component is never hooked
+// itself, so its root is the old root's piece, whose best[] holds 0, below
+// every key.
+__device__ __forceinline__ uint64_t no_key(const Dev &d, int32_t p) { return d.pkeep[p] ? 0 : KEY_INF; }
+// one edge per lane, merged within the wave
+__device__ __forceinline__ void select_edge(bool live, const Cross &e, int32_t ca, int32_t cb, uint64_t *best) {
+    // values only fall, so one already below cannot be lowered
+    const bool sa = live && best[ca] > e.key, sb = live && best[cb] > e.key;
+    if (__ballot(sa)) group_min_u64(sa, ca, e.key, best);
+    if (__ballot(sb)) group_min_u64(sb, cb, e.key, best);
 }
 
+constexpr int SEL_K = 4;                 // edges a thread takes at a time
+constexpr int SEL_UNIT = SEL_K * BLOCK;  // edges per unit of a dense list
+
+// The regions of x0 that hold this update's cross edges, and a workgroup's
+// share of them: a run of consecutive ones, so that the workgroup's minima
+// meet in its LDS table before they go to memory (edges stored near each
+// other join the same pieces).  When the orphan scan ran they are its own
+// regions, then those behind the base store's; else all from rlo.
+struct Regions {
+    int64_t om, rlo2, i0, i1;
+    __device__ __forceinline__ Regions(const Dev &d, bool with_scan) {
+        const bool scan = d.cnt[C_OMODE] != 0;
+        om = scan && with_scan ? or_regions((int64_t)d.cnt[C_OVOL], d.eb) : 0;
+        rlo2 = scan && d.ctl->rlo < d.ntiles ? d.ntiles : d.ctl->rlo;
+        const int64_t total = om + (d.ctl->rhi > rlo2 ? d.ctl->rhi - rlo2 : 0);
+        const int64_t per = (total + gridDim.x - 1) / gridDim.x;
+        i0 = blockIdx.x * per < total ? blockIdx.x * per : total;
+        i1 = i0 + per < total ? i0 + per : total;
+    }
+    __device__ __forceinline__ int64_t at(int64_t i) const { return i < om ? i : rlo2 + (i - om); }
+};
+
 // Round 0: every cross edge is live and every component is a single piece.
-// Workgroups take the regions [rlo, rhi) of x0 in turn.  With emit, the
-// insert regions are not filled yet: a workgroup taking one runs the insert
-// emit for its batch entries (writing the region for the next round) and
-// selects on the edges it found, and adds its count to the statistic.
-// Workgroup 0 sums the other region lengths (the cross edges found).
+// Regions that the orphan scan wrote are left out: their edges took part in
+// this round's selection already.  With emit, the insert regions are not
+// filled yet: a workgroup taking one runs the insert emit for its batch
+// entries (writing the region for the next round) and selects on the edges it
+// found.  Bound by the atomics that reach memory (2.9e6 cross edges of
+// G(1e6, 4e6): 128 us with minima merged per wave, 38 with the LDS table).
 __global__ __launch_bounds__(BLOCK) void k_bor_round0(Dev d, int emit) {
     if (stopped(d)) return;
-    // regions below ntiles hold the orphan scan's output when it ran: those
-    // edges took part in this round's selection already
-    const bool om = d.cnt[C_OMODE] != 0;
-    const int64_t rhi = d.ctl->rhi;
-    const int64_t rlo = om ? (d.ctl->rlo > d.ntiles ? d.ctl->rlo : d.ntiles) : d.ctl->rlo;
+    __shared__ MinTable s_min;
+    __shared__ int64_t s_cnt[BLOCK];
+    s_min.clear();
+    const Regions reg(d, false);
     const bool ins_here = emit && d.ctl->has_ins;
     const int64_t ib = d.ctl->ibase, ie = ins_here ? ib + (d.ctl->b + BLOCK - 1) / BLOCK : ib;
-    for (int64_t t = rlo + blockIdx.x; t < rhi; t += gridDim.x) {
-        if (t >= ib && t < ie) {  // uniform over the workgroup
-            Cross e;
-            int total;
-            const bool live = insert_emit_block(d, t - ib, &e, &total);
-            select_edge(d, live, e, e.pa, e.pb, d.best);
-            if (threadIdx.x == 0 && total) atomicAdd(&d.cnt[C_NCROSS], (unsigned long long)total);
-            continue;
-        }
-        const int64_t cntr = (int64_t)d.rcnt[t];
-        const Cross *in = d.x0 + t * TILE;
-        for (int64_t base = 0; base < cntr; base += BLOCK) {
-            const int64_t i = base + threadIdx.x;
-            const bool live = i < cntr;
-            Cross e;
-            e.pa = e.pb = 0;
-            e.key = 0;
-            if (live) e = in[i];
-            select_edge(d, live, e, e.pa, e.pb, d.best);
+    for (int64_t w = reg.i0; w < reg.i1; w += BLOCK) {
+        const int64_t mine = w + threadIdx.x;  // the counts of this run, loaded together
+        __syncthreads();
+        s_cnt[threadIdx.x] = mine < reg.i1 ? (int64_t)d.rcnt[reg.at(mine)] : 0;
+        __syncthreads();
+        for (int64_t i = w; i < reg.i1 && i < w + BLOCK; i++) {
+            const int64_t t = reg.at(i);
+            if (t >= ib && t < ie) {  // uniform over the workgroup
+                Cross e;
+                int total;
+                if (insert_emit_block(d, t - ib, &e, &total)) {
+                    s_min.add(e.pa, e.key, d.best);
+                    s_min.add(e.pb, e.key, d.best);
+                }
+                s_min.flush_half(d.best);
+                continue;
+            }
+            const int64_t cntr = s_cnt[i - w];
+            const Cross *in = d.x0 + t * TILE;
+            for (int64_t base = 0; base < cntr; base += SEL_UNIT) {
+                Cross e[SEL_K];
+                bool live[SEL_K];
+#pragma unroll
+                for (int k = 0; k < SEL_K; k++) {
+                    const int64_t q = base + k * BLOCK + threadIdx.x;
+                    live[k] = q < cntr;
+                    if (live[k]) e[k] = in[q];
+                }
+#pragma unroll
+                for (int k = 0; k < SEL_K; k++)
+                    if (live[k]) {
+                        s_min.add(e[k].pa, e[k].key, d.best);
+                        s_min.add(e[k].pb, e[k].key, d.best);
+                    }
+                s_min.flush_half(d.best);
+            }
         }
     }
-    if (blockIdx.x == 0) {
-        unsigned long long s = 0;
-        for (int64_t r = rlo + threadIdx.x; r < rhi; r += BLOCK)
-            if (r < ib || r >= ie) s += d.rcnt[r];
-        if (om) {
-            const int64_t nr = or_regions((int64_t)d.cnt[C_OVOL], d.eb);
-            for (int64_t r = threadIdx.x; r < nr; r += BLOCK) s += d.xcnt[r];
-        }
-        for (int o = WAVE / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
-        if (lane_id() == 0 && s) atomicAdd(&d.cnt[C_NCROSS], s);
-    }
+    s_min.flush(d.best);
 }
 
 // Round r >= 1: drop cross edges now inside one component, select again, and
 // compact the survivors into a dense list.  Round 1 reads the regions of x0;
 // later rounds alternate dense lists (out: x1 on odd rounds, x0 on even).
+// Bound by the latency of the dependent gathers (edge, hooks) and the atomics
+// of the selection, so each thread takes SEL_K edges at a time and minima are
+// merged in LDS.  A unit's survivors are first packed into its own front
+// (entries already read) and then copied, so that the list's length, a hot
+// address, costs one atomic per unit of up to 4096 edges instead of one per
+// 256 (2.9e6 cross edges of G(1e6, 4e6): 193 -> 75 us).
 __global__ __launch_bounds__(BLOCK) void k_bor_select(Dev d, int r) {
     if (stopped(d) || d.cnt[C_DONE_BOR]) return;
     Cross *out = (r & 1) ? d.x1 : d.x0;
@@ -1458,52 +1549,81 @@ __global__ __launch_bounds__(BLOCK) void k_bor_select(Dev d, int r) {
     const int64_t np = (int64_t)d.cnt[C_NP];
     uint64_t *best = best_of(d, r);
     __shared__ unsigned long long obase;
-    // work units: regions of x0 (round 1) or BLOCK-sized chunks of a dense list
-    int64_t u0, u1;
-    const Cross *dense = (r & 1) ? d.x0 : d.x1;
-    int64_t dcount = 0;
-    if (r == 1) {
-        u0 = d.ctl->rlo;
-        u1 = d.ctl->rhi;
-    } else {
+    __shared__ MinTable s_min;
+    __shared__ int64_t s_cnt[BLOCK];
+    s_min.clear();
+    // work units: regions of x0 (round 1) or chunks of a dense list
+    const Regions reg(d, true);
+    Cross *dense = (r & 1) ? d.x0 : d.x1;
+    int64_t dcount = 0, u0 = reg.i0, u1 = reg.i1, step = 1;
+    if (r > 1) {
         dcount = (int64_t)d.cnt[(r & 1) ? C_NX0 : C_NX1];
-        u0 = 0;
-        u1 = (dcount + BLOCK - 1) / BLOCK;
+        u0 = blockIdx.x;
+        u1 = (dcount + SEL_UNIT - 1) / SEL_UNIT;
+        step = gridDim.x;
     }
-    for (int64_t unit = u0 + blockIdx.x; unit < u1; unit += gridDim.x) {
-        const Cross *in;
+    for (int64_t unit = u0; unit < u1; unit += step) {
+        Cross *in;
         int64_t count;
         if (r == 1) {
-            in = d.x0 + unit * TILE;
-            count = (int64_t)d.rcnt[unit];
-        } else {
-            in = dense + unit * BLOCK;
-            count = dcount - unit * BLOCK < BLOCK ? dcount - unit * BLOCK : BLOCK;
-        }
-        for (int64_t base = 0; base < count; base += BLOCK) {
-            const int64_t i = base + threadIdx.x;
-            bool live = false;
-            Cross e;
-            e.key = 0;
-            e.pa = e.pb = 0;
-            int32_t ca = 0, cb = 0;
-            if (i < count) {
-                e = in[i];  // ends: pieces (round 1) or components at the last round's start
-                ca = comp_root(d, e.pa, (uint32_t)r, np);
-                cb = comp_root(d, e.pb, (uint32_t)r, np);
-                live = ca != cb;
+            if ((unit - u0) % BLOCK == 0) {  // the counts of the next units, loaded together
+                const int64_t mine = unit + threadIdx.x;
+                __syncthreads();
+                s_cnt[threadIdx.x] = mine < u1 ? (int64_t)d.rcnt[reg.at(mine)] : 0;
             }
-            select_edge(d, live, e, ca, cb, best);
-            e.pa = ca;
-            e.pb = cb;
-            int total;
-            const int off = block_excl_scan(live ? 1 : 0, &total);
-            if (threadIdx.x == 0) obase = total ? atomicAdd(cout, (unsigned long long)total) : 0ull;
             __syncthreads();
-            if (live) out[obase + off] = e;
-            __syncthreads();
+            in = d.x0 + reg.at(unit) * TILE;
+            count = s_cnt[(unit - u0) % BLOCK];
+        } else {
+            in = dense + unit * SEL_UNIT;
+            count = dcount - unit * SEL_UNIT < SEL_UNIT ? dcount - unit * SEL_UNIT : SEL_UNIT;
         }
+        int64_t kept = 0;
+        for (int64_t base = 0; base < count; base += SEL_UNIT) {
+            Cross e[SEL_K];
+            bool on[2 * SEL_K];
+            int32_t c[2 * SEL_K];  // ends: pieces (round 1) or components at the last round's start
+#pragma unroll
+            for (int k = 0; k < SEL_K; k++) {
+                const int64_t i = base + k * BLOCK + threadIdx.x;
+                on[2 * k] = on[2 * k + 1] = i < count;
+                e[k].key = 0;
+                e[k].pa = e[k].pb = 0;
+                if (i < count) e[k] = in[i];
+                c[2 * k] = e[k].pa;
+                c[2 * k + 1] = e[k].pb;
+            }
+            comp_roots(d, on, c, (uint32_t)r, np);
+            bool live[SEL_K];
+            int mine = 0;
+#pragma unroll
+            for (int k = 0; k < SEL_K; k++) {
+                live[k] = on[2 * k] && c[2 * k] != c[2 * k + 1];
+                mine += live[k];
+                if (live[k]) {
+                    s_min.add(c[2 * k], e[k].key, best);
+                    s_min.add(c[2 * k + 1], e[k].key, best);
+                }
+            }
+            int total;
+            int64_t at = kept + block_excl_scan(mine, &total);  // its barriers end this chunk's reads
+#pragma unroll
+            for (int k = 0; k < SEL_K; k++)
+                if (live[k]) {
+                    e[k].pa = c[2 * k];
+                    e[k].pb = c[2 * k + 1];
+                    in[at++] = e[k];
+                }
+            kept += total;
+            s_min.flush_half(best);
+        }
+        if (kept == 0) continue;  // uniform over the workgroup
+        if (threadIdx.x == 0) obase = atomicAdd(cout, (unsigned long long)kept);
+        __syncthreads();
+        for (int64_t i = threadIdx.x; i < kept; i += BLOCK) out[obase + i] = in[i];
+        __syncthreads();  // obase is reused by the next unit
     }
+    s_min.flush(best);
 }
 
 // Each selecting component hooks onto the component across its lowest-key
@@ -1530,10 +1650,10 @@ __global__ __launch_bounds__(BLOCK) void k_bor_hook(Dev d, int r) {
         bool rec = false;
         int4 er = make_int4(0, 0, 0, 0);
         if (p < np) {
-            next[p] = KEY_INF;
+            next[p] = no_key(d, (int32_t)p);
             // a root at this round's start (only p's own thread writes hook[p])
             const uint64_t k = d.hook[p] == HOOK_NONE ? best[p] : KEY_INF;
-            if (k != KEY_INF) {
+            if (k != KEY_INF && k != 0) {
                 const int32_t x = key_lo(k), y = key_hi(k);
                 const int32_t px = d.tidx[d.rep[x]], py = d.tidx[d.rep[y]];
                 if (px < 0 || py < 0) {
@@ -1596,7 +1716,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_bor_tail(Dev d, int r0) {
                 cb = comp_root(d, e.pb, (uint32_t)r, np);
                 live = ca != cb;
             }
-            select_edge(d, live, e, ca, cb, best);
+            select_edge(live, e, ca, cb, best);
             const uint64_t m = __ballot(live);
             if (m) {
                 const int leader = __ffsll((unsigned long long)m) - 1;
@@ -1622,8 +1742,8 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_bor_tail(Dev d, int r0) {
             int4 er[2] = {make_int4(0, 0, 0, 0), make_int4(0, 0, 0, 0)};
             if (i < nout) {
                 const Cross e = out[i];
-                nbest[e.pa] = KEY_INF;
-                nbest[e.pb] = KEY_INF;
+                nbest[e.pa] = no_key(d, e.pa);
+                nbest[e.pb] = no_key(d, e.pb);
                 for (int side = 0; side < 2; side++) {
                     const int32_t p = side ? e.pb : e.pa, other = side ? e.pa : e.pb;
                     if (best[p] != e.key) continue;
@@ -1656,11 +1776,23 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_bor_tail(Dev d, int r0) {
 // Super-root of each merged component: the piece holding its smallest
 // vertex (insert: the tree with the smallest root; delete: the piece that
 // kept the old root when present, since that root is the component's
-// minimum).  Runs only once the hooking rounds have finished.
-__global__ __launch_bounds__(BLOCK) void k_sf_root(Dev d) {
+// minimum).  Runs only once the hooking rounds have finished.  With `count`
+// the last workgroup only adds up the cross edges found (a statistic).
+__global__ __launch_bounds__(BLOCK) void k_sf_root(Dev d, int count) {
     if (stopped(d) || !d.cnt[C_DONE_BOR]) return;
+    if (count && blockIdx.x == gridDim.x - 1) {
+        const bool om = d.cnt[C_OMODE] != 0;
+        const int64_t rlo = om && d.ctl->rlo < d.ntiles ? d.ntiles : d.ctl->rlo, rhi = d.ctl->rhi;
+        const int64_t nr = om ? or_regions((int64_t)d.cnt[C_OVOL], d.eb) : 0;
+        unsigned long long s = 0;
+        for (int64_t r = rlo + threadIdx.x; r < rhi; r += BLOCK) s += d.rcnt[r];
+        for (int64_t r = threadIdx.x; r < nr; r += BLOCK) s += d.xcnt[r];
+        s = block_sum64(s);
+        if (threadIdx.x == 0) d.cnt[C_NCROSS] = s;
+        return;
+    }
     const int64_t np = (int64_t)d.cnt[C_NP];
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    const int64_t stride = (int64_t)(gridDim.x - count) * BLOCK;
     for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < np; base += stride) {
         const int64_t p = base + threadIdx.x;
         const bool act = p < np;
@@ -1889,34 +2021,37 @@ __global__ __launch_bounds__(BLOCK) void k_orient_lr(Dev d, int lr_rounds, int l
 // One thread per path.  Paths lie in distinct pieces (at most one per piece:
 // the attach path of a non-root piece or the re-root path of a super-root
 // piece), so the walks touch disjoint vertices; each thread reads a parent
-// before overwriting it (the old orientation is read exactly once).  A walk
-// first follows its path read-only for at most walk_k steps: a path that
-// does not reach its end by then is listed for the doubling pass below and
-// left untouched (the whole path, its new parent included), so one long
-// path cannot hold the update for its length in dependent reads.
+// before overwriting it (the old orientation is read exactly once).  A path
+// that does not reach its end within walk_k steps is turned back the way it
+// came, listed for the doubling pass below and left as it was (its new parent
+// included), so one long path cannot hold the update for its length in
+// dependent reads.  Bound by the longest path's dependent reads.
 __device__ void reverse_paths(const Dev &d, int64_t bid, int64_t nblk) {
     const int64_t nr = (int64_t)d.cnt[C_NR];
     const int64_t stride = nblk * BLOCK;
     for (int64_t i = bid * BLOCK + threadIdx.x; i < nr; i += stride) {
         const PathReq q = d.paths[i];
-        int32_t cur = q.start;
-        for (int64_t steps = 0; cur != q.stop && steps < d.walk_k; steps++) cur = d.parent[cur];
-        if (cur != q.stop) {
-            const unsigned long long k = atomicAdd(&d.cnt[C_NLONG], 1ull);
-            if ((int64_t)k < d.lpcap) d.lp_list[k] = (int32_t)i;
-            else atomicOr(d.status, ST_CAPACITY);
-            continue;
-        }
-        int32_t prev = q.newpar;
-        cur = q.start;
-        for (int64_t steps = 0;; steps++) {
+        int32_t prev = q.newpar, cur = q.start;
+        int64_t steps = 0;
+        for (; cur != q.stop && steps < d.walk_k; steps++) {
             const int32_t nxt = d.parent[cur];
             d.parent[cur] = prev;
-            if (cur == q.stop) break;
             prev = cur;
             cur = nxt;
-            if (steps > d.n) { atomicOr(d.status, ST_WALK_BOUND); break; }
         }
+        if (cur == q.stop) {
+            d.parent[cur] = prev;
+            continue;
+        }
+        for (; steps > 0; steps--) {  // prev hangs below cur again
+            const int32_t back = d.parent[prev];
+            d.parent[prev] = cur;
+            cur = prev;
+            prev = back;
+        }
+        const unsigned long long k = atomicAdd(&d.cnt[C_NLONG], 1ull);
+        if ((int64_t)k < d.lpcap) d.lp_list[k] = (int32_t)i;
+        else atomicOr(d.status, ST_CAPACITY);
     }
 }
 __global__ __launch_bounds__(BLOCK) void k_reverse_all(Dev d) {
@@ -1998,13 +2133,6 @@ __global__ __launch_bounds__(BLOCK) void k_lp_reverse(Dev d, LongPaths b) {
 
 // ------------------------------------------------------------ a9: labels
 
-// A wave's share of the orphans' edges, as they were last counted.
-__device__ __forceinline__ void add_edges(const Dev &d, unsigned long long x) {
-    for (int o = WAVE / 2; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    if (lane_id() == 0 && x)
-        atomicAdd(&d.cnt[C_OSLOTS + (blockIdx.x * (BLOCK / WAVE) + threadIdx.x / WAVE) % OSLOTS], x);
-}
-
 // Deletes: a vertex cut off from its old root takes its new component's
 // label.  Runs before the insert labels (mixed batches).  Restores
 // rep == label for the next update.
@@ -2028,41 +2156,75 @@ __device__ void label_delete(const Dev &d, int64_t bid, int64_t nblk) {
                 atomicOr(d.status, ST_WALK_BOUND);
             }
             d.obits[v >> 6] = 0;
-            d.bvol[v / BLOCK] = 0;
-            d.bcnt[v / BLOCK] = 0;
+            d.wvol[v >> 6] = 0;
         }
-        if (d.adeg) add_edges(d, edges);
+        if (d.adeg) {
+            edges = block_sum64(edges);
+            if (threadIdx.x == 0) d.osum[bid] = edges;
+        }
         return;
     }
-    const int64_t nb = (d.n + BLOCK - 1) / BLOCK;
+    // the store was swept: one wave per vertex block, four vertices per lane
+    typedef int v4i __attribute__((ext_vector_type(4)));
     const int64_t nvl_list = d.ctl->nvl;  // read once: stores below may alias it
-    for (int64_t j = bid;; j += nblk) {
-        const int64_t blk = list_block(d.vlist, nvl_list, j, nb);
+    const int lane = lane_id();
+    for (int64_t j = bid * (BLOCK / WAVE) + threadIdx.x / WAVE;; j += nblk * (BLOCK / WAVE)) {
+        const int64_t blk = list_block(d.vlist, nvl_list, j, d.nvb);
         if (blk < 0) break;
-        const int64_t v = blk * BLOCK + threadIdx.x;
-        uint64_t w = 0;
-        if (v < d.n) w = d.obits[v >> 6];
-        // the bitmap is all zero between updates (the sweeps read it for any
-        // vertex); the store depends on the loaded word, so it lands after
-        // every lane's read
-        if (lane_id() == 0 && w != 0) d.obits[v >> 6] = 0;
-        if (threadIdx.x == 0) {  // read only by this update's orphan scan
-            d.bvol[blk] = 0;
-            d.bcnt[blk] = 0;
+        const int64_t v = blk * BLOCK + lane * 4;
+        if (v >= d.n) continue;
+        const int64_t word = v / WAVE;
+        const uint64_t w = d.obits[word];
+        const int bits = (int)(w >> (v & 63)) & 15;
+        const bool first = (v & 63) == 0;  // of the word's sixteen lanes
+        if (d.adeg && w == ~0ull) {
+            if (first) edges += d.wdeg[word];  // 64 orphans: their sum is at hand
+        } else if (d.adeg) {
+            for (int k = 0; k < 4; k++)
+                if (bits >> k & 1) edges += (unsigned long long)d.adeg[v + k];
         }
-        if (v < d.n && ((w >> (v & 63)) & 1)) {
-            const int32_t p = d.tidx[d.rep[v]];
-            if (d.adeg) edges += (unsigned long long)d.adeg[v];
-            if (p >= 0) {
-                const int32_t l = d.newlab[d.comp[p]];
-                d.label[v] = l;
-                d.rep[v] = l;
-            } else {
+        int32_t r[4] = {0, 0, 0, 0}, t[4], l[4];
+        if (bits == 15) {
+            const v4i x = *reinterpret_cast<const v4i *>(d.rep + v);
+            r[0] = x.x; r[1] = x.y; r[2] = x.z; r[3] = x.w;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+                if (bits >> k & 1) r[k] = d.rep[v + k];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k++) t[k] = bits >> k & 1 ? d.tidx[r[k]] : 0;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            if (t[k] < 0) {
                 atomicOr(d.status, ST_WALK_BOUND);
+                t[k] = 0;
             }
+            l[k] = bits ? d.newlab[d.comp[t[k]]] : 0;
+        }
+        if (bits == 15) {
+            const v4i x = {l[0], l[1], l[2], l[3]};
+            *reinterpret_cast<v4i *>(d.label + v) = x;
+            *reinterpret_cast<v4i *>(d.rep + v) = x;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+                if (bits >> k & 1) {
+                    d.label[v + k] = l[k];
+                    d.rep[v + k] = l[k];
+                }
+        }
+        // the bitmap and the words' figures are zero between updates; the
+        // stores depend on the loaded word, so they land after the wave's reads
+        if (first && w != 0) {
+            d.obits[word] = 0;
+            d.wvol[word] = 0;
         }
     }
-    if (d.adeg) add_edges(d, edges);
+    if (d.adeg) {
+        edges = block_sum64(edges);
+        if (threadIdx.x == 0) d.osum[bid] = edges;
+    }
 }
 
 // Inserts: every vertex of a tree that merged into another takes the new
@@ -2375,6 +2537,13 @@ __global__ __launch_bounds__(BLOCK) void k_cleanup(Dev d) {
             d.rcnt[t] = 0;
     }
     if (!last_block_arrives(&d.cnt[C_ARRIVE])) return;
+    if (d.adeg && d.ctl->has_del) {
+        unsigned long long e = 0;
+        for (int64_t t = threadIdx.x; t < label_groups(d.n); t += BLOCK) e += d.osum[t];
+        e = block_sum64(e);
+        if (threadIdx.x == 0) d.cnt[C_OSLOTS] = e;
+        __syncthreads();
+    }
     for (int64_t t = threadIdx.x; t < d.ret_words; t += BLOCK) d.hret[t] = d.ctlmem[t];
     __threadfence_system();
     __syncthreads();  // every thread has copied before the completion word and any reset
@@ -2425,9 +2594,10 @@ void launch_register(const Dev &d, hipStream_t s) {
 void launch_insert_emit(const Dev &d, hipStream_t s) {
     hipLaunchKernelGGL(k_insert_emit, dim3((unsigned)insert_regions(d.lb)), dim3(BLOCK), 0, s, d);
 }
-void launch_count_edges(const Dev &d, int32_t *adeg, int64_t list, hipStream_t s) {
+void launch_count_edges(const Dev &d, int32_t *adeg, unsigned long long *wdeg, int64_t list, hipStream_t s) {
     hipLaunchKernelGGL(k_row_entries, dim3(grid_for(d.n, BLOCK)), dim3(BLOCK), 0, s, d, adeg);
     hipLaunchKernelGGL(k_live_edges, dim3(grid_for(std::max(d.eb, list), BLOCK)), dim3(BLOCK), 0, s, d, adeg);
+    hipLaunchKernelGGL(k_word_edges, dim3(grid_for(d.nvb, 1)), dim3(BLOCK), 0, s, d, adeg, wdeg);
 }
 void launch_rehash(const Dev &d, int64_t count, hipStream_t s) {
     launch_fill_u64(d.dhash, (int64_t)d.dhmask + 1, HASH_EMPTY, s);
@@ -2438,7 +2608,10 @@ void launch_rep_jump(const Dev &d, int rounds, hipStream_t s) {
         hipLaunchKernelGGL(k_rep_jump, dim3(grid_for(d.nvb, 1, GRID_CAP)), dim3(BLOCK), 0, s, d, k);
 }
 void launch_rep_chase(const Dev &d, hipStream_t s) {
-    hipLaunchKernelGGL(k_rep_chase, dim3(grid_for(d.nvb, REP_CH, GRID_CAP)), dim3(BLOCK), 0, s, d);
+    if (d.nvb <= CHASE_ONE)
+        hipLaunchKernelGGL(k_rep_chase<1>, dim3((unsigned)d.nvb), dim3(BLOCK), 0, s, d);
+    else
+        hipLaunchKernelGGL(k_rep_chase<2>, dim3(grid_for(d.nvb, 2, GRID_CAP)), dim3(BLOCK), 0, s, d);
 }
 void launch_sweep_base(const Dev &d, hipStream_t s) {
     // persistent: about as many workgroups as fit at once (24 KB of LDS each)
@@ -2446,11 +2619,11 @@ void launch_sweep_base(const Dev &d, hipStream_t s) {
         hipLaunchKernelGGL(k_sweep_base, dim3(grid_for(d.ntiles, 1, 6 * 256)), dim3(BLOCK), 0, s, d);
 }
 void launch_orphan_plan(const Dev &d, hipStream_t s) {
-    hipLaunchKernelGGL(k_orph_plan, dim3(grid_for(d.nvb, BLOCK, 1 << 30)), dim3(BLOCK), 0, s, d);
+    hipLaunchKernelGGL(k_orph_plan, dim3((unsigned)orphan_groups(d.nvb)), dim3(BLOCK), 0, s, d);
     hipLaunchKernelGGL(k_orph_total, dim3(1), dim3(BLOCK), 0, s, d);
 }
 void launch_orphan_fill(const Dev &d, hipStream_t s) {
-    hipLaunchKernelGGL(k_orph_fill, dim3(grid_for(d.nvb, BLOCK / 8, GRID_CAP)), dim3(BLOCK), 0, s, d);
+    hipLaunchKernelGGL(k_orph_fill, dim3(grid_for(orphan_words(d.nvb), BLOCK / 8, GRID_CAP)), dim3(BLOCK), 0, s, d);
 }
 void launch_orphan_scan(const Dev &d, hipStream_t s) {
     hipLaunchKernelGGL(k_orph_scan, dim3(grid_for(d.ntiles, 1, GRID_CAP)), dim3(BLOCK), 0, s, d);
@@ -2475,9 +2648,9 @@ void launch_boruvka(const Dev &d, int r0, int r1, int64_t units, bool emit, hipS
     // the tail reads a dense list, which rounds from 2 on have
     if (r1 >= 2 && r1 > r0) hipLaunchKernelGGL(k_bor_tail, dim3(1), dim3(TAIL_THREADS), 0, s, d, r1);
 }
-void launch_sf_root(const Dev &d, hipStream_t s) {
+void launch_sf_root(const Dev &d, bool count, hipStream_t s) {
     const int gp = grid_for(piece_bound(d), BLOCK, SMALL_CAP);
-    hipLaunchKernelGGL(k_sf_root, dim3(gp), dim3(BLOCK), 0, s, d);
+    hipLaunchKernelGGL(k_sf_root, dim3(gp + (count ? 1 : 0)), dim3(BLOCK), 0, s, d, count ? 1 : 0);
 }
 void launch_sf_bfs(const Dev &d, int l0, int l1, hipStream_t s) {
     const int ga = grid_for(2 * std::min<int64_t>(d.ercap, piece_bound(d)), BLOCK, SMALL_CAP);
@@ -2517,7 +2690,7 @@ void launch_finish(const Dev &d, bool ins, bool del, bool rev, hipStream_t s) {
                          : 0;
     // deletes relabel per vertex block or per listed orphan, inserts one wave
     // per vertex block
-    const int glab = del ? grid_for(d.n, BLOCK, FINISH_CAP) : grid_for(d.nvb, BLOCK / WAVE, FINISH_CAP);
+    const int glab = del ? (int)label_groups(d.n) : grid_for(d.nvb, BLOCK / WAVE, FINISH_CAP);
     hipLaunchKernelGGL(k_finish, dim3(grev + glab), dim3(BLOCK), 0, s, d, del ? 2 : 1, grev);
     if (ins && del)
         hipLaunchKernelGGL(k_label_insert, dim3(grid_for(d.nvb, BLOCK / WAVE, GRID_CAP)), dim3(BLOCK), 0,
