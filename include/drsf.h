@@ -102,12 +102,15 @@ typedef struct {
                                 launches finish them; 0 = chosen by the
                                 library: 2, raised (up to 12) to what an
                                 update that the host had to finish needed */
-    int levels_queued;       /* super-forest search levels placed in the graph;
-                                0 = chosen by the library: 4, raised (up to
-                                12) likewise, and once an update needed more
-                                than 12 the super-forest's Euler tour is
-                                queued after them (it skips itself when the
-                                search sufficed) (max 12) */
+    int levels_queued;       /* super-forest search levels queued in the update's
+                                kernel sequence (max 12); 0 = chosen by the
+                                library: 4, until an update needed more (the
+                                host finishes it); later updates of its kind
+                                orient super-trees as they grow, without a
+                                search, or, once that met too long a walk,
+                                queue the super-forest's Euler tour after 4
+                                levels (it skips itself when the search
+                                sufficed) */
     int reverse_mode;        /* path reversal: 0 (default) one thread walks each
                                 path; 1: Euler tour of F-hat with list ranking,
                                 start/finish times and the interval test

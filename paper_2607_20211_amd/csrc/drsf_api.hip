@@ -126,6 +126,7 @@ struct drsf_ctx {
     int32_t *tidx = nullptr, *owner = nullptr, *prt = nullptr, *pmin = nullptr, *comp = nullptr;
     uint8_t *pkeep = nullptr;
     int32_t *head = nullptr, *newlab = nullptr, *level = nullptr, *parc = nullptr;
+    uint64_t *up = nullptr;
     uint64_t *hook = nullptr, *best = nullptr, *srkey = nullptr;
     int64_t pcap = 0;
     // batch
@@ -180,10 +181,12 @@ struct drsf_ctx {
     // pointer-jumping rounds queued before root finding's chase: 0 until a
     // delete finds the forest deep (a chase of more than DEEP_STEPS steps)
     int jump_rounds = 0;
-    // the super-forest's Euler tour queued after the search (it skips itself
-    // when the search sufficed), per update kind (bit kind): set once an
-    // update of that kind needed it (tuning 0)
-    unsigned lr_kinds = 0;
+    // per update kind (bit kind), with levels left to the library (tuning 0):
+    // super-trees oriented as they grow, set once an update of that kind
+    // needed more search levels than are queued; and the super-forest's Euler
+    // tour queued after the search (it skips itself when the search
+    // sufficed), set once a walk of those was too long
+    unsigned walk_kinds = 0, lr_kinds = 0;
     // status word, counters and per-graph batch status share one allocation
     // so that one copy returns them: status at word 0, counters from word 1,
     // gstat after the counters
@@ -400,7 +403,7 @@ Dev make_dev(drsf_ctx *c) {
     d.tidx = c->tidx; d.owner = c->owner; d.pkeep = c->pkeep; d.prt = c->prt; d.pmin = c->pmin;
     d.comp = c->comp; d.hook = c->hook;
     d.best = c->best; d.srkey = c->srkey; d.head = c->head; d.newlab = c->newlab;
-    d.level = c->level; d.parc = c->parc; d.pcap = c->pcap;
+    d.level = c->level; d.parc = c->parc; d.up = c->up; d.pcap = c->pcap;
     d.bedges = c->bedges; d.bop = c->bop;
     d.bgid = c->ngraph > 1 ? c->bgid : nullptr;
     d.goff = c->ngraph > 1 ? c->goff : nullptr;
@@ -532,6 +535,7 @@ int alloc_state(drsf_ctx *c) {
     if ((rc = dalloc(c, &c->level, c->pcap))) return rc;
     if ((rc = dalloc(c, &c->parc, c->pcap))) return rc;
     if ((rc = dalloc(c, &c->newlab, c->pcap))) return rc;
+    if ((rc = dalloc(c, &c->up, c->pcap))) return rc;
     if ((rc = dalloc(c, &c->best, 2 * c->pcap))) return rc;
     if ((rc = dalloc(c, &c->srkey, c->pcap))) return rc;
     if ((rc = dalloc(c, &c->bedges, 2 * mb))) return rc;
@@ -1102,6 +1106,13 @@ int sg_reduce(drsf_ctx *c, const Dev &d, hipStream_t s) {
 // of every piece the context can register.
 int tour_rounds(const drsf_ctx *c) { return std::min(ceil_log2(2 * c->pcap + 2) + 2, MAX_ROUNDS); }
 
+// Super-trees are oriented as they grow, without a search.
+bool walks(const drsf_ctx *c, int kind) {
+    return c->opts.levels_queued <= 0 && (c->walk_kinds & ~c->lr_kinds & (1u << kind)) != 0;
+}
+// search levels queued
+int levels_of(const drsf_ctx *c, int kind) { return walks(c, kind) ? 0 : c->bfs_fast; }
+
 // The update sequence (see the file comment) for batches with inserts
 // (kind bit 1) and/or deletes (kind bit 2); with events when profiling.
 // kc: the control block, passed with the first kernel when the sequence is
@@ -1181,9 +1192,10 @@ void enqueue_update(drsf_ctx *c, int kind, bool profile, const Ctl *kc) {
     }
     mark(PH_ROOTING);
     launch_sf_root(d, c->opts.replacement_mode != 1, s);
-    launch_sf_bfs(d, 0, c->bfs_fast, s);
-    launch_orient_bfs(d, c->bfs_fast, s);
-    if (c->lr_kinds & (1u << kind)) launch_superforest_lr(d, tour_rounds(c), c->bfs_fast, s);
+    const int levels = levels_of(c, kind);
+    launch_sf_bfs(d, 0, levels, s);
+    launch_orient_bfs(d, levels, s);
+    if (c->lr_kinds & (1u << kind)) launch_superforest_lr(d, tour_rounds(c), levels, s);
     mark(PH_FINISH);
     const bool et = c->opts.reverse_mode == 1;
     if (et && launch_et_reverse(d, c->et_tmp, c->et_tmp_bytes, s))
@@ -1225,8 +1237,9 @@ int continue_update(drsf_ctx *c) {
         HIPCHK(c, hipMemcpyAsync(f, c->status, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipMemcpyAsync(f + 1, c->cnt + C_DONE_BOR, sizeof(unsigned long long),
                                  hipMemcpyDeviceToHost, s));
-        HIPCHK(c, hipMemcpyAsync(f + 2, c->cnt + C_BFS_ROUND + levels - 1, sizeof(unsigned long long),
-                                 hipMemcpyDeviceToHost, s));
+        // no levels: whether the trees that grew are not oriented after all
+        HIPCHK(c, hipMemcpyAsync(f + 2, c->cnt + (levels > 0 ? C_BFS_ROUND + levels - 1 : C_LONGTREE),
+                                 sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
         return DRSF_OK;
     };
@@ -1244,13 +1257,14 @@ int continue_update(drsf_ctx *c) {
     int how = 0;  // the bits of drsf_view.host_finished
     // profiled contexts time the continuation, host round trips included
     c->cont_timed = c->have_phases;
+    const int queued = levels_of(c, c->kind);  // search levels in the sequence
     if (!oriented) {
-        if ((rc = read_flags(c->bfs_fast))) return rc;
+        if ((rc = read_flags(queued))) return rc;
     }
     if (c->cont_timed) (void)hipEventRecord(c->ev[PH_N + 3], s);
     bad = !oriented && *(int32_t *)f != 0;
     bool done = oriented || f[1] != 0, bfs_done = oriented || f[2] == 0;
-    int r = c->round_base + c->bor_fast, lv = c->bfs_fast;
+    int r = c->round_base + c->bor_fast, lv = queued;
     if (!oriented && !bad && !done) {
         how |= 1;
         while (!done && !bad && r < bor_bound) {
@@ -1267,7 +1281,8 @@ int continue_update(drsf_ctx *c) {
         }
         if (!bad) {
             launch_sf_root(d, c->opts.replacement_mode != 1, s);
-            launch_sf_bfs(d, 0, c->bfs_fast, s);
+            launch_sf_bfs(d, 0, queued, s);
+            if (queued == 0) launch_orient_bfs(d, 0, s);
             if ((rc = read_flags(lv))) return rc;
             bad = *(int32_t *)f != 0;
             bfs_done = f[2] == 0;
@@ -1281,8 +1296,8 @@ int continue_update(drsf_ctx *c) {
             if ((rc = read_flags(lv))) return rc;
             bfs_done = f[2] == 0;
         }
-        if (bfs_done) launch_orient_bfs(d, lv, s);
-        else launch_superforest_lr(d, lr_rounds, lv, s);  // deep super-trees: Euler tour
+        if (bfs_done && lv > 0) launch_orient_bfs(d, lv, s);
+        else if (!bfs_done) launch_superforest_lr(d, lr_rounds, lv, s);  // deep super-trees: Euler tour
         const bool et = c->opts.reverse_mode == 1;
         if (et && launch_et_reverse(d, c->et_tmp, c->et_tmp_bytes, s))
             launch_fill_i32(c->status, 1, ST_ROUND_BOUND, s);
@@ -1302,23 +1317,21 @@ int continue_update(drsf_ctx *c) {
     HIPCHK(c, hipStreamSynchronize(s));
     c->view.host_finished = how ? how : 1;
     // counts left to the library (tuning 0): later updates queue the rounds
-    // and levels this one needed, so that updates like it finish on the
-    // device (each queued round or level that finds nothing costs one
-    // dispatch); bounded so that one outlier cannot make every update slow
+    // this one needed, so that updates like it finish on the device (each
+    // queued round that finds nothing costs one dispatch; bounded so that one
+    // outlier cannot make every update slow).  If the search was too short,
+    // they orient super-trees as they grow, and if that failed, they queue
+    // the tour
     if (!bad) {
         bool grew = false;
         if ((how & 1) && c->opts.rounds_queued <= 0 && r - c->round_base > c->bor_fast) {
             c->bor_fast = std::min(r - c->round_base, AUTO_ROUNDS_MAX);
             grew = true;
         }
-        if ((how & 2) && bfs_done && c->opts.levels_queued <= 0 && lv > c->bfs_fast) {
-            c->bfs_fast = std::min(lv, BFS_MAX);
-            grew = true;
-        }
-        // deeper than the levels may grow: queue the tour itself
-        if ((how & 2) && !bfs_done && c->opts.levels_queued <= 0 && !(c->lr_kinds & (1u << c->kind))) {
-            c->lr_kinds |= 1u << c->kind;
-            grew = true;
+        if ((how & 2) && c->opts.levels_queued <= 0) {
+            unsigned &kinds = queued == 0 ? c->lr_kinds : c->walk_kinds;
+            grew |= !(kinds & (1u << c->kind));
+            kinds |= 1u << c->kind;
         }
         if (grew) drop_graphs(c);
     }
@@ -1344,6 +1357,7 @@ int launch_update(drsf_ctx *c) {
     *(volatile unsigned long long *)(c->h_ret + c->ret_words + 7) = 0;
     c->kind = (c->h_ctl->has_ins ? 1 : 0) | (c->h_ctl->has_del ? 2 : 0);
     if (c->kind == 0) c->kind = 3;  // nothing but rejected or empty batches: run everything
+    c->h_ctl->walk = walks(c, c->kind);
     // the supergraph reads sizes back between its kernels, so it is not
     // captured (the Euler-tour reversal, sort included, is a fixed sequence).
     // An update queued behind a running one is launched kernel by kernel:
@@ -1370,6 +1384,7 @@ int launch_update(drsf_ctx *c) {
 int relaunch_update(drsf_ctx *c, int q) {
     select_slot(c, q);
     c->kind = c->pend[q].kind;
+    c->h_ctl->walk = walks(c, c->kind);  // the host's continuation may have changed it
     if (!graph_launch(c)) {
         enqueue_update(c, c->kind, false, c->h_ctl);
     } else {
@@ -1699,7 +1714,7 @@ int64_t drsf_footprint(int32_t n, int64_t nnz, const drsf_opts *opts) {
     b += 4 * (N + 1) * 3 + 4 * ntiles * TILE + 8 * eb + 4 * (ntiles + 1);  // bptr, lptr, zptr; bcol; lcol, twin
     b += 4 * N * 2;                                                       // zrow, parent
     b += 16 * N + (N + 63) / 64 * 8;                                      // label, rep, tidx, owner; bitmap
-    b += 49 * pcap + 40 * pcap + 16 * pcap + 16 * std::max(2 * pcap, N);  // pieces, tour, er, paths
+    b += 57 * pcap + 40 * pcap + 16 * pcap + 16 * std::max(2 * pcap, N);  // pieces, tour, er, paths
     b += 37 * mb + 8 * bh + 12 * lcap + 12 * dh + 5 * N;                          // batch, tables, inserted list
     b += 32 * xcap + 8 * (xcap / TILE);                                   // cross lists
     b += 16 * orphan_words(nvb) + 40 * N + 8 * (ntiles + 1) + 4 * (2 * ntiles + 1) +

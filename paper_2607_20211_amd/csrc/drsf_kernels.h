@@ -24,6 +24,8 @@ struct Ctl {
     const int32_t *edges;  // the batch in the caller's device memory, or null: staged copy
     uint64_t seq;          // update number, written to the completion word when done
     int32_t nsmall;        // small graphs with a batch in this update (SmallDev::tasks)
+    int32_t walk;          // super-trees are oriented as they grow instead of searched
+    int32_t pad;
     int32_t revive;        // inserts look for their deleted base entry also without validation
 };
 
@@ -108,6 +110,8 @@ struct Dev {
     int32_t *head;           // [pcap] first arc of the piece's super-forest arc list
     int32_t *level;          // [pcap] search level of the piece in its super-tree, -1 unreached
     int32_t *parc;           // [pcap] arc from the parent piece (search rooting)
+    uint64_t *up;            // [pcap] (arc << 32 | parent piece) the piece hangs by, kept as the
+                             // components hook (Ctl::walk), UP_NONE for a component's root
     int32_t *newlab;         // [pcap] new label of the component
     int64_t pcap;
     // batch
@@ -251,6 +255,8 @@ constexpr int C_DEEP = C_COUNT + 12;
 constexpr int C_NFREE = C_COUNT + 13;
 constexpr int C_LISTED = C_COUNT + 14;
 constexpr int C_FREED = C_COUNT + 15;
+// super-trees oriented as they grow: a walk was too long, the search or tour has to do it
+constexpr int C_LONGTREE = C_COUNT + 17;
 constexpr int C_OSLOTS = C_COUNT + 16;  // adeg over the orphans
 
 // Grid sizes.  Workgroups are dispatched at about 200-270 per microsecond
@@ -321,6 +327,7 @@ void launch_boruvka(const Dev &d, int r0, int r1, int64_t units, bool emit, hipS
 // count: also the number of cross edges found (the supergraph counts its own)
 void launch_sf_root(const Dev &d, bool count, hipStream_t s);
 void launch_sf_bfs(const Dev &d, int l0, int l1, hipStream_t s);
+// levels 0: super-trees oriented as they grew (re-rooted here)
 void launch_orient_bfs(const Dev &d, int levels, hipStream_t s);
 // the super-forest's Euler tour when the search of `levels` levels did not
 // finish (skips itself otherwise)

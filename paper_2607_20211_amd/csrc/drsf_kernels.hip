@@ -135,6 +135,7 @@ __device__ __forceinline__ void init_piece(const Dev &d, int64_t id, int32_t v, 
     d.best[id] = d.best[d.pcap + id] = keep ? 0 : KEY_INF;
     d.srkey[id] = KEY_INF;
     d.head[id] = NONE;
+    d.up[id] = UP_NONE;
     d.newlab[id] = v;
     d.pkeep[id] = keep ? 1 : 0;
     d.tidx[v] = (int32_t)id;  // read by later kernels only
@@ -1626,6 +1627,34 @@ __global__ __launch_bounds__(BLOCK) void k_bor_select(Dev d, int r) {
     s_min.flush(best);
 }
 
+// Super-trees oriented as they grow (Ctl::walk).  A component's pieces hang
+// below its root piece by up[].  When it hooks, its tree is re-rooted at the
+// piece that the hooking edge leaves (the arcs between that piece and the
+// root turned round) and that piece hangs below the edge's other end.  A
+// component hooks once a round and a walk stays inside it, so the walks of a
+// round touch different pieces.  It costs what lies between the hooking edges
+// and the roots, which is little where most components hook onto one large
+// one, instead of a launch per level of the finished super-trees (G(1e6, 4e6),
+// 12 levels in each update: 79 us of search a step -> 0.3 us more in each
+// hook; 256 graphs, search and tour: 225 us a step -> 3); a walk longer than
+// UP_WALK leaves the orientation to the search and the tour.
+constexpr int UP_WALK = 512;
+__device__ __forceinline__ void hang(const Dev &d, int32_t piece, uint64_t to) {
+    for (int steps = 0; steps < UP_WALK; steps++) {
+        const uint64_t old = d.up[piece];
+        d.up[piece] = to;
+        if (old == UP_NONE) return;
+        to = (((old >> 32) ^ 1) << 32) | (uint32_t)piece;
+        piece = (int32_t)(uint32_t)old;
+    }
+    d.cnt[C_LONGTREE] = 1;
+}
+// component c hooks by the er entry `slot` (x, y, px, py), where x's end is in c if `from_x`
+__device__ __forceinline__ void hang_hooked(const Dev &d, int64_t slot, int32_t px, int32_t py, bool from_x) {
+    const uint64_t arc = 2 * (uint64_t)slot + (from_x ? 1 : 0);  // even: from px to py
+    hang(d, from_x ? px : py, (arc << 32) | (uint32_t)(from_x ? py : px));
+}
+
 // Each selecting component hooks onto the component across its lowest-key
 // edge; when two components pick the same edge the smaller id stays a root.
 // Distinct keys make the chosen edges a forest (Boruvka).  Round r >= 1 ends
@@ -1642,12 +1671,13 @@ __global__ __launch_bounds__(BLOCK) void k_bor_hook(Dev d, int r) {
         if (r >= 2 && blockIdx.x == 0 && threadIdx.x == 0) d.cnt[(r & 1) ? C_NX0 : C_NX1] = 0;
     }
     const int64_t np = (int64_t)d.cnt[C_NP];
+    const bool walk = d.ctl->walk;
     const uint64_t *best = best_of(d, r);
     uint64_t *next = best_of(d, r + 1);
     const int64_t stride = (int64_t)gridDim.x * BLOCK;
     for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < np; base += stride) {
         const int64_t p = base + threadIdx.x;
-        bool rec = false;
+        bool rec = false, from_x = false;
         int4 er = make_int4(0, 0, 0, 0);
         if (p < np) {
             next[p] = no_key(d, (int32_t)p);
@@ -1661,7 +1691,8 @@ __global__ __launch_bounds__(BLOCK) void k_bor_hook(Dev d, int r) {
                 } else {
                     const int32_t cx = comp_root(d, px, (uint32_t)r, np);
                     const int32_t cy = comp_root(d, py, (uint32_t)r, np);
-                    const int32_t other = (cx == (int32_t)p) ? cy : cx;
+                    from_x = cx == (int32_t)p;
+                    const int32_t other = from_x ? cy : cx;
                     if (!(best[other] == k && (int32_t)p < other)) {
                         d.hook[p] = hook_pack(r, other);
                         rec = true;
@@ -1671,7 +1702,10 @@ __global__ __launch_bounds__(BLOCK) void k_bor_hook(Dev d, int r) {
             }
         }
         const int64_t slot = block_append(rec ? 1 : 0, &d.cnt[C_NER]);
-        if (rec) d.er[slot] = er;
+        if (rec) {
+            d.er[slot] = er;
+            if (walk) hang_hooked(d, slot, er.z, er.w, from_x);
+        }
     }
 }
 
@@ -1693,6 +1727,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_bor_tail(Dev d, int r0) {
     if (cin > TAIL_MAX) return;
     __shared__ int s_nout;
     const int64_t np = (int64_t)d.cnt[C_NP];
+    const bool walk = d.ctl->walk;
     for (int r = r0;; r++) {
         if (r >= MAX_ROUNDS) {
             if (threadIdx.x == 0) atomicOr(d.status, ST_ROUND_BOUND);
@@ -1738,7 +1773,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_bor_tail(Dev d, int r0) {
         }
         for (int64_t base = 0; base < nout; base += TAIL_THREADS) {
             const int64_t i = base + threadIdx.x;
-            bool rec[2] = {false, false};
+            bool rec[2] = {false, false}, from_x[2] = {false, false};
             int4 er[2] = {make_int4(0, 0, 0, 0), make_int4(0, 0, 0, 0)};
             if (i < nout) {
                 const Cross e = out[i];
@@ -1757,13 +1792,17 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_bor_tail(Dev d, int r0) {
                     if (atomicCAS((unsigned long long *)&d.hook[p], (unsigned long long)HOOK_NONE,
                                   (unsigned long long)hook_pack(r, other)) == HOOK_NONE) {
                         rec[side] = true;
+                        from_x[side] = walk && comp_root(d, px, (uint32_t)r, np) == p;
                         er[side] = make_int4(x, y, px, py);
                     }
                 }
             }
             for (int side = 0; side < 2; side++) {
                 const int64_t slot = wave_append(rec[side], &d.cnt[C_NER]);
-                if (rec[side]) d.er[slot] = er[side];
+                if (rec[side]) {
+                    d.er[slot] = er[side];
+                    if (walk) hang_hooked(d, slot, er[side].z, er[side].w, from_x[side]);
+                }
             }
         }
         __syncthreads();
@@ -1842,14 +1881,29 @@ __global__ __launch_bounds__(BLOCK) void k_sf_bfs(Dev d, int L) {
     if (__ballot(active) && lane_id() == 0) d.cnt[C_BFS_ROUND + L] = 1;
 }
 
+// Super-trees oriented as they grew: each component's tree re-rooted at its
+// super-root (the walk stays inside the component).
+__global__ __launch_bounds__(BLOCK) void k_sf_reroot(Dev d) {
+    if (stopped(d) || !d.cnt[C_DONE_BOR] || d.cnt[C_LONGTREE]) return;
+    const int64_t np = (int64_t)d.cnt[C_NP];
+    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    for (int64_t p = (int64_t)blockIdx.x * BLOCK + threadIdx.x; p < np; p += stride) {
+        if (d.comp[p] != (int32_t)p) continue;
+        const int32_t root = (int32_t)(uint32_t)d.srkey[p];
+        if (root != (int32_t)p) hang(d, root, UP_NONE);
+    }
+}
+
 // Orientation from the search, once the rounds have finished and the last
-// queued level reached nothing new: a piece reached through arc a (from the
+// queued level reached nothing new (or, with levels 0, from the trees as they
+// grew): a piece reached through arc a (from the
 // parent piece) reverses the path from a's endpoint in the piece to the
 // piece's root and hangs that endpoint below a's other endpoint (Algorithm 1,
 // R and new parents).  A super-root piece whose root is not the component's
 // smallest vertex m is re-rooted at m; m is the component's new label.
 __global__ __launch_bounds__(BLOCK) void k_orient_bfs(Dev d, int levels) {
-    if (stopped(d) || !d.cnt[C_DONE_BOR] || d.cnt[C_BFS_ROUND + levels - 1] != 0) return;
+    if (stopped(d) || !d.cnt[C_DONE_BOR]) return;
+    if (levels > 0 ? d.cnt[C_BFS_ROUND + levels - 1] != 0 : d.cnt[C_LONGTREE] != 0) return;
     const int64_t np = (int64_t)d.cnt[C_NP];
     const int64_t stride = (int64_t)gridDim.x * BLOCK;
     if (blockIdx.x == 0 && threadIdx.x == 0) d.cnt[C_ORIENTED] = 1;
@@ -1860,13 +1914,13 @@ __global__ __launch_bounds__(BLOCK) void k_orient_bfs(Dev d, int levels) {
         q1.start = q1.newpar = q1.stop = q1.pad = 0;
         q2 = q1;
         if (p < np) {
-            const int32_t a = d.parc[p];
+            const int32_t a = levels > 0 ? d.parc[p] : (int32_t)(d.up[p] >> 32);  // UP_NONE: -1
             if (a >= 0) {
                 const int4 e = d.er[a >> 1];
                 e1 = true;
                 if ((a & 1) == 0) { q1.start = e.y; q1.newpar = e.x; q1.stop = d.prt[e.w]; }
                 else { q1.start = e.x; q1.newpar = e.y; q1.stop = d.prt[e.z]; }
-            } else if (d.level[p] < 0 && !is_super_root(d, (int32_t)p)) {
+            } else if ((levels == 0 || d.level[p] < 0) && !is_super_root(d, (int32_t)p)) {
                 atomicOr(d.status, ST_ROUND_BOUND);  // piece not reached: search incomplete
             }
             if (d.comp[p] == (int32_t)p) {
@@ -2657,6 +2711,8 @@ void launch_sf_bfs(const Dev &d, int l0, int l1, hipStream_t s) {
     for (int L = l0; L < l1; L++) hipLaunchKernelGGL(k_sf_bfs, dim3(ga), dim3(BLOCK), 0, s, d, L);
 }
 void launch_orient_bfs(const Dev &d, int levels, hipStream_t s) {
+    if (levels == 0)
+        hipLaunchKernelGGL(k_sf_reroot, dim3(grid_for(piece_bound(d), BLOCK, SMALL_CAP)), dim3(BLOCK), 0, s, d);
     hipLaunchKernelGGL(k_orient_bfs, dim3(grid_for(piece_bound(d), BLOCK, SMALL_CAP)), dim3(BLOCK), 0, s, d,
                        levels);
 }

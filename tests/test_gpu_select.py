@@ -59,3 +59,30 @@ def test_one_piece_that_every_edge_touches(leaves):
     g = gen.make_graph("star", n, np.zeros(0, np.uint64))
     _run(g, [(rays, drsf.DRSF_INSERT), (rays[::2], drsf.DRSF_DELETE), (rays[::2], drsf.DRSF_INSERT),
              (rays, drsf.DRSF_DELETE)])
+
+
+@pytest.mark.parametrize("k,bits", [(300, (2, 0, 0)), (16384, (2, 2, 0))])
+@pytest.mark.parametrize("launch_mode", [2, 1])
+def test_super_trees_searched_then_oriented_as_they_grow(k, bits, launch_mode):
+    """A chain of k two-vertex pieces joined by edges whose keys follow the
+    ruler sequence, inserted three times: a context's first deep super-tree is
+    finished by the host (search and tour), the next is oriented while it
+    grows, which on the long chain meets a walk past its bound, so the host
+    finishes it too and the third queues the tour."""
+    drsf = _lib()
+    _case(f"ruler chain of {k} pieces, launch mode {launch_mode}")
+    weight = [((j + 1) & -(j + 1)).bit_length() for j in range(k)]
+    order = sorted(range(k), key=lambda j: (weight[j], j))
+    u = np.empty(k + 1, np.int64)
+    u[np.array(order)] = np.arange(k)
+    u[k] = 2 * k + 1
+    v = np.arange(k, 2 * k + 1, dtype=np.int64)
+    keys = np.sort(gen.keys_of_edges(np.stack([u, v], 1)))
+    g = gen.make_graph("ruler", 2 * k + 2, keys)
+    pair = Pair(g, max_batch=k, launch_mode=launch_mode)
+    ins = np.stack([u[:k], v[1:k + 1]], axis=1).astype(np.int32)
+    for i, want in enumerate(bits):
+        st, _ = pair.step(ins, drsf.DRSF_INSERT, f"insert {i}")
+        assert st["host_finished"] & 2 == want, (i, st)
+        pair.step(ins, drsf.DRSF_DELETE, f"delete {i}")
+    pair.gpu.close()
