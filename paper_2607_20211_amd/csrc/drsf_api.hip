@@ -1170,16 +1170,17 @@ void enqueue_update(drsf_ctx *c, int kind, bool profile, const Ctl *kc) {
         launch_orphan_plan(d, s);
         launch_orphan_fill(d, s);
     }
+    // one launch, or one per phase when profiled
     mark(PH_ORPH_SCAN, del);
-    if (del) launch_orphan_scan(d, s);
+    if (del) launch_key_edges(d, profile ? 2 : 7, s);
     mark(PH_SWEEP, del);
-    if (del) launch_sweep_base(d, s);
+    if (del && profile) launch_key_edges(d, 4, s);
     mark(PH_SWEEP_DELTA);
     // the supergraph reads the insert regions before the rounds; otherwise
     // the first round emits them itself
     const bool sg = c->opts.replacement_mode == 1;
     if (ins && sg) launch_insert_emit(d, s);
-    if (del) launch_sweep_delta(d, s);
+    if (del && profile) launch_key_edges(d, 1, s);
     mark(PH_REPL);
     const int64_t units = (ins ? insert_regions(d.lb) : 0) + (del ? c->ntiles + d.ltiles : 0);
     if (sg) {  // supergraph, then its rounds

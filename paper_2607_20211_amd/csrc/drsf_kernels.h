@@ -274,6 +274,7 @@ constexpr int GRID_CAP = 2048;
 #endif
 constexpr int SMALL_CAP = DRSF_SMALL_CAP;  // kernels over pieces, arcs and paths
 constexpr int EDGE_CAP = DRSF_EDGE_CAP;    // first hooking selections
+constexpr int EMIT_CAP = 1024;             // insert emit: each workgroup writes its minima once
 #ifndef DRSF_FINISH_CAP
 #define DRSF_FINISH_CAP 2048
 #endif
@@ -315,15 +316,16 @@ void launch_rehash(const Dev &d, int64_t count, hipStream_t s);
 // after one that changed nothing exits at once
 void launch_rep_jump(const Dev &d, int rounds, hipStream_t s);
 void launch_rep_chase(const Dev &d, hipStream_t s);
-void launch_sweep_base(const Dev &d, hipStream_t s);
 void launch_orphan_plan(const Dev &d, hipStream_t s);  // block prefixes, totals and scan mode
 void launch_orphan_fill(const Dev &d, hipStream_t s);  // the orphan list
-void launch_orphan_scan(const Dev &d, hipStream_t s);
-void launch_sweep_delta(const Dev &d, hipStream_t s);
+// the key edges of a delete, with the first round's selection: parts 1 the
+// inserted-edge list, 2 the orphans' adjacency, 4 the whole store (the plan
+// chooses between 2 and 4)
+void launch_key_edges(const Dev &d, int parts, hipStream_t s);
 // units: regions of x0 the first two rounds may read (sizes their grids)
-// rounds [r0, r1); emit: round 0 also emits the insert cross edges
-// (k_insert_emit not launched)
-void launch_boruvka(const Dev &d, int r0, int r1, int64_t units, bool emit, hipStream_t s);
+// rounds [r0, r1); ins: round 0 emits the insert cross edges and selects on
+// them (a delete's scans have made their selection)
+void launch_boruvka(const Dev &d, int r0, int r1, int64_t units, bool ins, hipStream_t s);
 // count: also the number of cross edges found (the supergraph counts its own)
 void launch_sf_root(const Dev &d, bool count, hipStream_t s);
 void launch_sf_bfs(const Dev &d, int l0, int l1, hipStream_t s);

@@ -813,17 +813,40 @@ __global__ __launch_bounds__(BLOCK) void k_rep_chase(Dev d) {
 // rest; the row vertices sit in LDS beside it.  So the only global gathers
 // are the orphan bits of both ends (all of a thread's issued together) and
 // rep for the flagged edges.  Cross edges go to the
-// tile's own region of x0.
-__global__ __launch_bounds__(BLOCK) void k_sweep_base(Dev d) {
-    if (stopped(d) || !d.ctl->has_del || d.cnt[C_OMODE]) return;
-    typedef int v4i __attribute__((ext_vector_type(4)));
+// tile's own region of x0, and take part in the first hooking round's
+// selection from here (their keys meet in the LDS table).
+typedef int v4i __attribute__((ext_vector_type(4)));
+constexpr int HALF = EPT / 2;
+// the selection over a region that this workgroup has just written
+__device__ __forceinline__ void select_region(const Dev &d, MinTable &tab, const Cross *region, int count) {
+    __syncthreads();
+    for (int base = 0; base < count; base += BLOCK) {  // uniform over the workgroup
+        const int i = base + (int)threadIdx.x;
+        if (i < count) {
+            const Cross e = region[i];
+            tab.add(e.pa, e.key, d.best);
+            tab.add(e.pb, e.key, d.best);
+        }
+        if ((base / BLOCK & 3) == 3) tab.flush_half(d.best);
+    }
+    tab.flush_half(d.best);
+}
+struct SweepLds {
+    v4i rowv[TILE / 8];      // int16 local row index per edge
+    int32_t u[TILE + 1];     // row vertex per local row
+    int16_t wmax[BLOCK / WAVE];
+    MinTable tab;            // lowest key per piece
+};
+__device__ __forceinline__ void sweep_base(const Dev &d, SweepLds &lds, int64_t bid, int64_t nblk) {
     typedef short v4s __attribute__((ext_vector_type(4)));
-    __shared__ v4i s_rowv[TILE / 8];      // int16 local row index per edge
-    __shared__ int32_t s_u[TILE + 1];     // row vertex per local row
-    __shared__ int16_t s_wmax[BLOCK / WAVE];
+    v4i *const s_rowv = lds.rowv;
+    int32_t *const s_u = lds.u;
+    int16_t *const s_wmax = lds.wmax;
     int16_t *s_row = reinterpret_cast<int16_t *>(s_rowv);
+    const uint32_t *const obits32 = reinterpret_cast<const uint32_t *>(d.obits);
+    lds.tab.clear();
     const int64_t ntl_list = d.ctl->ntl;  // read once: stores below may alias it
-    for (int64_t jt = blockIdx.x;; jt += gridDim.x) {
+    for (int64_t jt = bid;; jt += nblk) {
         const int64_t tile = list_block(d.tlist, ntl_list, jt, d.ntiles);
         if (tile < 0) break;
         __syncthreads();  // the previous tile is finished with the LDS
@@ -833,14 +856,11 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_base(Dev d) {
         // thread's edges: local positions pbase + q * 256 + j, q, j < 4
         const int pbase = wid * (TILE / 4) + lane * 4;
         // the store is padded with deleted entries to whole tiles
-        int32_t c[EPT];
+        v4i cv[4];
         {
             const v4i *p = reinterpret_cast<const v4i *>(d.bcol + base + pbase);
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const v4i t = __builtin_nontemporal_load(p + q * 64);
-                c[4 * q] = t.x; c[4 * q + 1] = t.y; c[4 * q + 2] = t.z; c[4 * q + 3] = t.w;
-            }
+            for (int q = 0; q < 4; q++) cv[q] = __builtin_nontemporal_load(p + q * 64);
         }
         // row map: mark row starts
         const v4i zero = {0, 0, 0, 0};
@@ -906,125 +926,145 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_base(Dev d) {
             }
         }
         __syncthreads();
-        // row vertex of each of the thread's edges
-        int32_t urow[EPT];
+        // half of the thread's edges at a time (all sixteen need 214 VGPRs, two
+        // waves per SIMD, and the loads of more waves hide more): the row
+        // vertices, then every gather is issued before any result is used:
+        // the bitmap words of both ends unconditionally (a deleted entry's
+        // masked id is still a vertex; edges of one row share the row's
+        // word), then rep only for flagged edges, the others pointed at rep[0]
+        int total = 0;
+        for (int h = 0; h < 2; h++) {
+            int32_t c[HALF], urow[HALF];
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const v4s r = *reinterpret_cast<const v4s *>(s_row + pbase + q * 256);
-            urow[4 * q] = s_u[r.x]; urow[4 * q + 1] = s_u[r.y];
-            urow[4 * q + 2] = s_u[r.z]; urow[4 * q + 3] = s_u[r.w];
+            for (int q = 0; q < 2; q++) {
+                const v4i t = h ? cv[2 + q] : cv[q];
+                c[4 * q] = t.x; c[4 * q + 1] = t.y; c[4 * q + 2] = t.z; c[4 * q + 3] = t.w;
+                const v4s r = *reinterpret_cast<const v4s *>(s_row + pbase + (2 * h + q) * 256);
+                urow[4 * q] = s_u[r.x]; urow[4 * q + 1] = s_u[r.y];
+                urow[4 * q + 2] = s_u[r.z]; urow[4 * q + 3] = s_u[r.w];
+            }
+            uint32_t bu[HALF], bv[HALF];
+#pragma unroll
+            for (int j = 0; j < HALF; j++) {
+                bu[j] = obits32[urow[j] >> 5];
+                bv[j] = obits32[(c[j] & COLMASK) >> 5];
+            }
+            uint32_t cand = 0;
+#pragma unroll
+            for (int j = 0; j < HALF; j++)
+                if (c[j] >= 0 && (((bu[j] >> (urow[j] & 31)) | (bv[j] >> (c[j] & 31))) & 1)) cand |= 1u << j;
+            int32_t ra[HALF], rb[HALF];
+            uint32_t mask = 0;
+            if (__ballot(cand != 0)) {
+#pragma unroll
+                for (int j = 0; j < HALF; j++) {
+                    const bool k = cand >> j & 1;
+                    ra[j] = d.rep[k ? urow[j] : 0];
+                    rb[j] = d.rep[k ? c[j] : 0];
+                }
+#pragma unroll
+                for (int j = 0; j < HALF; j++)
+                    if ((cand >> j & 1) && ra[j] != rb[j]) mask |= 1u << j;
+            }
+            int found;
+            const int off = total + block_excl_scan(__popc(mask), &found);
+            total += found;
+            if (mask) {
+                Cross *out = d.x0 + tile * TILE + off;
+                int w = 0;
+#pragma unroll
+                for (int j = 0; j < HALF; j++) {
+                    if (mask >> j & 1) {
+                        Cross x;
+                        x.key = ((uint64_t)(uint32_t)urow[j] << 32) | (uint32_t)c[j];
+                        x.pa = d.tidx[ra[j]];
+                        x.pb = d.tidx[rb[j]];
+                        if (x.pa < 0 || x.pb < 0) {
+                            atomicOr(d.status, ST_WALK_BOUND);
+                            x.pa = x.pb = 0;
+                        }
+                        out[w++] = x;
+                    }
+                }
+            }
         }
-        // every gather of a thread is issued before any result is used: the
-        // bitmap words of both ends unconditionally (a deleted entry's masked id
-        // is still a vertex; edges of one row share the row's word), then rep
-        // only for flagged edges, the others pointed at rep[0]
-        uint64_t bu[EPT], bv[EPT];
+        if (threadIdx.x == 0) d.rcnt[tile] = (unsigned long long)total;
+        select_region(d, lds.tab, d.x0 + tile * TILE, total);
+    }
+    lds.tab.flush(d.best);
+}
+
+// The same test over the list of inserted edges: workgroup t takes list
+// entries [t * TILE, (t + 1) * TILE) and writes region ntiles + t.  Lane
+// layout, gathers and selection as in sweep_base.
+__device__ __forceinline__ void sweep_list(const Dev &d, MinTable &tab, int64_t t) {
+    const int64_t nd = (int64_t)d.cnt[C_NDELTA];
+    if (t * TILE >= nd) return;
+    tab.clear();
+    const int lane = lane_id(), wid = threadIdx.x / WAVE;
+    const int64_t i0 = t * TILE + wid * (TILE / 4) + lane * 4;  // + q * 256 + j
+    const int64_t reg = d.ntiles + t;
+    const uint32_t *const obits32 = reinterpret_cast<const uint32_t *>(d.obits);
+    int total = 0;
+    for (int h = 0; h < 2; h++) {
+        uint64_t k[HALF];
 #pragma unroll
-        for (int j = 0; j < EPT; j++) {
-            bu[j] = d.obits[urow[j] >> 6];
-            bv[j] = d.obits[(c[j] & COLMASK) >> 6];
+        for (int q = 0; q < 2; q++)
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const int64_t i = i0 + (2 * h + q) * 256 + j;
+                k[4 * q + j] = i < nd ? d.dkey[i] : KEY_DEAD;
+            }
+        uint32_t wu[HALF], wv[HALF];
+#pragma unroll
+        for (int j = 0; j < HALF; j++) {
+            const bool live = k[j] != KEY_DEAD;
+            wu[j] = obits32[live ? key_lo(k[j]) >> 5 : 0];
+            wv[j] = obits32[live ? key_hi(k[j]) >> 5 : 0];
         }
         uint32_t cand = 0;
 #pragma unroll
-        for (int j = 0; j < EPT; j++)
-            if (c[j] >= 0 && (((bu[j] >> (urow[j] & 63)) | (bv[j] >> (c[j] & 63))) & 1)) cand |= 1u << j;
-        int32_t ra[EPT], rb[EPT];
+        for (int j = 0; j < HALF; j++)
+            if (k[j] != KEY_DEAD && (((wu[j] >> (key_lo(k[j]) & 31)) | (wv[j] >> (key_hi(k[j]) & 31))) & 1))
+                cand |= 1u << j;
+        int32_t ra[HALF], rb[HALF];
         uint32_t mask = 0;
         if (__ballot(cand != 0)) {
 #pragma unroll
-            for (int j = 0; j < EPT; j++) {
-                const bool k = cand >> j & 1;
-                ra[j] = d.rep[k ? urow[j] : 0];
-                rb[j] = d.rep[k ? c[j] : 0];
+            for (int j = 0; j < HALF; j++) {
+                const bool c = cand >> j & 1;
+                ra[j] = d.rep[c ? key_lo(k[j]) : 0];
+                rb[j] = d.rep[c ? key_hi(k[j]) : 0];
             }
 #pragma unroll
-            for (int j = 0; j < EPT; j++)
+            for (int j = 0; j < HALF; j++)
                 if ((cand >> j & 1) && ra[j] != rb[j]) mask |= 1u << j;
         }
-        int total;
-        const int off = block_excl_scan(__popc(mask), &total);
-        if (threadIdx.x == 0) d.rcnt[tile] = (unsigned long long)total;
+        int found;
+        const int off = total + block_excl_scan(__popc(mask), &found);
+        total += found;
         if (mask) {
-            Cross *out = d.x0 + tile * TILE + off;
+            Cross *out = d.x0 + reg * TILE + off;
             int w = 0;
 #pragma unroll
-            for (int j = 0; j < EPT; j++) {
+            for (int j = 0; j < HALF; j++) {
                 if (mask >> j & 1) {
                     Cross x;
-                    x.key = ((uint64_t)(uint32_t)urow[j] << 32) | (uint32_t)c[j];
+                    x.key = k[j];
                     x.pa = d.tidx[ra[j]];
                     x.pb = d.tidx[rb[j]];
-                    if (x.pa < 0 || x.pb < 0) atomicOr(d.status, ST_WALK_BOUND);
+                    if (x.pa < 0 || x.pb < 0) {
+                        atomicOr(d.status, ST_WALK_BOUND);
+                        x.pa = x.pb = 0;
+                    }
                     out[w++] = x;
                 }
             }
         }
     }
-}
-
-// The same test over the list of inserted edges: workgroup t takes list
-// entries [t * TILE, (t + 1) * TILE) and writes region ntiles + t.  Lane
-// layout and gathers as in k_sweep_base.
-__global__ __launch_bounds__(BLOCK) void k_sweep_delta(Dev d) {
-    if (stopped(d) || !d.ctl->has_del) return;
-    const int64_t nd = (int64_t)d.cnt[C_NDELTA];
-    const int64_t t = blockIdx.x;
-    if (t * TILE >= nd) return;
-    const int lane = lane_id(), wid = threadIdx.x / WAVE;
-    const int64_t i0 = t * TILE + wid * (TILE / 4) + lane * 4;  // + q * 256 + j
-    uint64_t k[EPT];
-#pragma unroll
-    for (int q = 0; q < 4; q++)
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            const int64_t i = i0 + q * 256 + j;
-            k[4 * q + j] = i < nd ? d.dkey[i] : KEY_DEAD;
-        }
-    uint64_t wu[EPT], wv[EPT];
-#pragma unroll
-    for (int j = 0; j < EPT; j++) {
-        const bool live = k[j] != KEY_DEAD;
-        wu[j] = d.obits[live ? key_lo(k[j]) >> 6 : 0];
-        wv[j] = d.obits[live ? key_hi(k[j]) >> 6 : 0];
-    }
-    uint32_t cand = 0;
-#pragma unroll
-    for (int j = 0; j < EPT; j++)
-        if (k[j] != KEY_DEAD &&
-            (((wu[j] >> (key_lo(k[j]) & 63)) | (wv[j] >> (key_hi(k[j]) & 63))) & 1))
-            cand |= 1u << j;
-    int32_t ra[EPT], rb[EPT];
-    uint32_t mask = 0;
-    if (__ballot(cand != 0)) {
-#pragma unroll
-        for (int j = 0; j < EPT; j++) {
-            const bool c = cand >> j & 1;
-            ra[j] = d.rep[c ? key_lo(k[j]) : 0];
-            rb[j] = d.rep[c ? key_hi(k[j]) : 0];
-        }
-#pragma unroll
-        for (int j = 0; j < EPT; j++)
-            if ((cand >> j & 1) && ra[j] != rb[j]) mask |= 1u << j;
-    }
-    int total;
-    const int off = block_excl_scan(__popc(mask), &total);
-    const int64_t reg = d.ntiles + t;
     if (threadIdx.x == 0) d.rcnt[reg] = (unsigned long long)total;
-    if (mask) {
-        Cross *out = d.x0 + reg * TILE + off;
-        int w = 0;
-#pragma unroll
-        for (int j = 0; j < EPT; j++) {
-            if (mask >> j & 1) {
-                Cross x;
-                x.key = k[j];
-                x.pa = d.tidx[ra[j]];
-                x.pb = d.tidx[rb[j]];
-                if (x.pa < 0 || x.pb < 0) atomicOr(d.status, ST_WALK_BOUND);
-                out[w++] = x;
-            }
-        }
-    }
+    select_region(d, tab, d.x0 + reg * TILE, total);
+    tab.flush(d.best);
 }
 
 // ------------------ f4: key-edge scan restricted to the orphans (delete)
@@ -1035,7 +1075,9 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_delta(Dev d) {
 // few slots this replaces the sweep of the whole store.  Root finding left,
 // per word of the orphan bitmap, the word's orphans and their slots.
 // Prefixes over the words are taken in two levels: within groups of BLOCK
-// words here, then over the groups in k_orph_total.
+// words here, then over the groups: by every workgroup of the list fill for
+// itself, or by k_orph_total where the groups are too many for that.
+constexpr int FILL_GROUPS = 4 * BLOCK;  // groups up to which the list fill takes its own prefixes (n up to 2^24)
 __global__ __launch_bounds__(BLOCK) void k_orph_plan(Dev d) {
     if (stopped(d) || !d.ctl->has_del) return;
     const int64_t w = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
@@ -1081,8 +1123,43 @@ __global__ __launch_bounds__(BLOCK) void k_orph_total(Dev d) {
 // at a time (most words hold few).  Nothing is staged by root finding: where
 // most vertices are orphans the store is swept instead and no list is made
 // (40 bytes a vertex, 0.67 GB of the 16.7e6-vertex grid's root finding).
-__global__ __launch_bounds__(BLOCK) void k_orph_fill(Dev d) {
-    if (stopped(d) || !d.ctl->has_del || !d.cnt[C_OMODE]) return;
+// With `own` a workgroup first takes the prefixes over the groups itself
+// (they are few) and the first one publishes the totals and the choice of
+// scan, instead of a launch of one workgroup in between (4.7 us).
+__global__ __launch_bounds__(BLOCK) void k_orph_fill(Dev d, int own) {
+    if (stopped(d) || !d.ctl->has_del) return;
+    __shared__ int64_t s_gv[FILL_GROUPS];  // slots and orphans before each group
+    __shared__ int32_t s_gc[FILL_GROUPS];
+    if (own) {
+        const int64_t ng = orphan_groups(d.nvb);
+        unsigned long long v[FILL_GROUPS / BLOCK], sv = 0, sc = 0;
+#pragma unroll
+        for (int k = 0; k < FILL_GROUPS / BLOCK; k++) {
+            const int64_t g = threadIdx.x * (FILL_GROUPS / BLOCK) + k;
+            v[k] = g < ng ? d.gsum[g] : 0;
+            sv += ovol(v[k]);
+            sc += ocnt(v[k]);
+        }
+        unsigned long long tv, tc;
+        unsigned long long pv = block_excl_scan64(sv, &tv), pc = block_excl_scan64(sc, &tc);
+#pragma unroll
+        for (int k = 0; k < FILL_GROUPS / BLOCK; k++) {
+            s_gv[threadIdx.x * (FILL_GROUPS / BLOCK) + k] = (int64_t)pv;
+            s_gc[threadIdx.x * (FILL_GROUPS / BLOCK) + k] = (int32_t)pc;
+            pv += ovol(v[k]);
+            pc += ocnt(v[k]);
+        }
+        const bool om = d.ctl->smode != 1 && (int64_t)tv <= d.eb;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            d.cnt[C_OVOL] = tv;
+            d.cnt[C_NORPH] = tc;
+            d.cnt[C_OMODE] = om;
+        }
+        if (!om) return;
+        __syncthreads();
+    } else if (!d.cnt[C_OMODE]) {
+        return;
+    }
     constexpr int FILL_LANES = 8;
     constexpr int WPB = BLOCK / WAVE;  // words per vertex block
     const int64_t per_block = BLOCK / FILL_LANES;
@@ -1097,8 +1174,9 @@ __global__ __launch_bounds__(BLOCK) void k_orph_fill(Dev d) {
         uint64_t bits = d.obits[w];
         if (bits == 0) continue;
         const unsigned long long pre = d.wpre[w];
-        int64_t idx = d.gopre[w / BLOCK] + (int64_t)ocnt(pre);
-        int64_t vb = d.gpre[w / BLOCK] + (int64_t)ovol(pre);
+        const int64_t g = w / BLOCK;
+        int64_t idx = (own ? (int64_t)s_gc[g] : d.gopre[g]) + (int64_t)ocnt(pre);
+        int64_t vb = (own ? s_gv[g] : d.gpre[g]) + (int64_t)ovol(pre);
         while (bits) {  // uniform over the lanes of the word
             uint64_t m = bits;
             for (int i = 0; i < FILL_LANES; i++) {
@@ -1161,17 +1239,21 @@ __global__ __launch_bounds__(BLOCK) void k_orph_fill(Dev d) {
 // u's piece (an orphan piece, which never holds an old root); edges between
 // two orphan pieces are seen from both ends and counted once (from the
 // smaller end).
-__global__ __launch_bounds__(BLOCK) void k_orph_scan(Dev d) {
-    if (stopped(d) || !d.ctl->has_del || !d.cnt[C_OMODE]) return;
+struct ScanLds {
+    OrphEnt o[BLOCK];
+    int64_t pre[BLOCK];
+    unsigned long long min[BLOCK];   // lowest cross key per staged orphan
+    unsigned long long mink[BLOCK];  // lowest key to the old root's piece
+};
+__device__ __forceinline__ void orphan_scan(const Dev &d, ScanLds &lds, int64_t bid, int64_t nblk) {
+    OrphEnt *const s_o = lds.o;
+    int64_t *const s_pre = lds.pre;
+    unsigned long long *const s_min = lds.min, *const s_mink = lds.mink;
     const int64_t V = (int64_t)d.cnt[C_OVOL];
     const int64_t no = (int64_t)d.cnt[C_NORPH];
     const int64_t per = or_region_slots(V, d.eb) / OR_W;  // ranges per region
     const int64_t nreg = or_regions(V, d.eb);
-    __shared__ OrphEnt s_o[BLOCK];
-    __shared__ int64_t s_pre[BLOCK];
-    __shared__ unsigned long long s_min[BLOCK];   // lowest cross key per staged orphan
-    __shared__ unsigned long long s_mink[BLOCK];  // lowest key to the old root's piece
-    for (int64_t w = blockIdx.x; w < nreg; w += gridDim.x) {
+    for (int64_t w = bid; w < nreg; w += nblk) {
         Cross *const region = d.x0 + w * TILE;
         int64_t emitted = 0;
         int ncross = 0;
@@ -1381,6 +1463,33 @@ __global__ __launch_bounds__(BLOCK) void k_orph_scan(Dev d) {
     }
 }
 
+// The key edges of a delete in one launch: workgroups below ltiles take the
+// tiles of the inserted-edge list, the others the orphans' adjacency or the
+// tiles of the whole store, whichever the orphan plan chose.  The two parts
+// share nothing, and on their own neither the list's few tiles nor the
+// orphans of a small batch fill the device (R-MAT 22, b = 1e5: list 22 us,
+// orphans 13, an idle store sweep 4.5 and the selection over the list's edges
+// 9 -> 25 us together; G(1e6, 4e6): 130 -> 107).  parts: 1 list, 2 orphans, 4 store (a profiled update
+// launches them one by one).
+__global__ __launch_bounds__(BLOCK, 4) void k_key_edges(Dev d, int parts) {
+    if (stopped(d) || !d.ctl->has_del) return;
+    __shared__ union {
+        ScanLds scan;
+        SweepLds sweep;
+    } lds;
+    const int64_t nl = parts & 1 ? d.ltiles : 0;
+    if (blockIdx.x < nl) {
+        sweep_list(d, lds.sweep.tab, blockIdx.x);
+        return;
+    }
+    const int64_t bid = blockIdx.x - nl, nblk = gridDim.x - nl;
+    if (d.cnt[C_OMODE]) {
+        if (parts & 2) orphan_scan(d, lds.scan, bid, nblk);
+    } else if (parts & 4) {
+        sweep_base(d, lds.sweep, bid, nblk);
+    }
+}
+
 // ------------------------------- a6: replacement edges by hooking rounds
 
 // Hooks.  A component hooks at most once per update, so hook[] is written
@@ -1466,9 +1575,9 @@ constexpr int SEL_UNIT = SEL_K * BLOCK;  // edges per unit of a dense list
 // regions, then those behind the base store's; else all from rlo.
 struct Regions {
     int64_t om, rlo2, i0, i1;
-    __device__ __forceinline__ Regions(const Dev &d, bool with_scan) {
+    __device__ __forceinline__ explicit Regions(const Dev &d) {
         const bool scan = d.cnt[C_OMODE] != 0;
-        om = scan && with_scan ? or_regions((int64_t)d.cnt[C_OVOL], d.eb) : 0;
+        om = scan ? or_regions((int64_t)d.cnt[C_OVOL], d.eb) : 0;
         rlo2 = scan && d.ctl->rlo < d.ntiles ? d.ntiles : d.ctl->rlo;
         const int64_t total = om + (d.ctl->rhi > rlo2 ? d.ctl->rhi - rlo2 : 0);
         const int64_t per = (total + gridDim.x - 1) / gridDim.x;
@@ -1479,57 +1588,27 @@ struct Regions {
 };
 
 // Round 0: every cross edge is live and every component is a single piece.
-// Regions that the orphan scan wrote are left out: their edges took part in
-// this round's selection already.  With emit, the insert regions are not
-// filled yet: a workgroup taking one runs the insert emit for its batch
-// entries (writing the region for the next round) and selects on the edges it
-// found.  Bound by the atomics that reach memory (2.9e6 cross edges of
-// G(1e6, 4e6): 128 us with minima merged per wave, 38 with the LDS table).
-__global__ __launch_bounds__(BLOCK) void k_bor_round0(Dev d, int emit) {
-    if (stopped(d)) return;
+// The key-edge scans of a delete made their selection already, so only insert
+// edges are left: a workgroup takes a run of batch regions, runs the insert
+// emit for their batch entries if `emit` (writing the regions for the next
+// round) and selects on the edges found.  Bound by the atomics that reach
+// memory (a tree that most of the batch hooks onto is one address; R-MAT 22,
+// b = 1e6: 98 us with minima merged per wave, 71 with the LDS table).
+__global__ __launch_bounds__(BLOCK) void k_bor_round0(Dev d) {
+    if (stopped(d) || !d.ctl->has_ins) return;
     __shared__ MinTable s_min;
-    __shared__ int64_t s_cnt[BLOCK];
     s_min.clear();
-    const Regions reg(d, false);
-    const bool ins_here = emit && d.ctl->has_ins;
-    const int64_t ib = d.ctl->ibase, ie = ins_here ? ib + (d.ctl->b + BLOCK - 1) / BLOCK : ib;
-    for (int64_t w = reg.i0; w < reg.i1; w += BLOCK) {
-        const int64_t mine = w + threadIdx.x;  // the counts of this run, loaded together
-        __syncthreads();
-        s_cnt[threadIdx.x] = mine < reg.i1 ? (int64_t)d.rcnt[reg.at(mine)] : 0;
-        __syncthreads();
-        for (int64_t i = w; i < reg.i1 && i < w + BLOCK; i++) {
-            const int64_t t = reg.at(i);
-            if (t >= ib && t < ie) {  // uniform over the workgroup
-                Cross e;
-                int total;
-                if (insert_emit_block(d, t - ib, &e, &total)) {
-                    s_min.add(e.pa, e.key, d.best);
-                    s_min.add(e.pb, e.key, d.best);
-                }
-                s_min.flush_half(d.best);
-                continue;
-            }
-            const int64_t cntr = s_cnt[i - w];
-            const Cross *in = d.x0 + t * TILE;
-            for (int64_t base = 0; base < cntr; base += SEL_UNIT) {
-                Cross e[SEL_K];
-                bool live[SEL_K];
-#pragma unroll
-                for (int k = 0; k < SEL_K; k++) {
-                    const int64_t q = base + k * BLOCK + threadIdx.x;
-                    live[k] = q < cntr;
-                    if (live[k]) e[k] = in[q];
-                }
-#pragma unroll
-                for (int k = 0; k < SEL_K; k++)
-                    if (live[k]) {
-                        s_min.add(e[k].pa, e[k].key, d.best);
-                        s_min.add(e[k].pb, e[k].key, d.best);
-                    }
-                s_min.flush_half(d.best);
-            }
+    __syncthreads();
+    const int64_t total = (d.ctl->b + BLOCK - 1) / BLOCK;
+    const int64_t per = (total + gridDim.x - 1) / gridDim.x;
+    for (int64_t t = blockIdx.x * per; t < total && t < (blockIdx.x + 1) * per; t++) {
+        Cross e;
+        int found;
+        if (insert_emit_block(d, t, &e, &found)) {
+            s_min.add(e.pa, e.key, d.best);
+            s_min.add(e.pb, e.key, d.best);
         }
+        s_min.flush_half(d.best);
     }
     s_min.flush(d.best);
 }
@@ -1554,7 +1633,7 @@ __global__ __launch_bounds__(BLOCK) void k_bor_select(Dev d, int r) {
     __shared__ int64_t s_cnt[BLOCK];
     s_min.clear();
     // work units: regions of x0 (round 1) or chunks of a dense list
-    const Regions reg(d, true);
+    const Regions reg(d);
     Cross *dense = (r & 1) ? d.x0 : d.x1;
     int64_t dcount = 0, u0 = reg.i0, u1 = reg.i1, step = 1;
     if (r > 1) {
@@ -2564,52 +2643,55 @@ __global__ __launch_bounds__(BLOCK) void k_et_reverse(Dev d) {
 
 // ------------------------------------------------------------- cleanup
 
-// Resets the per-update scratch once the update has finished (or failed);
-// the workgroup that finishes last then hands status, counters and per-graph
-// batch status to the host (pinned memory, also when the update is
-// unfinished and the host continues it) and resets them once the update has
-// finished.
+// The first workgroup hands status, counters and per-graph batch status to
+// the host (pinned memory, also when the update is unfinished and the host
+// continues it) as soon as the kernel starts: they and the forest are final
+// then.  Meanwhile the others reset the per-update scratch, if the update has
+// finished (or failed), and the workgroup that arrives last the counters.
 __global__ __launch_bounds__(BLOCK) void k_cleanup(Dev d) {
     if (held(d)) return;  // queued behind an unfinished update: no handoff, no reset
     // else unfinished: the host continues (more rounds or levels, or the
     // paths too long for one thread)
     const bool fin = (d.cnt[C_ORIENTED] && !d.cnt[C_NLONG]) || *d.status;
-    if (fin) {
-        const int64_t np = (int64_t)d.cnt[C_NP];
+    const int64_t np = (int64_t)d.cnt[C_NP];
+    // the search state (not touched where super-trees grew oriented)
+    const bool searched = !d.ctl->walk || d.cnt[C_LONGTREE];
+    if (blockIdx.x == 0) {
+        if (d.adeg && d.ctl->has_del) {
+            unsigned long long e = 0;
+            for (int64_t t = threadIdx.x; t < label_groups(d.n); t += BLOCK) e += d.osum[t];
+            e = block_sum64(e);
+            if (threadIdx.x == 0) d.cnt[C_OSLOTS] = e;
+            __syncthreads();
+        }
+        for (int64_t t = threadIdx.x; t < d.ret_words; t += BLOCK) d.hret[t] = d.ctlmem[t];
+        __threadfence_system();
+        __syncthreads();  // every thread has copied before the completion word
+        if (threadIdx.x == 0) {
+            if (!fin) d.status[1] = 1;  // later updates on the stream wait for the host's continuation
+            __hip_atomic_store(d.hdone, (unsigned long long)d.ctl->seq, __ATOMIC_RELEASE,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+    if (!fin) return;
+    if (blockIdx.x > 0 || gridDim.x == 1) {
         const int64_t b = d.ctl->b;
-        const int64_t stride = (int64_t)gridDim.x * BLOCK;
-        for (int64_t p = (int64_t)blockIdx.x * BLOCK + threadIdx.x; p < np; p += stride) {
+        const int64_t nw = gridDim.x > 1 ? gridDim.x - 1 : 1, w = gridDim.x > 1 ? blockIdx.x - 1 : 0;
+        const int64_t stride = nw * BLOCK, t0 = w * BLOCK + threadIdx.x;
+        for (int64_t p = t0; p < np; p += stride) {
             d.tidx[d.prt[p]] = NONE;
-            d.level[p] = -1;  // the super-forest search starts from all -1
-            d.parc[p] = NONE;
+            if (searched) {
+                d.level[p] = -1;  // the super-forest search starts from all -1
+                d.parc[p] = NONE;
+            }
             if (d.et_support) d.et_support[d.prt[p]] = NONE;  // path ends are piece roots
         }
-        for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < b; i += stride)
+        for (int64_t i = t0; i < b; i += stride)
             if (d.bslot[i] != NONE) d.bhash[d.bslot[i]] = HASH_EMPTY;
         const int64_t rlo = d.ctl->rlo, rhi = d.ctl->rhi;  // read once: the stores may alias them
-        for (int64_t t = rlo + (int64_t)blockIdx.x * BLOCK + threadIdx.x; t < rhi; t += stride)
-            d.rcnt[t] = 0;
+        for (int64_t t = rlo + t0; t < rhi; t += stride) d.rcnt[t] = 0;
     }
     if (!last_block_arrives(&d.cnt[C_ARRIVE])) return;
-    if (d.adeg && d.ctl->has_del) {
-        unsigned long long e = 0;
-        for (int64_t t = threadIdx.x; t < label_groups(d.n); t += BLOCK) e += d.osum[t];
-        e = block_sum64(e);
-        if (threadIdx.x == 0) d.cnt[C_OSLOTS] = e;
-        __syncthreads();
-    }
-    for (int64_t t = threadIdx.x; t < d.ret_words; t += BLOCK) d.hret[t] = d.ctlmem[t];
-    __threadfence_system();
-    __syncthreads();  // every thread has copied before the completion word and any reset
-    if (!fin) {
-        // later updates on the stream wait for the host's continuation
-        if (threadIdx.x == 0) d.status[1] = 1;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        __hip_atomic_store(d.hdone, (unsigned long long)d.ctl->seq, __ATOMIC_RELEASE,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
-    if (!fin) return;
     const int t = threadIdx.x;
     for (int u = t; u < C_TOTAL; u += BLOCK)
         if (u != C_NDELTA && u != C_NFREE) d.cnt[u] = 0;
@@ -2667,36 +2749,30 @@ void launch_rep_chase(const Dev &d, hipStream_t s) {
     else
         hipLaunchKernelGGL(k_rep_chase<2>, dim3(grid_for(d.nvb, 2, GRID_CAP)), dim3(BLOCK), 0, s, d);
 }
-void launch_sweep_base(const Dev &d, hipStream_t s) {
-    // persistent: about as many workgroups as fit at once (24 KB of LDS each)
-    if (d.ntiles > 0)
-        hipLaunchKernelGGL(k_sweep_base, dim3(grid_for(d.ntiles, 1, 6 * 256)), dim3(BLOCK), 0, s, d);
-}
 void launch_orphan_plan(const Dev &d, hipStream_t s) {
     hipLaunchKernelGGL(k_orph_plan, dim3((unsigned)orphan_groups(d.nvb)), dim3(BLOCK), 0, s, d);
-    hipLaunchKernelGGL(k_orph_total, dim3(1), dim3(BLOCK), 0, s, d);
+    if (orphan_groups(d.nvb) > FILL_GROUPS) hipLaunchKernelGGL(k_orph_total, dim3(1), dim3(BLOCK), 0, s, d);
 }
 void launch_orphan_fill(const Dev &d, hipStream_t s) {
-    hipLaunchKernelGGL(k_orph_fill, dim3(grid_for(orphan_words(d.nvb), BLOCK / 8, GRID_CAP)), dim3(BLOCK), 0, s, d);
+    hipLaunchKernelGGL(k_orph_fill, dim3(grid_for(orphan_words(d.nvb), BLOCK / 8, GRID_CAP)), dim3(BLOCK), 0, s, d,
+                       orphan_groups(d.nvb) <= FILL_GROUPS ? 1 : 0);
 }
-void launch_orphan_scan(const Dev &d, hipStream_t s) {
-    hipLaunchKernelGGL(k_orph_scan, dim3(grid_for(d.ntiles, 1, GRID_CAP)), dim3(BLOCK), 0, s, d);
-}
-void launch_sweep_delta(const Dev &d, hipStream_t s) {
-    if (d.ltiles > 0)
-        hipLaunchKernelGGL(k_sweep_delta, dim3((unsigned)d.ltiles), dim3(BLOCK), 0, s, d);
+void launch_key_edges(const Dev &d, int parts, hipStream_t s) {
+    // persistent over orphan regions and store tiles
+    const int64_t g = (parts & 1 ? d.ltiles : 0) + (parts & 6 ? grid_for(d.ntiles, 1, GRID_CAP) : 0);
+    if (g > 0) hipLaunchKernelGGL(k_key_edges, dim3((unsigned)g), dim3(BLOCK), 0, s, d, parts);
 }
 // The hooking, rooting and reversal kernels index pieces, arcs and paths
 // (at most 2 max_batch): grids of one workgroup per CU, grid-stride, so a
 // round that finds nothing to do costs little dispatch.
-void launch_boruvka(const Dev &d, int r0, int r1, int64_t units, bool emit, hipStream_t s) {
+void launch_boruvka(const Dev &d, int r0, int r1, int64_t units, bool ins, hipStream_t s) {
     const int ge = grid_for(units, 1, EDGE_CAP);
     const int gp = grid_for(piece_bound(d), BLOCK, SMALL_CAP);
     for (int r = r0; r < r1; r++) {
-        if (r == 0)
-            hipLaunchKernelGGL(k_bor_round0, dim3(ge), dim3(BLOCK), 0, s, d, emit ? 1 : 0);
-        else
+        if (r > 0)
             hipLaunchKernelGGL(k_bor_select, dim3(r == 1 ? ge : gp), dim3(BLOCK), 0, s, d, r);
+        else if (ins)
+            hipLaunchKernelGGL(k_bor_round0, dim3(grid_for(d.lb, BLOCK, EMIT_CAP)), dim3(BLOCK), 0, s, d);
         hipLaunchKernelGGL(k_bor_hook, dim3(gp), dim3(BLOCK), 0, s, d, r);
     }
     // the tail reads a dense list, which rounds from 2 on have
@@ -2803,7 +2879,7 @@ int launch_et_reverse(const Dev &d, void *tmp, size_t tmp_bytes, hipStream_t s) 
 void launch_cleanup(const Dev &d, hipStream_t s) {
     const int64_t m = std::max<int64_t>(piece_bound(d), d.lb);
     // few workgroups: each arrives once on one counter (serialised atomics)
-    hipLaunchKernelGGL(k_cleanup, dim3(grid_for(m, BLOCK, CLEANUP_CAP)), dim3(BLOCK), 0, s, d);
+    hipLaunchKernelGGL(k_cleanup, dim3(1 + grid_for(m, BLOCK, CLEANUP_CAP)), dim3(BLOCK), 0, s, d);
 }
 
 // ------------------------------------------------------ store rebuild
