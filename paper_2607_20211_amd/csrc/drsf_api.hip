@@ -49,6 +49,8 @@ constexpr int CREATE_DEEP_LOG = 16;
 enum Phase { PH_VALIDATE, PH_UPDATE, PH_ROOT, PH_ORPH_LIST, PH_ORPH_SCAN, PH_SWEEP, PH_SWEEP_DELTA,
              PH_REPL, PH_ROOTING, PH_FINISH, PH_N };
 
+constexpr int64_t PINNED_BATCH = 8192;  // host batches read in place from pinned memory
+
 // The inserted-edge list is merged into the base store every delta_capacity
 // inserts, or kept when at most an eighth of that many of its entries are
 // live; so it can hold that many more.
@@ -187,6 +189,13 @@ struct drsf_ctx {
     // tour queued after the search (it skips itself when the search
     // sufficed), set once a walk of those was too long
     unsigned walk_kinds = 0, lr_kinds = 0;
+    // small batches run their rounds in one workgroup: a delete after
+    // solo_from full-grid selections, one more for each time its list of live
+    // edges was still too long for it (past SOLO_ROUND_MAX all rounds are
+    // full-grid ones); and whether the update being queued, or waited for,
+    // does (its solo_from, or 0)
+    int solo_from = 1;
+    int solo = 0;
     // status word, counters and per-graph batch status share one allocation
     // so that one copy returns them: status at word 0, counters from word 1,
     // gstat after the counters
@@ -225,6 +234,7 @@ struct drsf_ctx {
         int kind, op;
         int64_t b;
         int64_t nins;  // inserts into the edge store
+        int solo;      // its rounds ran in one workgroup: after so many selections
     } pend[2] = {};
     int npend = 0;
     // results of updates that a call of the library waited for on the
@@ -1113,6 +1123,16 @@ bool walks(const drsf_ctx *c, int kind) {
 // search levels queued
 int levels_of(const drsf_ctx *c, int kind) { return walks(c, kind) ? 0 : c->bfs_fast; }
 
+// A sequence laid out for lb batch edges runs its rounds in one workgroup,
+// after so many full-grid selections (0: it does not).  A schedule set by the
+// caller is kept to, a profiled one has its phases apart.
+int solo_update(const drsf_ctx *c, int kind, int64_t lb) {
+    if (c->opts.profile || c->ngraph > 1 || c->opts.replacement_mode != 0 || c->opts.rounds_queued > 0 ||
+        c->opts.levels_queued > 0 || (c->lr_kinds & (1u << kind)) || lb > SOLO_BATCH)
+        return 0;
+    return kind == 1 ? 1 : c->solo_from <= SOLO_ROUND_MAX ? c->solo_from : 0;
+}
+
 // The update sequence (see the file comment) for batches with inserts
 // (kind bit 1) and/or deletes (kind bit 2); with events when profiling.
 // kc: the control block, passed with the first kernel when the sequence is
@@ -1156,12 +1176,19 @@ void enqueue_update(drsf_ctx *c, int kind, bool profile, const Ctl *kc) {
             launch_fill_i32(c->status, 1, ST_ROUND_BOUND, c->s2);
         (void)hipEventRecord(c->ev_join, c->s2);
     }
+    const int levels = levels_of(c, kind);
+    const int solo = solo_update(c, kind, d.lb);
+    const bool front = solo && d.lb <= SOLO_FRONT;
     mark(PH_VALIDATE);
-    launch_classify(d, kc, s);
-    if (c->opts.validate_batches) launch_dedupe(d, s);
-    mark(PH_UPDATE);
-    launch_prepare(d, del, s);
-    launch_register(d, s);
+    if (front) {
+        launch_solo_front(d, kc, ins, levels, s);
+    } else {
+        launch_classify(d, kc, s);
+        if (c->opts.validate_batches) launch_dedupe(d, s);
+        mark(PH_UPDATE);
+        launch_prepare(d, del, s);
+        launch_register(d, s);
+    }
     mark(PH_ROOT, del);
     if (del && c->jump_rounds) launch_rep_jump(d, c->jump_rounds, s);
     if (del) launch_rep_chase(d, s);
@@ -1183,7 +1210,10 @@ void enqueue_update(drsf_ctx *c, int kind, bool profile, const Ctl *kc) {
     if (del && profile) launch_key_edges(d, 1, s);
     mark(PH_REPL);
     const int64_t units = (ins ? insert_regions(d.lb) : 0) + (del ? c->ntiles + d.ltiles : 0);
-    if (sg) {  // supergraph, then its rounds
+    if (solo) {  // the rounds and the rooting
+        c->round_base = 0;
+        if (!(front && ins)) launch_solo_rounds(d, ins, solo, units, levels, s);
+    } else if (sg) {  // supergraph, then its rounds
         c->round_base = SG_ROUND0;
         if (sg_reduce(c, d, s)) launch_fill_i32(c->status, 1, ST_ROUND_BOUND, s);
         launch_boruvka(d, SG_ROUND0, SG_ROUND0 + c->bor_fast, units, false, s);
@@ -1192,10 +1222,11 @@ void enqueue_update(drsf_ctx *c, int kind, bool profile, const Ctl *kc) {
         launch_boruvka(d, 0, c->bor_fast, units, ins, s);
     }
     mark(PH_ROOTING);
-    launch_sf_root(d, c->opts.replacement_mode != 1, s);
-    const int levels = levels_of(c, kind);
-    launch_sf_bfs(d, 0, levels, s);
-    launch_orient_bfs(d, levels, s);
+    if (!solo) {
+        launch_sf_root(d, c->opts.replacement_mode != 1, s);
+        launch_sf_bfs(d, 0, levels, s);
+        launch_orient_bfs(d, levels, s);
+    }
     if (c->lr_kinds & (1u << kind)) launch_superforest_lr(d, tour_rounds(c), levels, s);
     mark(PH_FINISH);
     const bool et = c->opts.reverse_mode == 1;
@@ -1259,6 +1290,7 @@ int continue_update(drsf_ctx *c) {
     // profiled contexts time the continuation, host round trips included
     c->cont_timed = c->have_phases;
     const int queued = levels_of(c, c->kind);  // search levels in the sequence
+    const int solo = c->solo;
     if (!oriented) {
         if ((rc = read_flags(queued))) return rc;
     }
@@ -1268,6 +1300,10 @@ int continue_update(drsf_ctx *c) {
     int r = c->round_base + c->bor_fast, lv = queued;
     if (!oriented && !bad && !done) {
         how |= 1;
+        if (solo) {  // left at the hooks of that round
+            launch_bor_hook(d, solo, s);
+            r = solo + 1;
+        }
         while (!done && !bad && r < bor_bound) {
             const int r1 = std::min(r + BOR_CHUNK, bor_bound);
             launch_boruvka(d, r, r1, 4096, false, s);
@@ -1325,7 +1361,11 @@ int continue_update(drsf_ctx *c) {
     // the tour
     if (!bad) {
         bool grew = false;
-        if ((how & 1) && c->opts.rounds_queued <= 0 && r - c->round_base > c->bor_fast) {
+        if ((how & 1) && solo) {
+            c->solo_from = solo + 1;
+            grew = true;
+        }
+        if ((how & 1) && !solo && c->opts.rounds_queued <= 0 && r - c->round_base > c->bor_fast) {
             c->bor_fast = std::min(r - c->round_base, AUTO_ROUNDS_MAX);
             grew = true;
         }
@@ -1365,7 +1405,9 @@ int launch_update(drsf_ctx *c) {
     // the device then goes from one update to the next as from one kernel
     // to the next, where a graph launch starts some microseconds after the
     // work before it
-    if (prof || c->opts.replacement_mode == 1 || c->npend > 0 || !graph_launch(c)) {
+    const bool graph = !(prof || c->opts.replacement_mode == 1 || c->npend > 0 || !graph_launch(c));
+    c->solo = solo_update(c, c->kind, graph ? c->max_batch : std::max<int64_t>(c->h_ctl->b, 1));
+    if (!graph) {
         enqueue_update(c, c->kind, prof, c->h_ctl);
     } else {
         int rc;
@@ -1373,7 +1415,7 @@ int launch_update(drsf_ctx *c) {
         HIPCHK(c, hipGraphLaunch(c->gexec[c->slot][c->kind], s));
     }
     HIPCHK(c, hipGetLastError());
-    c->pend[c->slot] = drsf_ctx::Pend{c->seq, c->kind, c->last_op, c->last_b, c->last_nins};
+    c->pend[c->slot] = drsf_ctx::Pend{c->seq, c->kind, c->last_op, c->last_b, c->last_nins, c->solo};
     c->last_slot = c->slot;
     c->npend++;
     c->have_phases = prof;
@@ -1386,6 +1428,7 @@ int relaunch_update(drsf_ctx *c, int q) {
     select_slot(c, q);
     c->kind = c->pend[q].kind;
     c->h_ctl->walk = walks(c, c->kind);  // the host's continuation may have changed it
+    c->pend[q].solo = solo_update(c, c->kind, graph_launch(c) ? c->max_batch : std::max<int64_t>(c->h_ctl->b, 1));
     if (!graph_launch(c)) {
         enqueue_update(c, c->kind, false, c->h_ctl);
     } else {
@@ -1446,15 +1489,18 @@ void set_regions(drsf_ctx *c, Ctl &k) {
     }
 }
 
-int stage_edges(drsf_ctx *c, const int32_t *edges, int64_t b) {
+int stage_edges(drsf_ctx *c, const int32_t *edges, int64_t b, bool in_place) {
     if (b == 0) return DRSF_OK;
     hipStream_t s = c->stream;
     if (c->opts.inputs_on_device) {
         HIPCHK(c, hipMemcpyAsync(c->bedges, edges, sizeof(int32_t) * 2 * (size_t)b,
                                  hipMemcpyDeviceToDevice, s));
     } else {
-        // the previous update has completed, so the pinned staging is free
+        // the previous update has completed, so the pinned staging is free;
+        // a small batch is read from there by the first kernel (a copy costs
+        // the host about 10 us)
         memcpy(c->h_edges, edges, sizeof(int32_t) * 2 * (size_t)b);
+        if (in_place && b <= PINNED_BATCH) return DRSF_OK;
         HIPCHK(c, hipMemcpyAsync(c->bedges, c->h_edges, sizeof(int32_t) * 2 * (size_t)b,
                                  hipMemcpyHostToDevice, s));
     }
@@ -1799,7 +1845,7 @@ int drsf_apply_async(drsf_ctx *c, const int32_t *edges, int64_t b, int op) {
     }
     // a device batch is read in place by the first kernel (the stream orders
     // it before later work the caller queues there); a host batch is staged
-    if (!c->opts.inputs_on_device && (rc = stage_edges(c, edges, b))) return rc;
+    if (!c->opts.inputs_on_device && (rc = stage_edges(c, edges, b, true))) return rc;
     c->last_b = b;
     c->last_op = op;
     // queued updates alternate between the two slots; one waited for alone
@@ -1808,6 +1854,7 @@ int drsf_apply_async(drsf_ctx *c, const int32_t *edges, int64_t b, int op) {
     Ctl &k = *c->h_ctl;
     memset(&k, 0, sizeof k);
     if (c->opts.inputs_on_device) k.edges = edges;
+    else if (b <= PINNED_BATCH) k.edges = c->h_edges;
     k.b = b;
     k.op = op;
     k.has_ins = op == DRSF_INSERT;
@@ -1942,7 +1989,7 @@ int drsf_multi_apply_async(drsf_ctx *c, const int32_t *edges, const int64_t *b_o
         HIPCHK(c, hipMemcpyAsync(c->bop, c->h_bop, (size_t)b, hipMemcpyHostToDevice, s));
         HIPCHK(c, hipMemcpyAsync(c->bgid, c->h_bgid, sizeof(int32_t) * (size_t)b, hipMemcpyHostToDevice, s));
     }
-    if ((rc = stage_edges(c, edges, b))) return rc;
+    if ((rc = stage_edges(c, edges, b, false))) return rc;
     Ctl &k = *c->h_ctl;
     memset(&k, 0, sizeof k);
     k.b = b;
@@ -1979,6 +2026,7 @@ int wait_oldest(drsf_ctx *c) {
     c->kind = c->pend[q].kind;
     c->last_b = c->pend[q].b;
     c->last_op = c->pend[q].op;
+    c->solo = c->pend[q].solo;
     c->npend--;
     // the last kernel writes the completion word once the results in
     // h_ret are final: poll it (a stream synchronisation wakes up later),

@@ -233,6 +233,20 @@ constexpr int MAX_ROUNDS = 64;
 // live cross-edge list it takes on
 constexpr int TAIL_THREADS = 1024;
 constexpr int64_t TAIL_MAX = 4096;
+// small batches: the workgroup that takes whole steps of an update, the batch
+// sizes up to which it takes the front and the rounds, and the longest list
+// of live edges
+constexpr int SOLO_THREADS = 1024;
+static_assert(SOLO_THREADS == TAIL_THREADS, "the workgroup runs the same rounds");
+#ifndef DRSF_SOLO_FRONT
+#define DRSF_SOLO_FRONT 512
+#endif
+#ifndef DRSF_SOLO_BATCH
+#define DRSF_SOLO_BATCH 4096
+#endif
+constexpr int64_t SOLO_FRONT = DRSF_SOLO_FRONT;
+constexpr int64_t SOLO_BATCH = DRSF_SOLO_BATCH;
+constexpr int64_t SOLO_LIST = 8192;
 // extra counter slots: per-round activity flags
 constexpr int C_LR_ROUND = C_COUNT + MAX_ROUNDS;       // [MAX_ROUNDS]
 constexpr int C_BFS_ROUND = C_COUNT + 2 * MAX_ROUNDS;  // [MAX_ROUNDS]
@@ -326,6 +340,14 @@ void launch_key_edges(const Dev &d, int parts, hipStream_t s);
 // rounds [r0, r1); ins: round 0 emits the insert cross edges and selects on
 // them (a delete's scans have made their selection)
 void launch_boruvka(const Dev &d, int r0, int r1, int64_t units, bool ins, hipStream_t s);
+void launch_bor_hook(const Dev &d, int r, hipStream_t s);
+// small batches in one workgroup: up to the cut and the registration (an
+// insert: up to the orientation); and from an insert's cross edges, or a
+// delete's hooks of round r, to the orientation (levels 0: super-trees
+// oriented as they grow)
+void launch_solo_front(const Dev &d, const Ctl *kc, bool ins, int levels, hipStream_t s);
+void launch_solo_rounds(const Dev &d, bool ins, int r, int64_t units, int levels, hipStream_t s);
+constexpr int SOLO_ROUND_MAX = 4;  // full-grid rounds before the workgroup's, at most
 // count: also the number of cross edges found (the supergraph counts its own)
 void launch_sf_root(const Dev &d, bool count, hipStream_t s);
 void launch_sf_bfs(const Dev &d, int l0, int l1, hipStream_t s);

@@ -26,6 +26,8 @@ int grid_for(int64_t items, int64_t per_block, int cap) {
 
 // ------------------------------------------------------------------ helpers
 
+typedef int v4i __attribute__((ext_vector_type(4)));
+
 // Position of column v in the ascending run col[lo, hi) (tombstone bits
 // ignored), or -1; *raw receives the stored entry.  Each step loads
 // SEARCH_FAN evenly spaced entries at once and keeps the part of the run
@@ -142,9 +144,10 @@ __device__ __forceinline__ void init_piece(const Dev &d, int64_t id, int32_t v, 
 }
 
 // Exclusive scan of one int per thread over the block; also returns the total.
-// Every thread of the block must call it.
+// Every thread of the block (NT of them) must call it.
+template <int NT = BLOCK>
 __device__ int block_excl_scan(int x, int *total) {
-    __shared__ int wsum[BLOCK / WAVE];
+    __shared__ int wsum[NT / WAVE];
     const int lane = lane_id(), wid = threadIdx.x / WAVE;
     int inc = x;
 #pragma unroll
@@ -156,7 +159,7 @@ __device__ int block_excl_scan(int x, int *total) {
     __syncthreads();
     int before = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < BLOCK / WAVE; w++) {
+    for (int w = 0; w < NT / WAVE; w++) {
         before += w < wid ? wsum[w] : 0;
         tot += wsum[w];
     }
@@ -216,10 +219,11 @@ __device__ __forceinline__ unsigned long long ocnt(unsigned long long p) { retur
 // Block-aggregated append: each thread reserves k consecutive slots of
 // *counter and gets the first; one atomic per workgroup (a counter shared by
 // the whole grid is a hot address).  Every thread of the block must call it.
+template <int NT = BLOCK>
 __device__ int64_t block_append(int k, unsigned long long *counter) {
     __shared__ unsigned long long s_base;
     int total;
-    const int off = block_excl_scan(k, &total);
+    const int off = block_excl_scan<NT>(k, &total);
     if (threadIdx.x == 0 && total) s_base = atomicAdd(counter, (unsigned long long)total);
     __syncthreads();
     const int64_t r = (int64_t)s_base + off;
@@ -280,33 +284,29 @@ __device__ __forceinline__ int64_t list_block(const int32_t *list, int64_t cnt, 
 // the child endpoint of a tree edge (parent[u] == v or parent[v] == u;
 // Algorithm 1, the cut step).  Errors mark the edge's graph as rejected;
 // nothing but batch scratch is written.
-__global__ __launch_bounds__(BLOCK) void k_classify(Dev d, Ctl kc, int from_arg) {
-    if (held(d)) return;  // the device copy of the control block still serves the held update
-    // the update's control block comes from pinned host memory (a captured
-    // launch) or with the launch (a kernel-by-kernel one); the first
-    // workgroup publishes it for the later kernels, which read the device copy
+// The update's control block comes from pinned host memory (a captured
+// launch) or with the launch (a kernel-by-kernel one); the first workgroup
+// publishes it for what follows, which reads the device copy.
+struct BatchHead {
     int64_t b;
-    int opm, revive;
+    int op, revive;
     const int32_t *edges;
+};
+__device__ __forceinline__ BatchHead publish_ctl(const Dev &d, const Ctl &kc, int from_arg) {
     if (from_arg) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *d.ctlw = kc;
-        b = kc.b;
-        opm = kc.op;
-        revive = kc.revive;
-        edges = kc.edges;
-    } else {
-        const Ctl *hc = d.hctl;
-        if (blockIdx.x == 0 && threadIdx.x < sizeof(Ctl) / 8)
-            reinterpret_cast<uint64_t *>(d.ctlw)[threadIdx.x] =
-                reinterpret_cast<const uint64_t *>(hc)[threadIdx.x];
-        b = hc->b;
-        opm = hc->op;
-        revive = hc->revive;
-        edges = hc->edges;
+        return BatchHead{kc.b, kc.op, kc.revive, kc.edges};
     }
-    const int32_t *be = edges ? edges : d.bedges;  // caller's device batch, or the staged one
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < b; i += stride) {
+    const Ctl *hc = d.hctl;
+    if (blockIdx.x == 0 && threadIdx.x < sizeof(Ctl) / 8)
+        reinterpret_cast<uint64_t *>(d.ctlw)[threadIdx.x] = reinterpret_cast<const uint64_t *>(hc)[threadIdx.x];
+    return BatchHead{hc->b, hc->op, hc->revive, hc->edges};
+}
+__device__ __forceinline__ void classify_edges(const Dev &d, const BatchHead &hd, int64_t t0, int64_t stride) {
+    const int64_t b = hd.b;
+    const int opm = hd.op, revive = hd.revive;
+    const int32_t *be = hd.edges ? hd.edges : d.bedges;  // caller's device batch, or the staged one
+    for (int64_t i = t0; i < b; i += stride) {
         d.bslot[i] = NONE;
         d.bchild[i] = NONE;
         d.bloc[i] = 0;
@@ -375,16 +375,19 @@ __global__ __launch_bounds__(BLOCK) void k_classify(Dev d, Ctl kc, int from_arg)
     }
 }
 
+__global__ __launch_bounds__(BLOCK) void k_classify(Dev d, Ctl kc, int from_arg) {
+    if (held(d)) return;  // the device copy of the control block still serves the held update
+    const BatchHead hd = publish_ctl(d, kc, from_arg);
+    classify_edges(d, hd, (int64_t)blockIdx.x * BLOCK + threadIdx.x, (int64_t)gridDim.x * BLOCK);
+}
+
 // Repeated pairs inside the batch.  Equal keys hash to one slot and exactly
 // one of their stamps survives, so an edge that finds another edge's stamp
 // compares keys: equal is a repeat; different is a collision, and such edges
 // claim their key in a table with compare-and-swap, where repeats among them
 // meet.  Only the colliding edges (about 1 in 16) pay for an atomic.
-__global__ __launch_bounds__(BLOCK) void k_dedupe(Dev d) {
-    if (held(d)) return;
-    const int64_t b = d.ctl->b;
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < b; i += stride) {
+__device__ __forceinline__ void dedupe_edges(const Dev &d, int64_t b, int64_t t0, int64_t stride) {
+    for (int64_t i = t0; i < b; i += stride) {
         const uint64_t k = d.bkey[i];
         if (k == 0) continue;  // rejected pair (its graph is marked already)
         const int32_t j = d.dslot[hmix(k) & d.dsmask];
@@ -411,6 +414,11 @@ __global__ __launch_bounds__(BLOCK) void k_dedupe(Dev d) {
     }
 }
 
+__global__ __launch_bounds__(BLOCK) void k_dedupe(Dev d) {
+    if (held(d)) return;
+    dedupe_edges(d, d.ctl->b, (int64_t)blockIdx.x * BLOCK + threadIdx.x, (int64_t)gridDim.x * BLOCK);
+}
+
 // ---------------------------- a2 + a3: update the edge store, cut tree edges
 
 // An inserted edge whose deleted entry is still in the base store gets that
@@ -429,11 +437,10 @@ __global__ __launch_bounds__(BLOCK) void k_dedupe(Dev d) {
 // finding instead: rep <- parent over the listed vertex blocks, one wave per
 // block, four vertices per lane (16-byte accesses).  A cut child may be
 // copied before or after its cut; k_register then sets rep[c] = c.
-__device__ void rep_init(const Dev &d, int64_t bid, int64_t nblk) {
+__device__ void rep_init(const Dev &d, int64_t nvl_list, int64_t bid, int64_t nblk) {
     typedef int v4i __attribute__((ext_vector_type(4)));
     const int64_t nb = (d.n + BLOCK - 1) / BLOCK;
     const int w = threadIdx.x / WAVE;
-    const int64_t nvl_list = d.ctl->nvl;  // read once: stores below may alias it
     for (int64_t j = bid * (BLOCK / WAVE) + w;; j += nblk * (BLOCK / WAVE)) {
         const int64_t blk = list_block(d.vlist, nvl_list, j, nb);
         if (blk < 0) break;
@@ -446,18 +453,13 @@ __device__ void rep_init(const Dev &d, int64_t bid, int64_t nblk) {
     }
 }
 
-__global__ __launch_bounds__(BLOCK) void k_prepare(Dev d, int gb) {
-    if (stopped(d)) return;
-    if ((int)blockIdx.x >= gb) {
-        if (d.ctl->has_del) rep_init(d, (int64_t)blockIdx.x - gb, (int64_t)gridDim.x - gb);
-        return;
-    }
+template <int NT>
+__device__ __forceinline__ void prepare_edges(const Dev &d, int64_t bid, int64_t nblk) {
     const int64_t b = d.ctl->b;
     const bool has_ins = d.ctl->has_ins, has_del = d.ctl->has_del;
     // free positions and length of the inserted-edge list before this update
     const int64_t nfree = (int64_t)d.cnt[C_NFREE], nd = (int64_t)d.cnt[C_NDELTA];
-    const int64_t stride = (int64_t)gb * BLOCK;
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < b; base += stride) {
+    for (int64_t base = bid * NT; base < b; base += nblk * NT) {
         const int64_t i = base + threadIdx.x;
         const bool valid = i < b && edge_op(d, i) != 2 && edge_ok(d, i);
         const int op = valid ? edge_op(d, i) : -1;
@@ -479,7 +481,7 @@ __global__ __launch_bounds__(BLOCK) void k_prepare(Dev d, int gb) {
         }
         if (has_del) {  // uniform over the grid
             const bool list = op == 1 && loc < 0;
-            const int64_t at = block_append(list ? 1 : 0, &d.cnt[C_FREED]);
+            const int64_t at = block_append<NT>(list ? 1 : 0, &d.cnt[C_FREED]);
             if (list) {  // its index slot is marked deleted in k_register, after the inserts' probes
                 const int32_t pos = d.dhpos[-loc - 1];
                 d.dkey[pos] = KEY_DEAD;
@@ -489,7 +491,7 @@ __global__ __launch_bounds__(BLOCK) void k_prepare(Dev d, int gb) {
         }
         if (has_ins) {
             const bool list = op == 0 && loc < 0;
-            const int64_t at = block_append(list ? 1 : 0, &d.cnt[C_LISTED]);
+            const int64_t at = block_append<NT>(list ? 1 : 0, &d.cnt[C_LISTED]);
             if (op == 0) {
                 const uint64_t k = d.bkey[i];
                 if (list) {
@@ -511,15 +513,25 @@ __global__ __launch_bounds__(BLOCK) void k_prepare(Dev d, int gb) {
     }
 }
 
+__global__ __launch_bounds__(BLOCK) void k_prepare(Dev d, int gb) {
+    if (stopped(d)) return;
+    if ((int)blockIdx.x >= gb) {
+        if (d.ctl->has_del) rep_init(d, d.ctl->nvl, (int64_t)blockIdx.x - gb, (int64_t)gridDim.x - gb);
+        return;
+    }
+    prepare_edges<BLOCK>(d, blockIdx.x, gb);
+}
+
 // The list's length and free positions after the update (one workgroup):
 // the inserts took free positions from the end of dfree first, the deletes
 // appended theirs behind it; with both, appended ones fill the taken places.
-__device__ void settle_list(const Dev &d) {
+template <int NT>
+__device__ __forceinline__ void settle_list(const Dev &d) {
     const int64_t nfree = (int64_t)d.cnt[C_NFREE];
     const int64_t listed = (int64_t)d.cnt[C_LISTED], freed = (int64_t)d.cnt[C_FREED];
     const int64_t taken = listed < nfree ? listed : nfree;
     const int64_t move = taken < freed ? taken : freed;
-    for (int64_t i = threadIdx.x; i < move; i += BLOCK)
+    for (int64_t i = threadIdx.x; i < move; i += NT)
         d.dfree[nfree - taken + i] = d.dfree[nfree + freed - 1 - i];
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -529,11 +541,10 @@ __device__ void settle_list(const Dev &d) {
 }
 
 // Dense ids for the nominated pieces: the owning batch entry registers.
-__global__ __launch_bounds__(BLOCK) void k_register(Dev d) {
-    if (stopped(d)) return;
+template <int NT>
+__device__ __forceinline__ void register_pieces(const Dev &d, int64_t bid, int64_t nblk) {
     const int64_t b = d.ctl->b;
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < b; base += stride) {
+    for (int64_t base = bid * NT; base < b; base += nblk * NT) {
         const int64_t i = base + threadIdx.x;
         int32_t a = NONE, c2 = NONE;
         bool del = false;
@@ -556,12 +567,16 @@ __global__ __launch_bounds__(BLOCK) void k_register(Dev d) {
         }
         const bool ga = a != NONE && d.owner[a] == (int32_t)(2 * i);
         const bool gb = c2 != NONE && d.owner[c2] == (int32_t)(2 * i + 1);
-        const int64_t ia = block_append((ga ? 1 : 0) + (gb ? 1 : 0), &d.cnt[C_NP]);
+        const int64_t ia = block_append<NT>((ga ? 1 : 0) + (gb ? 1 : 0), &d.cnt[C_NP]);
         const int64_t ib = ia + (ga ? 1 : 0);
         if (ga) init_piece(d, ia, a, false);
         if (gb) init_piece(d, ib, c2, del);
     }
-    if (blockIdx.x == 0) settle_list(d);
+    if (bid == 0) settle_list<NT>(d);
+}
+__global__ __launch_bounds__(BLOCK) void k_register(Dev d) {
+    if (stopped(d)) return;
+    register_pieces<BLOCK>(d, blockIdx.x, gridDim.x);
 }
 
 // Live edges of each vertex: its entries in the store's two halves, less the
@@ -815,7 +830,6 @@ __global__ __launch_bounds__(BLOCK) void k_rep_chase(Dev d) {
 // rep for the flagged edges.  Cross edges go to the
 // tile's own region of x0, and take part in the first hooking round's
 // selection from here (their keys meet in the LDS table).
-typedef int v4i __attribute__((ext_vector_type(4)));
 constexpr int HALF = EPT / 2;
 // the selection over a region that this workgroup has just written
 __device__ __forceinline__ void select_region(const Dev &d, MinTable &tab, const Cross *region, int count) {
@@ -1077,7 +1091,9 @@ __device__ __forceinline__ void sweep_list(const Dev &d, MinTable &tab, int64_t 
 // Prefixes over the words are taken in two levels: within groups of BLOCK
 // words here, then over the groups: by every workgroup of the list fill for
 // itself, or by k_orph_total where the groups are too many for that.
-constexpr int FILL_GROUPS = 4 * BLOCK;  // groups up to which the list fill takes its own prefixes (n up to 2^24)
+// groups up to which the list fill takes its own prefixes (n up to 2^25); with
+// no more words than that (n up to 2^17) over the words themselves, unplanned
+constexpr int FILL_GROUPS = 8 * BLOCK;
 __global__ __launch_bounds__(BLOCK) void k_orph_plan(Dev d) {
     if (stopped(d) || !d.ctl->has_del) return;
     const int64_t w = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
@@ -1124,19 +1140,20 @@ __global__ __launch_bounds__(BLOCK) void k_orph_total(Dev d) {
 // most vertices are orphans the store is swept instead and no list is made
 // (40 bytes a vertex, 0.67 GB of the 16.7e6-vertex grid's root finding).
 // With `own` a workgroup first takes the prefixes over the groups itself
-// (they are few) and the first one publishes the totals and the choice of
+// (they are few; 2: over the words) and the first one publishes the totals and the choice of
 // scan, instead of a launch of one workgroup in between (4.7 us).
 __global__ __launch_bounds__(BLOCK) void k_orph_fill(Dev d, int own) {
     if (stopped(d) || !d.ctl->has_del) return;
     __shared__ int64_t s_gv[FILL_GROUPS];  // slots and orphans before each group
     __shared__ int32_t s_gc[FILL_GROUPS];
     if (own) {
-        const int64_t ng = orphan_groups(d.nvb);
+        const int64_t ng = own == 2 ? orphan_words(d.nvb) : orphan_groups(d.nvb);
+        const unsigned long long *sums = own == 2 ? d.wvol : d.gsum;
         unsigned long long v[FILL_GROUPS / BLOCK], sv = 0, sc = 0;
 #pragma unroll
         for (int k = 0; k < FILL_GROUPS / BLOCK; k++) {
             const int64_t g = threadIdx.x * (FILL_GROUPS / BLOCK) + k;
-            v[k] = g < ng ? d.gsum[g] : 0;
+            v[k] = g < ng ? sums[g] : 0;
             sv += ovol(v[k]);
             sc += ocnt(v[k]);
         }
@@ -1173,8 +1190,8 @@ __global__ __launch_bounds__(BLOCK) void k_orph_fill(Dev d, int own) {
         if (w * WAVE >= d.n) continue;
         uint64_t bits = d.obits[w];
         if (bits == 0) continue;
-        const unsigned long long pre = d.wpre[w];
-        const int64_t g = w / BLOCK;
+        const unsigned long long pre = own == 2 ? 0 : d.wpre[w];
+        const int64_t g = own == 2 ? w : w / BLOCK;
         int64_t idx = (own ? (int64_t)s_gc[g] : d.gopre[g]) + (int64_t)ocnt(pre);
         int64_t vb = (own ? s_gv[g] : d.gpre[g]) + (int64_t)ovol(pre);
         while (bits) {  // uniform over the lanes of the word
@@ -1800,12 +1817,10 @@ __global__ __launch_bounds__(BLOCK) void k_bor_hook(Dev d, int r) {
 // longer than TAIL_MAX leaves everything untouched (the full-grid rounds
 // then go on).  Within one workgroup a barrier makes earlier global writes
 // and atomics visible to every thread of it.
-__global__ __launch_bounds__(TAIL_THREADS) void k_bor_tail(Dev d, int r0) {
-    if (stopped(d) || d.cnt[C_DONE_BOR]) return;
-    int64_t cin = (int64_t)d.cnt[(r0 & 1) ? C_NX0 : C_NX1];
-    if (cin > TAIL_MAX) return;
+// With `selected`, round r0's selection is made already (its list, of cin
+// edges, is the round's output) and the rounds start at its hooks.
+__device__ __forceinline__ void hook_rounds(const Dev &d, int r0, int64_t cin, bool selected, int64_t np) {
     __shared__ int s_nout;
-    const int64_t np = (int64_t)d.cnt[C_NP];
     const bool walk = d.ctl->walk;
     for (int r = r0;; r++) {
         if (r >= MAX_ROUNDS) {
@@ -1815,9 +1830,9 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_bor_tail(Dev d, int r0) {
         const Cross *in = (r & 1) ? d.x0 : d.x1;
         Cross *out = (r & 1) ? d.x1 : d.x0;
         uint64_t *best = best_of(d, r), *nbest = best_of(d, r + 1);
-        if (threadIdx.x == 0) s_nout = 0;
+        if (threadIdx.x == 0) s_nout = selected ? (int)cin : 0;
         __syncthreads();
-        for (int64_t base = 0; base < cin; base += TAIL_THREADS) {
+        for (int64_t base = selected ? cin : 0; base < cin; base += TAIL_THREADS) {
             const int64_t i = base + threadIdx.x;
             bool live = false;
             Cross e;
@@ -1844,6 +1859,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_bor_tail(Dev d, int r0) {
                 }
             }
         }
+        selected = false;
         __syncthreads();
         const int64_t nout = s_nout;
         if (nout == 0) {
@@ -1888,6 +1904,11 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_bor_tail(Dev d, int r0) {
         cin = nout;
     }
 }
+__global__ __launch_bounds__(TAIL_THREADS) void k_bor_tail(Dev d, int r0) {
+    if (stopped(d) || d.cnt[C_DONE_BOR]) return;
+    const int64_t cin = (int64_t)d.cnt[(r0 & 1) ? C_NX0 : C_NX1];
+    if (cin <= TAIL_MAX) hook_rounds(d, r0, cin, false, (int64_t)d.cnt[C_NP]);
+}
 
 // ------------------------------------------- a7: super-forest rooting
 
@@ -1931,6 +1952,24 @@ __device__ __forceinline__ bool is_super_root(const Dev &d, int32_t p) {
 // every piece has exactly one neighbour on the previous level, so each
 // piece's level and parent arc have a single writer.  A level that reaches no
 // new piece ends the search.
+// The arc at level L: true if it reaches a new piece.
+__device__ __forceinline__ bool reach_arc(const Dev &d, int64_t a, int L) {
+    const int4 e = d.er[a >> 1];
+    const int32_t src = (a & 1) ? e.w : e.z, dst = (a & 1) ? e.z : e.w;
+    bool from;
+    if (L == 0) {
+        from = is_super_root(d, src);
+        if (from) d.level[src] = 0;  // same value from every arc of src
+    } else {
+        from = d.level[src] == L;
+    }
+    // a super-root's neighbours are on level 1, so level 0 reaches no
+    // super-root; later levels never see one at -1 (marked on level 0)
+    if (!from || d.level[dst] >= 0) return false;
+    d.level[dst] = L + 1;
+    d.parc[dst] = (int32_t)a;
+    return true;
+}
 __global__ __launch_bounds__(BLOCK) void k_sf_bfs(Dev d, int L) {
     if (stopped(d) || !d.cnt[C_DONE_BOR]) return;
     if (L > 0 && d.cnt[C_BFS_ROUND + L - 1] == 0) return;
@@ -1939,24 +1978,7 @@ __global__ __launch_bounds__(BLOCK) void k_sf_bfs(Dev d, int L) {
     bool active = false;
     // every level starts at -1 (cleanup of the previous update); level 0 is
     // the super-roots, recognised here and marked on the first level
-    for (int64_t a = (int64_t)blockIdx.x * BLOCK + threadIdx.x; a < na; a += stride) {
-        const int4 e = d.er[a >> 1];
-        const int32_t src = (a & 1) ? e.w : e.z, dst = (a & 1) ? e.z : e.w;
-        bool from;
-        if (L == 0) {
-            from = is_super_root(d, src);
-            if (from) d.level[src] = 0;  // same value from every arc of src
-        } else {
-            from = d.level[src] == L;
-        }
-        // a super-root's neighbours are on level 1, so level 0 reaches no
-        // super-root; later levels never see one at -1 (marked on level 0)
-        if (from && d.level[dst] < 0) {
-            d.level[dst] = L + 1;
-            d.parc[dst] = (int32_t)a;
-            active = true;
-        }
-    }
+    for (int64_t a = (int64_t)blockIdx.x * BLOCK + threadIdx.x; a < na; a += stride) active |= reach_arc(d, a, L);
     if (__ballot(active) && lane_id() == 0) d.cnt[C_BFS_ROUND + L] = 1;
 }
 
@@ -1970,6 +1992,33 @@ __global__ __launch_bounds__(BLOCK) void k_sf_reroot(Dev d) {
         if (d.comp[p] != (int32_t)p) continue;
         const int32_t root = (int32_t)(uint32_t)d.srkey[p];
         if (root != (int32_t)p) hang(d, root, UP_NONE);
+    }
+}
+
+// The paths of piece p: q1 (if *e1) from the arc it hangs by, q2 (if *e2) the
+// re-root of a component's super-root, whose new label it also sets.
+__device__ __forceinline__ void orient_piece(const Dev &d, int64_t p, int64_t np, int levels, bool *e1, PathReq *q1,
+                                             bool *e2, PathReq *q2) {
+    q1->start = q1->newpar = q1->stop = q1->pad = 0;
+    *q2 = *q1;
+    if (p >= np) return;
+    const int32_t a = levels > 0 ? d.parc[p] : (int32_t)(d.up[p] >> 32);  // UP_NONE: -1
+    if (a >= 0) {
+        const int4 e = d.er[a >> 1];
+        *e1 = true;
+        if ((a & 1) == 0) { q1->start = e.y; q1->newpar = e.x; q1->stop = d.prt[e.w]; }
+        else { q1->start = e.x; q1->newpar = e.y; q1->stop = d.prt[e.z]; }
+    } else if ((levels == 0 || d.level[p] < 0) && !is_super_root(d, (int32_t)p)) {
+        atomicOr(d.status, ST_ROUND_BOUND);  // piece not reached: search incomplete
+    }
+    if (d.comp[p] == (int32_t)p) {
+        const uint64_t sk = d.srkey[p];
+        const int32_t S = (int32_t)(uint32_t)sk, m = (int32_t)(sk >> 32);
+        d.newlab[p] = m;
+        if (m != d.prt[S]) {
+            *e2 = true;
+            q2->start = m; q2->newpar = m; q2->stop = d.prt[S];
+        }
     }
 }
 
@@ -1990,33 +2039,184 @@ __global__ __launch_bounds__(BLOCK) void k_orient_bfs(Dev d, int levels) {
         const int64_t p = base + threadIdx.x;
         bool e1 = false, e2 = false;
         PathReq q1, q2;
-        q1.start = q1.newpar = q1.stop = q1.pad = 0;
-        q2 = q1;
-        if (p < np) {
-            const int32_t a = levels > 0 ? d.parc[p] : (int32_t)(d.up[p] >> 32);  // UP_NONE: -1
-            if (a >= 0) {
-                const int4 e = d.er[a >> 1];
-                e1 = true;
-                if ((a & 1) == 0) { q1.start = e.y; q1.newpar = e.x; q1.stop = d.prt[e.w]; }
-                else { q1.start = e.x; q1.newpar = e.y; q1.stop = d.prt[e.z]; }
-            } else if ((levels == 0 || d.level[p] < 0) && !is_super_root(d, (int32_t)p)) {
-                atomicOr(d.status, ST_ROUND_BOUND);  // piece not reached: search incomplete
-            }
-            if (d.comp[p] == (int32_t)p) {
-                const uint64_t sk = d.srkey[p];
-                const int32_t S = (int32_t)(uint32_t)sk, m = (int32_t)(sk >> 32);
-                d.newlab[p] = m;
-                if (m != d.prt[S]) {
-                    e2 = true;
-                    q2.start = m; q2.newpar = m; q2.stop = d.prt[S];
-                }
-            }
-        }
+        orient_piece(d, p, np, levels, &e1, &q1, &e2, &q2);
         const int64_t s1 = block_append((e1 ? 1 : 0) + (e2 ? 1 : 0), &d.cnt[C_NR]);
         const int64_t s2 = s1 + (e1 ? 1 : 0);
         if (e1) { if (s1 < d.pathcap) d.paths[s1] = q1; else atomicOr(d.status, ST_CAPACITY); }
         if (e2) { if (s2 < d.pathcap) d.paths[s2] = q2; else atomicOr(d.status, ST_CAPACITY); }
     }
+}
+
+// ------------------------------------- small batches in one workgroup
+//
+// A small batch has little for each of the update's many launches to do: a
+// launch costs the host about 4 us and the device 2 to 5 however few threads
+// find work, where a barrier inside a workgroup costs well under one.  So one
+// workgroup of SOLO_THREADS takes the steps that touch batch entries and
+// pieces only: for a batch of at most SOLO_FRONT edges all up to the cut and
+// the registration (an insert: up to the orientation), for one of at most
+// SOLO_BATCH the hooking rounds after the first, the super-roots, the search
+// and the orientation.  Beyond, a pass over the batch takes the workgroup
+// longer than the launches (b = 3163: front 34 us in one workgroup against 22
+// in four launches).  Counters and minima written by atomics are read back
+// after a fence (the L1 may hold their lines).
+
+__device__ __forceinline__ void see_atomics() {
+    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+
+// The super-roots, the search of `levels` levels (or, with none, the
+// re-rooting of trees that grew oriented) and the orientation, as k_sf_root,
+// k_sf_bfs, k_sf_reroot and k_orient_bfs.
+__device__ __forceinline__ void orient_pieces(const Dev &d, int levels) {
+    constexpr int NT = SOLO_THREADS;
+    __shared__ int s_active;
+    const int64_t np = (int64_t)d.cnt[C_NP];
+    if (np == 0) {  // nothing was cut or joined
+        if (threadIdx.x == 0) d.cnt[C_ORIENTED] = 1;
+        return;
+    }
+    for (int64_t base = 0; base < np; base += NT) {
+        const int64_t p = base + threadIdx.x;
+        const bool act = p < np;
+        const int32_t c = act ? comp_root(d, (int32_t)p, ~0u, np) : 0;
+        if (act) d.comp[p] = c;
+        const uint64_t key = act ? (((uint64_t)(uint32_t)d.pmin[p] << 32) | (uint64_t)p) : KEY_INF;
+        group_min_u64(act, c, key, d.srkey);
+    }
+    see_atomics();
+    if (levels == 0) {
+        if (d.cnt[C_LONGTREE]) return;  // the host continues
+        for (int64_t p = threadIdx.x; p < np; p += NT) {
+            if (d.comp[p] != (int32_t)p) continue;
+            const int32_t root = (int32_t)(uint32_t)d.srkey[p];
+            if (root != (int32_t)p) hang(d, root, UP_NONE);
+        }
+        see_atomics();
+        if (d.cnt[C_LONGTREE]) return;
+    }
+    const int64_t na = 2 * (int64_t)d.cnt[C_NER];
+    for (int L = 0; L < levels; L++) {
+        if (threadIdx.x == 0) s_active = 0;
+        __syncthreads();
+        for (int64_t a = threadIdx.x; a < na; a += NT) {
+            if (reach_arc(d, a, L)) s_active = 1;
+        }
+        __syncthreads();
+        const int active = s_active;
+        __syncthreads();
+        if (!active) break;
+        if (threadIdx.x == 0) d.cnt[C_BFS_ROUND + L] = 1;
+        if (L == levels - 1) return;  // deeper: the host continues
+    }
+    if (threadIdx.x == 0) d.cnt[C_ORIENTED] = 1;
+    for (int64_t base = 0; base < np; base += NT) {
+        bool e1 = false, e2 = false;
+        PathReq q1, q2;
+        orient_piece(d, base + threadIdx.x, np, levels, &e1, &q1, &e2, &q2);
+        const int64_t s1 = block_append<NT>((e1 ? 1 : 0) + (e2 ? 1 : 0), &d.cnt[C_NR]);
+        const int64_t s2 = s1 + (e1 ? 1 : 0);
+        if (e1) { if (s1 < d.pathcap) d.paths[s1] = q1; else atomicOr(d.status, ST_CAPACITY); }
+        if (e2) { if (s2 < d.pathcap) d.paths[s2] = q2; else atomicOr(d.status, ST_CAPACITY); }
+    }
+}
+
+// An insert from its cross edges (dense in x1, as round 0 reads them) on.
+__device__ __forceinline__ void solo_insert(const Dev &d, int levels) {
+    __shared__ int s_n;
+    const int64_t b = d.ctl->b;
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    for (int64_t base = 0; base < b; base += SOLO_THREADS) {
+        const int64_t i = base + threadIdx.x;
+        Cross e;
+        bool cross = false;
+        if (i < b && edge_ok(d, i)) {
+            e.key = d.bkey[i];
+            const int32_t la = d.label[key_lo(e.key)], lb = d.label[key_hi(e.key)];
+            cross = la != lb;
+            if (cross) {
+                e.pa = d.tidx[la];
+                e.pb = d.tidx[lb];
+            }
+        }
+        const uint64_t m = __ballot(cross);
+        if (m) {
+            const int leader = __ffsll((unsigned long long)m) - 1;
+            int at = 0;
+            if (lane_id() == leader) at = atomicAdd(&s_n, __popcll(m));
+            at = __shfl(at, leader);
+            if (cross) d.x1[at + lanes_below(m)] = e;
+        }
+    }
+    __syncthreads();
+    const int64_t n = s_n;
+    if (threadIdx.x == 0) d.cnt[C_NCROSS] = (unsigned long long)n;
+    hook_rounds(d, 0, n, false, (int64_t)d.cnt[C_NP]);
+    see_atomics();
+    if (d.cnt[C_DONE_BOR]) orient_pieces(d, levels);
+}
+
+// Validation and, for an insert, everything up to the orientation; the other
+// workgroups (a delete's) start root finding: rep <- parent, before the cut.
+__global__ __launch_bounds__(SOLO_THREADS) void k_solo_front(Dev d, Ctl kc, int from_arg, int ins, int levels) {
+    if (held(d)) return;
+    if (blockIdx.x > 0) {
+        const int64_t stride = (int64_t)(gridDim.x - 1) * SOLO_THREADS * 4;
+        for (int64_t v = ((int64_t)(blockIdx.x - 1) * SOLO_THREADS + threadIdx.x) * 4; v < d.n; v += stride) {
+            if (v + 4 <= d.n) {
+                *reinterpret_cast<v4i *>(d.rep + v) = *reinterpret_cast<const v4i *>(d.parent + v);
+            } else {
+                for (int64_t u = v; u < d.n; u++) d.rep[u] = d.parent[u];
+            }
+        }
+        return;
+    }
+    const BatchHead hd = publish_ctl(d, kc, from_arg);
+    classify_edges(d, hd, threadIdx.x, SOLO_THREADS);
+    __syncthreads();
+    if (d.validate) dedupe_edges(d, hd.b, threadIdx.x, SOLO_THREADS);
+    if (!ins) return;
+    see_atomics();  // the batch's status
+    if (stopped(d)) return;
+    prepare_edges<SOLO_THREADS>(d, 0, 1);
+    see_atomics();
+    register_pieces<SOLO_THREADS>(d, 0, 1);
+    see_atomics();
+    solo_insert(d, levels);
+}
+
+// The cut and the registration of a small delete, after its k_solo_front.
+__global__ __launch_bounds__(SOLO_THREADS) void k_solo_cut(Dev d) {
+    if (stopped(d)) return;
+    prepare_edges<SOLO_THREADS>(d, 0, 1);
+    see_atomics();
+    register_pieces<SOLO_THREADS>(d, 0, 1);
+}
+
+// From the cross edges of an insert, or from the hooks of a delete's round r
+// (whose list must be short enough for one workgroup: else the host goes on
+// with the full-grid rounds), to the orientation.
+__global__ __launch_bounds__(SOLO_THREADS) void k_solo_rounds(Dev d, int ins, int r, int levels) {
+    if (stopped(d)) return;
+    if (ins) {
+        solo_insert(d, levels);
+        return;
+    }
+    unsigned long long found = 0;
+    const Regions reg(d);
+    for (int64_t i = threadIdx.x; i < reg.om; i += SOLO_THREADS) found += d.xcnt[i];
+    for (int64_t i = reg.rlo2 + threadIdx.x; i < d.ctl->rhi; i += SOLO_THREADS) found += d.rcnt[i];
+    for (int o = WAVE / 2; o > 0; o >>= 1) found += __shfl_xor(found, o);
+    if (lane_id() == 0 && found) atomicAdd(&d.cnt[C_NCROSS], found);
+    if (!d.cnt[C_DONE_BOR]) {
+        const int64_t n = (int64_t)d.cnt[(r & 1) ? C_NX1 : C_NX0];
+        if (n > SOLO_LIST) return;
+        hook_rounds(d, r, n, true, (int64_t)d.cnt[C_NP]);
+    }
+    see_atomics();
+    if (d.cnt[C_DONE_BOR]) orient_pieces(d, levels);
 }
 
 // Fallback for deep super-trees: Euler tour of the super-forest and list
@@ -2750,12 +2950,13 @@ void launch_rep_chase(const Dev &d, hipStream_t s) {
         hipLaunchKernelGGL(k_rep_chase<2>, dim3(grid_for(d.nvb, 2, GRID_CAP)), dim3(BLOCK), 0, s, d);
 }
 void launch_orphan_plan(const Dev &d, hipStream_t s) {
+    if (orphan_words(d.nvb) <= FILL_GROUPS) return;  // the list fill does without
     hipLaunchKernelGGL(k_orph_plan, dim3((unsigned)orphan_groups(d.nvb)), dim3(BLOCK), 0, s, d);
     if (orphan_groups(d.nvb) > FILL_GROUPS) hipLaunchKernelGGL(k_orph_total, dim3(1), dim3(BLOCK), 0, s, d);
 }
 void launch_orphan_fill(const Dev &d, hipStream_t s) {
     hipLaunchKernelGGL(k_orph_fill, dim3(grid_for(orphan_words(d.nvb), BLOCK / 8, GRID_CAP)), dim3(BLOCK), 0, s, d,
-                       orphan_groups(d.nvb) <= FILL_GROUPS ? 1 : 0);
+                       orphan_words(d.nvb) <= FILL_GROUPS ? 2 : orphan_groups(d.nvb) <= FILL_GROUPS ? 1 : 0);
 }
 void launch_key_edges(const Dev &d, int parts, hipStream_t s) {
     // persistent over orphan regions and store tiles
@@ -2777,6 +2978,23 @@ void launch_boruvka(const Dev &d, int r0, int r1, int64_t units, bool ins, hipSt
     }
     // the tail reads a dense list, which rounds from 2 on have
     if (r1 >= 2 && r1 > r0) hipLaunchKernelGGL(k_bor_tail, dim3(1), dim3(TAIL_THREADS), 0, s, d, r1);
+}
+void launch_bor_hook(const Dev &d, int r, hipStream_t s) {
+    hipLaunchKernelGGL(k_bor_hook, dim3(grid_for(piece_bound(d), BLOCK, SMALL_CAP)), dim3(BLOCK), 0, s, d, r);
+}
+void launch_solo_front(const Dev &d, const Ctl *kc, bool ins, int levels, hipStream_t s) {
+    const Ctl none{};
+    const int gc = ins ? 0 : grid_for(d.n, 4 * SOLO_THREADS, COPY_CAP / 4);
+    hipLaunchKernelGGL(k_solo_front, dim3(1 + gc), dim3(SOLO_THREADS), 0, s, d, kc ? *kc : none, kc ? 1 : 0,
+                       ins ? 1 : 0, levels);
+    if (!ins) hipLaunchKernelGGL(k_solo_cut, dim3(1), dim3(SOLO_THREADS), 0, s, d);
+}
+void launch_solo_rounds(const Dev &d, bool ins, int r, int64_t units, int levels, hipStream_t s) {
+    for (int q = 1; !ins && q <= r; q++) {
+        launch_bor_hook(d, q - 1, s);
+        hipLaunchKernelGGL(k_bor_select, dim3(q == 1 ? grid_for(units, 1, EDGE_CAP) : 256), dim3(BLOCK), 0, s, d, q);
+    }
+    hipLaunchKernelGGL(k_solo_rounds, dim3(1), dim3(SOLO_THREADS), 0, s, d, ins ? 1 : 0, r, levels);
 }
 void launch_sf_root(const Dev &d, bool count, hipStream_t s) {
     const int gp = grid_for(piece_bound(d), BLOCK, SMALL_CAP);

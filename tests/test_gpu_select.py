@@ -86,3 +86,67 @@ def test_super_trees_searched_then_oriented_as_they_grow(k, bits, launch_mode):
         assert st["host_finished"] & 2 == want, (i, st)
         pair.step(ins, drsf.DRSF_DELETE, f"delete {i}")
     pair.gpu.close()
+
+
+@pytest.mark.parametrize("device", [True, False])
+@pytest.mark.parametrize("b", [1, 2, 511, 512, 513, 4096, 4097, 8193])
+def test_batches_around_the_one_workgroup_bounds(b, device):
+    drsf = _lib()
+    _case(f"batches of {b}, device {device}")
+    n = 20011
+    g = gen.make_graph("gnm", n, gen.gnm(n, 30000, gen.seed(85, 0, gen.P_GRAPH)))
+    ins = gen.insert_batches(n, g.keys, 2, b, gen.seed(85, b, gen.P_INSERT))
+    dl = gen.delete_batches(n, g.keys, g.parent, 1, b, (b + 1) // 2, gen.seed(85, b, gen.P_DELETE))[0]
+    pair = Pair(g, device=device, max_batch=max(b, 16))
+    for i, (e, op) in enumerate([(ins[0], 0), (dl, 1), (ins[1], 0), (dl, 0), (ins[0], 1)]):
+        pair.step(e, (drsf.DRSF_INSERT, drsf.DRSF_DELETE)[op], f"batch {i}")
+    bad = np.concatenate([ins[0], ins[1][:1]]) if b > 1 else np.array([[3, 3]], np.int32)  # ins[1] is there
+    if len(bad) <= max(b, 16):
+        with pytest.raises(drsf.DrsfError):
+            if device:
+                import torch
+                with torch.cuda.stream(pair.stream):
+                    bad = torch.from_numpy(np.ascontiguousarray(bad)).to(pair.dev)
+            pair.gpu.apply(bad, drsf.DRSF_INSERT)
+        pair.check_equal("rejected")
+    pair.gpu.close()
+
+
+def test_one_workgroup_rounds_meet_a_long_list():
+    """Pieces that pair up in round 0 (their smallest vertices are joined) and
+    keep 60,000 edges between them: the list after the first selection is too
+    long for one workgroup, the host finishes the update, and later ones make
+    more full-grid selections first."""
+    drsf = _lib()
+    k, size = 800, 10
+    n = k * size
+    # piece p: its smallest vertex p, then k + 9 p ... k + 9 p + 8, a path
+    verts = [[p] + list(range(k + (size - 1) * p, k + (size - 1) * (p + 1))) for p in range(k)]
+    parent = np.arange(n, dtype=np.int32)
+    edges = []
+    for p, vs in enumerate(verts):
+        for a, c in zip(vs, vs[1:]):
+            edges.append((a, c))
+            parent[c] = a
+        if p:
+            edges.append((verts[p - 1][-1], vs[0]))  # the edges that go
+            parent[vs[0]] = verts[p - 1][-1]
+    chain = np.array([(verts[p - 1][-1], verts[p][0]) for p in range(1, k)], np.int32)
+    edges += [(2 * j, 2 * j + 1) for j in range(k // 2)]
+    rng = np.random.default_rng(86)
+    r = rng.integers(k, n, (60000, 2))
+    keys = np.unique(gen.keys_of_edges(np.concatenate([np.array(edges), r[r[:, 0] != r[:, 1]]])))
+    row_ptr, col = gen.keys_to_csr(n, keys)
+    _case(f"long list: {k} pieces, {len(keys)} edges")
+    pair = Pair(gen.Graph("pairs", n, keys, row_ptr, col, parent), max_batch=1024)
+    done = []
+    for i in range(6):
+        st, _ = pair.step(chain, drsf.DRSF_DELETE, f"delete {i}")
+        done.append(st["host_finished"] & 1)
+        # back to the chain: a fresh context would start there too
+        pair.step(chain, drsf.DRSF_INSERT, f"insert {i}")
+        if i == 0:
+            assert done[0] == 1, st
+            chain = np.stack([np.arange(n), pair.parent], 1)[pair.parent != np.arange(n)][: len(chain)].astype(np.int32)
+    assert done[-1] == 0, done
+    pair.gpu.close()
