@@ -348,13 +348,13 @@ int drsf_digest(drsf_ctx *ctx, uint64_t *out);
 /*
  * Static rebuild (the baseline of the dynamic update, Sec. V's static GPU
  * forest; no context): a rooted spanning forest of G from scratch.
- * Connected components by hooking (the larger root of an edge's two
- * components takes the smaller as its root, repeated with pointer jumping
- * until no edge joins two roots), so each component is rooted at its
- * smallest vertex, then a breadth-first forest from all roots at once
- * (a level is expanded top-down from its frontier's rows when they are few
- * and short, else bottom-up: every unvisited vertex takes the first
- * neighbour on the frontier in its row).
+ * Connected components by linking (the larger root of an edge's two
+ * components takes the smaller as its root; vertices of the largest component
+ * found by their first two edges skip the rest of theirs), so each component
+ * is rooted at its smallest vertex, then a breadth-first forest from all roots
+ * at once (a level is expanded top-down from its frontier's rows when they are
+ * few, else bottom-up: every unvisited vertex takes a neighbour on the
+ * frontier in its row).
  * row_ptr: DEVICE int64[n + 1]; col: DEVICE int32[row_ptr[n]] (may be NULL
  * when row_ptr[n] == 0), a symmetric CSR without self-loops (not checked
  * here).  parent_out, label_out: DEVICE
@@ -362,7 +362,7 @@ int drsf_digest(drsf_ctx *ctx, uint64_t *out);
  * vertex.  The breadth-first parent is one of several valid choices (ties
  * between frontier vertices are decided by the hardware).  stream: hipStream_t
  * or NULL.  levels_out (host, may be NULL): breadth-first levels.  Allocates
- * and frees its own scratch (about 12 bytes per vertex and 4 per CSR entry)
+ * and frees its own scratch (about 12 bytes per vertex)
  * and returns when the result is final.  Errors: DRSF_E_ARG, DRSF_E_NOMEM,
  * DRSF_E_DEVICE.
  */

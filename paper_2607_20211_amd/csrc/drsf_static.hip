@@ -1,6 +1,6 @@
 // Static rebuild of a rooted spanning forest (the baseline the dynamic update
 // is measured against, Sec. V's static GPU BFS): connected components by
-// hooking, each rooted at its smallest vertex, then a breadth-first forest
+// linking, each rooted at its smallest vertex, then a breadth-first forest
 // from all roots at once.  Kept apart from the update path; it shares only
 // the small fill and grid helpers.
 #include <hip/hip_runtime.h>
@@ -14,30 +14,6 @@
 
 namespace drsf {
 namespace {
-
-// Row of every CSR slot: the number of rows u >= 1 whose first slot is at
-// or before it.  Each row u >= 1 counts 1 at its first slot (k_st_marks;
-// empty rows share the next row's first slot), an exclusive sum over the
-// slots follows, and the row of slot s is that sum plus its own count.
-__global__ __launch_bounds__(BLOCK) void k_st_marks(int32_t n, const int64_t *row_ptr, int64_t nnz,
-                                                    uint32_t *mark) {
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    for (int64_t u = 1 + (int64_t)blockIdx.x * BLOCK + threadIdx.x; u < n; u += stride) {
-        const int64_t a = row_ptr[u];
-        if (a < nnz) atomicAdd(&mark[a], 1u);
-    }
-}
-__global__ __launch_bounds__(BLOCK) void k_st_rows(int64_t nnz, const uint32_t *mark, const uint32_t *excl,
-                                                   int32_t *erow) {
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    for (int64_t s = (int64_t)blockIdx.x * BLOCK + threadIdx.x; s < nnz; s += stride)
-        erow[s] = (int32_t)(excl[s] + mark[s]);
-}
-
-__global__ __launch_bounds__(BLOCK) void k_st_iota(int32_t n, int32_t *comp) {
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    for (int64_t v = (int64_t)blockIdx.x * BLOCK + threadIdx.x; v < n; v += stride) comp[v] = (int32_t)v;
-}
 
 // position of this lane's entry in a list counted by *cnt, one atomic per
 // wave (every lane of the wave calls it)
@@ -58,6 +34,11 @@ __device__ __forceinline__ int64_t wave_append(bool take, unsigned long long *cn
 // frontier counter costs a serialised round trip, so per-wave appends from
 // thousands of waves were most of a level's time.
 constexpr int APP_BUF = 4096;
+// Threads of a workgroup that a wide level runs with: its atomics on the level
+// counters (three a workgroup, on the same words) were most of its time (R-MAT
+// 20's widest level, 524288 threads: 178 us in workgroups of 256, 92 of 512, 50
+// of 1024).
+constexpr int WIDE_BLOCK = 1024;
 struct Appender {
     int32_t buf[APP_BUF];
     int n;
@@ -85,21 +66,23 @@ __device__ __forceinline__ void app_push(Appender &a, bool take, int32_t w, int3
     }
 }
 // every thread of the workgroup calls it
+template <int BS>
 __device__ __forceinline__ void app_end(Appender &a, int32_t *next, unsigned long long *ncnt) {
     __syncthreads();
     const int k = a.n < APP_BUF ? a.n : APP_BUF;
     if (threadIdx.x == 0 && k > 0) a.base = atomicAdd(ncnt, (unsigned long long)k);
     __syncthreads();
-    for (int i = threadIdx.x; i < k; i += BLOCK) next[a.base + i] = a.buf[i];
+    for (int i = threadIdx.x; i < k; i += BS) next[a.base + i] = a.buf[i];
 }
 
 // Row lengths of the vertices a workgroup claimed, into the next level's
 // degree sum and maximum (stat[0] sum, stat[1] max): each thread accumulates
 // over its whole grid-stride loop, then one atomic pair per workgroup (every
 // thread calls it once, at the end of the kernel).
+template <int BS>
 __device__ __forceinline__ void block_degree(unsigned long long sum, unsigned long long mx,
                                              unsigned long long *stat) {
-    __shared__ unsigned long long s_sum[BLOCK / WAVE], s_max[BLOCK / WAVE];
+    __shared__ unsigned long long s_sum[BS / WAVE], s_max[BS / WAVE];
     for (int o = WAVE / 2; o > 0; o >>= 1) {
         sum += __shfl_xor(sum, o);
         const unsigned long long y = __shfl_xor(mx, o);
@@ -112,7 +95,7 @@ __device__ __forceinline__ void block_degree(unsigned long long sum, unsigned lo
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long t = 0, m = 0;
-        for (int w = 0; w < BLOCK / WAVE; w++) {
+        for (int w = 0; w < BS / WAVE; w++) {
             t += s_sum[w];
             m = s_max[w] > m ? s_max[w] : m;
         }
@@ -122,92 +105,197 @@ __device__ __forceinline__ void block_degree(unsigned long long sum, unsigned lo
         }
     }
 }
-__device__ __forceinline__ void add_degree(bool take, const int64_t *row_ptr, int32_t w, unsigned long long &sum,
-                                           unsigned long long &mx) {
-    if (!take) return;
-    const unsigned long long dg = (unsigned long long)(row_ptr[w + 1] - row_ptr[w]);
-    sum += dg;
-    mx = dg > mx ? dg : mx;
-}
-
 // Level counters: three groups of four words, level L's in group L % 3
-// (frontier size, row-length sum, longest row), then the depth word (the
-// number of non-empty levels seen so far).  The kernel of level L reads group
-// L % 3, fills group (L + 1) % 3 and clears group (L + 2) % 3 for the level
-// after, so levels run back to back with no host step between them.
-constexpr int CNT_WORDS = 13;
-constexpr int CNT_DEPTH = 12;
+// (frontier vertices with rows of up to LONG_ROW slots, listed from the
+// frontier's front; row-length sum; longest row; frontier vertices with longer
+// rows, listed from its end), then the depth word (the number of non-empty
+// levels seen so far) and two words for the level reached: launch k reads the
+// one of its parity and writes the other, so levels run back to back with no
+// host step between them, whatever number of levels a launch does.  The kernel
+// of level L reads group L % 3, fills group (L + 1) % 3 and clears group
+// (L + 2) % 3 for the level after.
+constexpr int CNT_DEPTH = 12, CNT_LEVEL = 13, CNT_WORDS = 15;
 __device__ __forceinline__ unsigned long long *level_group(unsigned long long *g, int L) { return g + 4 * (L % 3); }
-__device__ __forceinline__ void level_begin(unsigned long long *g, int L, bool nonempty) {
+__device__ __forceinline__ void level_begin(unsigned long long *g, int L, int k, bool nonempty) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         unsigned long long *c = level_group(g, L + 2);
         c[0] = 0;
         c[1] = 0;
         c[2] = 0;
+        c[3] = 0;
         if (nonempty) g[CNT_DEPTH] = (unsigned long long)(L + 1);
+        g[CNT_LEVEL + ((k + 1) & 1)] = (unsigned long long)(L + (nonempty ? 1 : 0));
     }
 }
 
-__device__ __forceinline__ int32_t st_root(const int32_t *comp, int32_t x) {
-    for (int32_t y = comp[x]; y != x; y = comp[x]) x = y;
-    return x;
+// A claimed vertex (every lane of the wave calls it): its row length into the
+// sums, itself into the next frontier.
+constexpr int LONG_ROW = 1024;
+__device__ __forceinline__ void claim_vertex(Appender &app, bool take, const int64_t *row_ptr, int32_t n, int32_t w,
+                                             int32_t *next, unsigned long long *ng, unsigned long long &sum,
+                                             unsigned long long &mx) {
+    unsigned long long dg = 0;
+    if (take) {
+        dg = (unsigned long long)(row_ptr[w + 1] - row_ptr[w]);
+        sum += dg;
+        mx = dg > mx ? dg : mx;
+        if (dg > LONG_ROW) next[n - 1 - (int64_t)atomicAdd(&ng[3], 1ull)] = w;
+    }
+    app_push(app, take && dg <= LONG_ROW, w, next, ng);
 }
 
-// Hooking: for every edge (u, v), u < v, whose ends have different roots, the
-// larger root hooks onto the smaller (an atomic minimum), so every root only
-// ever decreases and each component ends rooted at its smallest vertex.
-__global__ __launch_bounds__(BLOCK) void k_st_hook(int64_t nnz, const int32_t *erow, const int32_t *col,
-                                                   int32_t *comp, int32_t *changed) {
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    bool any = false;
-    for (int64_t s = (int64_t)blockIdx.x * BLOCK + threadIdx.x; s < nnz; s += stride) {
-        const int32_t u = erow[s], v = col[s];
-        if (v <= u) continue;  // each undirected edge once
-        const int32_t ru = st_root(comp, u), rv = st_root(comp, v);
-        if (ru == rv) continue;
-        const int32_t hi = ru > rv ? ru : rv, lo = ru > rv ? rv : ru;
-        if (comp[hi] > lo) {
-            atomicMin(&comp[hi], lo);
-            any = true;
+// ------------------------------------------------------------ components
+//
+// Every tree of comp[] is rooted at its smallest vertex: a root only ever
+// hooks below a smaller one.  One pass that links the ends of every edge is
+// enough (a link ends when both ends hang below one vertex), and most edges
+// need not be looked at: after each vertex has been linked to its first two
+// neighbours, nearly all of a large component hangs together, so its vertices
+// skip the rest of their rows, which their neighbours outside it cover from
+// their side (the sampling of Sutton, Ben-Nun and Barak's Afforest).  Bound by
+// the gathers of the first two slots.  R-MAT 20 with 31.4e6 slots: 51 us for
+// these kernels; three hooking rounds over every slot took 408 and the row of
+// every slot, which they read, 326.
+
+// A link only swaps roots, it does not shorten the path it walks.  Halving it
+// was slower (G(1e6, 5e6), first links: 117 us without, 552 from the ninth step
+// on): its stores race, so they have to be atomic ones.  By plain stores, two
+// XCDs that store one word in one launch can be left with L2 copies that differ
+// beyond its end; on a grid 2048 wide a few vertices, whose compression read
+// the copy of its own XCD, kept an ancestor as their label.
+__device__ __forceinline__ void st_link(int32_t *comp, int32_t u, int32_t v) {
+    int32_t a = comp[u], b = comp[v];
+    while (a != b) {
+        const int32_t hi = a > b ? a : b, lo = a > b ? b : a;
+        int32_t up = comp[hi];  // may be stale: an ancestor at most hi all the same
+        if (up == hi) {
+            up = atomicCAS(&comp[hi], hi, lo);
+            if (up == hi) return;
         }
+        a = up;  // below hi: every turn goes down in ids
+        b = lo;
     }
-    if (__ballot(any) && lane_id() == 0) *changed = 1;
 }
-
-// pointer jumping to the roots
+// every vertex below its first neighbour if that is smaller, else a root (and
+// the level counters cleared)
+__global__ __launch_bounds__(BLOCK) void k_st_comp_init(int32_t n, const int64_t *row_ptr, const int32_t *col,
+                                                        int32_t *comp, unsigned long long *g) {
+    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    if (blockIdx.x == 0 && threadIdx.x < CNT_WORDS) g[threadIdx.x] = 0;
+    for (int64_t v = (int64_t)blockIdx.x * BLOCK + threadIdx.x; v < n; v += stride) {
+        const int64_t a = row_ptr[v];
+        int32_t c = (int32_t)v;
+        if (a < row_ptr[v + 1] && col[a] < c) c = col[a];
+        comp[v] = c;
+    }
+}
+__global__ __launch_bounds__(BLOCK) void k_st_link_first(int32_t n, const int64_t *row_ptr, const int32_t *col,
+                                                         int32_t *comp) {
+    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    for (int64_t v = (int64_t)blockIdx.x * BLOCK + threadIdx.x; v < n; v += stride) {
+        const int64_t a = row_ptr[v], b = row_ptr[v + 1];
+        if (a < b && col[a] > v) st_link(comp, (int32_t)v, col[a]);
+        if (a + 1 < b) st_link(comp, (int32_t)v, col[a + 1]);
+    }
+}
+// pointer jumping to the roots, every step published (long chains of
+// vertices walked at the same time shorten each other)
 __global__ __launch_bounds__(BLOCK) void k_st_compress(int32_t n, int32_t *comp) {
     const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    for (int64_t v = (int64_t)blockIdx.x * BLOCK + threadIdx.x; v < n; v += stride)
-        comp[v] = st_root(comp, (int32_t)v);
+    for (int64_t v = (int64_t)blockIdx.x * BLOCK + threadIdx.x; v < n; v += stride) {
+        int32_t x = comp[v];
+        for (int32_t y = comp[x]; y != x; y = comp[x]) {
+            comp[v] = y;
+            x = y;
+        }
+    }
+}
+// the label that most of a sample of the vertices carry
+constexpr int SAMPLE = 1024;
+__global__ __launch_bounds__(BLOCK) void k_st_sample(int32_t n, const int32_t *comp, int32_t *giant) {
+    __shared__ int32_t s_id[SAMPLE * 2];
+    __shared__ int s_cnt[SAMPLE * 2];
+    __shared__ int s_best;
+    for (int i = threadIdx.x; i < SAMPLE * 2; i += BLOCK) {
+        s_id[i] = -1;
+        s_cnt[i] = 0;
+    }
+    if (threadIdx.x == 0) s_best = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < SAMPLE; i += BLOCK) {
+        const int32_t l = comp[hmix((uint64_t)i + 1) % (uint64_t)n];
+        uint32_t h = (uint32_t)l * 2654435769u % (SAMPLE * 2);
+        for (;;) {  // at most SAMPLE labels in twice as many places
+            const int32_t was = atomicCAS(&s_id[h], -1, l);
+            if (was == -1 || was == l) break;
+            h = (h + 1) % (SAMPLE * 2);
+        }
+        atomicAdd(&s_cnt[h], 1);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < SAMPLE * 2; i += BLOCK)
+        if (s_cnt[i]) atomicMax(&s_best, s_cnt[i] << 11 | i);
+    __syncthreads();
+    if (threadIdx.x == 0) *giant = s_id[s_best & (SAMPLE * 2 - 1)];
+}
+static_assert(SAMPLE * 2 == 1 << 11, "a place fits the low bits of the vote");
+// the rest of the rows outside the sampled component: short ones by a lane,
+// longer ones by the wave
+__global__ __launch_bounds__(BLOCK) void k_st_link_rest(int32_t n, const int64_t *row_ptr, const int32_t *col,
+                                                        int32_t *comp, const int32_t *giant) {
+    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    const int32_t skip = *giant;
+    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < n; base += stride) {
+        const int64_t v = base + threadIdx.x;
+        int64_t a = 0, b = 0;
+        if (v < n && comp[v] != skip) {
+            a = row_ptr[v] + 2;
+            b = row_ptr[v + 1];
+        }
+        const bool big = b - a > 32;
+        if (!big)
+            for (int64_t s = a; s < b; s++) st_link(comp, (int32_t)v, col[s]);
+        uint64_t m = __ballot(big);
+        while (m) {
+            const int l = __ffsll((unsigned long long)m) - 1;
+            m &= m - 1;
+            const int32_t bv = __shfl((int32_t)v, l);
+            const int64_t ba = __shfl(a, l), bb = __shfl(b, l);
+            for (int64_t s = ba + lane_id(); s < bb; s += WAVE) st_link(comp, bv, col[s]);
+        }
+    }
 }
 
-// roots: level 0, their own parents, the first frontier
-__global__ __launch_bounds__(BLOCK) void k_st_bfs_init(int32_t n, const int64_t *row_ptr, const int32_t *comp,
+// --------------------------------------------------- breadth-first levels
+
+// roots: level 0, their own parents, the first frontier (those with edges)
+__global__ __launch_bounds__(WIDE_BLOCK) void k_st_bfs_init(int32_t n, const int64_t *row_ptr, const int32_t *comp,
                                                        int32_t *level, int32_t *parent, int32_t *front,
                                                        unsigned long long *g) {
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    unsigned long long *fcnt = level_group(g, 0), *fstat = fcnt + 1;
+    const int64_t stride = (int64_t)gridDim.x * WIDE_BLOCK;
+    unsigned long long *fg = level_group(g, 0);
     __shared__ Appender app;
     app_begin(app);
     unsigned long long dsum = 0, dmax = 0;
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < n; base += stride) {
+    for (int64_t base = (int64_t)blockIdx.x * WIDE_BLOCK; base < n; base += stride) {
         const int64_t v = base + threadIdx.x;
         const bool root = v < n && comp[v] == (int32_t)v;
         if (v < n) {
             level[v] = root ? 0 : -1;
             parent[v] = root ? (int32_t)v : -1;
         }
-        app_push(app, root, (int32_t)v, front, fcnt);
-        add_degree(root, row_ptr, (int32_t)v, dsum, dmax);
+        const bool start = root && row_ptr[v + 1] > row_ptr[v];
+        claim_vertex(app, start, row_ptr, n, (int32_t)v, front, fg, dsum, dmax);
     }
-    app_end(app, front, fcnt);
-    block_degree(dsum, dmax, fstat);
+    app_end<WIDE_BLOCK>(app, front, fg);
+    block_degree<WIDE_BLOCK>(dsum, dmax, fg + 1);
 }
 
-// Top-down level from a small frontier: each unvisited neighbour is claimed
-// by a compare-and-swap on its level.  Rows of up to SHORT_ROW slots are
-// walked by four lanes each (sixteen frontier vertices per wave, the wave
-// looping to its longest such row); a longer row is walked by the whole wave.
+// Top-down level: each unvisited neighbour of the frontier is claimed by a
+// compare-and-swap on its level.  Rows of up to SHORT_ROW slots are walked by
+// four lanes each (sixteen frontier vertices per wave, the wave looping to its
+// longest such row), rows of up to LONG_ROW by the whole wave, and longer ones
+// (a hub's) by the whole grid.
 constexpr int SHORT_ROW = 32;
 __device__ __forceinline__ bool td_claim(const int32_t *col, int32_t *level, int32_t *parent, int L, int32_t v,
                                          int64_t s, int32_t &w) {
@@ -216,18 +304,16 @@ __device__ __forceinline__ bool td_claim(const int32_t *col, int32_t *level, int
     if (claim) parent[w] = v;
     return claim;
 }
-__global__ __launch_bounds__(BLOCK) void k_st_top_down(const int64_t *row_ptr, const int32_t *col,
-                                                       int32_t *level, int32_t *parent, int L,
-                                                       const int32_t *front, int32_t *next, unsigned long long *g) {
-    const int64_t nf = (int64_t)*level_group(g, L);
-    unsigned long long *ncnt = level_group(g, L + 1), *nstat = ncnt + 1;
-    level_begin(g, L, nf > 0);
-    __shared__ Appender app;
-    app_begin(app);
+template <int BS>
+__device__ __forceinline__ void top_down(Appender &app, int32_t n, const int64_t *row_ptr, const int32_t *col,
+                                         int32_t *level, int32_t *parent, int L, const int32_t *front,
+                                         int32_t *next, unsigned long long *g, unsigned long long &dsum,
+                                         unsigned long long &dmax) {
+    const int64_t nf = (int64_t)level_group(g, L)[0], nlong = (int64_t)level_group(g, L)[3];
+    unsigned long long *ng = level_group(g, L + 1);
     const int sub = lane_id() & 3;
-    const int64_t step = (int64_t)gridDim.x * (BLOCK / WAVE) * (WAVE / 4);
-    unsigned long long dsum = 0, dmax = 0;
-    for (int64_t f0 = ((int64_t)blockIdx.x * (BLOCK / WAVE) + threadIdx.x / WAVE) * (WAVE / 4); f0 < nf;
+    const int64_t step = (int64_t)gridDim.x * (BS / WAVE) * (WAVE / 4);
+    for (int64_t f0 = ((int64_t)blockIdx.x * (BS / WAVE) + threadIdx.x / WAVE) * (WAVE / 4); f0 < nf;
          f0 += step) {
         const int64_t f = f0 + (lane_id() >> 2);
         int32_t v = 0;
@@ -248,8 +334,7 @@ __global__ __launch_bounds__(BLOCK) void k_st_top_down(const int64_t *row_ptr, c
             bool claim = false;
             int32_t w = 0;
             if (!big && sl < b) claim = td_claim(col, level, parent, L, v, sl, w);
-            app_push(app, claim, w, next, ncnt);
-            add_degree(claim, row_ptr, w, dsum, dmax);
+            claim_vertex(app, claim, row_ptr, n, w, next, ng, dsum, dmax);
         }
         uint64_t bm = __ballot(big && sub == 0);
         while (bm) {
@@ -262,78 +347,193 @@ __global__ __launch_bounds__(BLOCK) void k_st_top_down(const int64_t *row_ptr, c
                 bool claim = false;
                 int32_t w = 0;
                 if (sl < bb) claim = td_claim(col, level, parent, L, bv, sl, w);
-                app_push(app, claim, w, next, ncnt);
-                add_degree(claim, row_ptr, w, dsum, dmax);
+                claim_vertex(app, claim, row_ptr, n, w, next, ng, dsum, dmax);
             }
         }
     }
-    app_end(app, next, ncnt);
-    block_degree(dsum, dmax, nstat);
-}
-
-// Edge-parallel level for a frontier with long rows but few edges: every
-// slot (u, w) with u on level L claims w.
-__global__ __launch_bounds__(BLOCK) void k_st_edges(int64_t nnz, const int64_t *row_ptr, const int32_t *erow,
-                                                    const int32_t *col, int32_t *level, int32_t *parent, int L,
-                                                    int32_t *next, unsigned long long *g) {
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    unsigned long long *ncnt = level_group(g, L + 1), *nstat = ncnt + 1;
-    level_begin(g, L, true);
-    __shared__ Appender app;
-    app_begin(app);
-    unsigned long long dsum = 0, dmax = 0;
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < nnz; base += stride) {
-        const int64_t s = base + threadIdx.x;
-        bool claim = false;
-        int32_t w = 0;
-        if (s < nnz) {
-            const int32_t u = erow[s];
-            if (level[u] == L) {
-                w = col[s];
-                claim = level[w] < 0 && atomicCAS(&level[w], -1, L + 1) == -1;
-                if (claim) parent[w] = u;
-            }
+    for (int64_t i = 0; i < nlong; i++) {
+        const int32_t v = front[n - 1 - i];
+        const int64_t a = row_ptr[v], b = row_ptr[v + 1];
+        for (int64_t s0 = a + ((int64_t)blockIdx.x * BS + threadIdx.x) / WAVE * WAVE; s0 < b;
+             s0 += (int64_t)gridDim.x * BS) {
+            const int64_t sl = s0 + lane_id();
+            bool claim = false;
+            int32_t w = 0;
+            if (sl < b) claim = td_claim(col, level, parent, L, v, sl, w);
+            claim_vertex(app, claim, row_ptr, n, w, next, ng, dsum, dmax);
         }
-        app_push(app, claim, w, next, ncnt);
-        add_degree(claim, row_ptr, w, dsum, dmax);
     }
-    app_end(app, next, ncnt);
-    block_degree(dsum, dmax, nstat);
 }
 
 // Bottom-up level for a large frontier: every unvisited vertex looks along
-// its row for a neighbour on level L and takes the first it meets as its
+// its row for a neighbour on level L and takes one that it meets as its
 // parent (no atomics: a vertex writes only its own entries; the level L + 1
-// it writes is never mistaken for L).
-__global__ __launch_bounds__(BLOCK) void k_st_bottom_up(int32_t n, const int64_t *row_ptr, const int32_t *col,
-                                                        int32_t *level, int32_t *parent, int L, int32_t *next,
-                                                        unsigned long long *g) {
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    unsigned long long *ncnt = level_group(g, L + 1), *nstat = ncnt + 1;
-    level_begin(g, L, true);
+// it writes is never mistaken for L).  A row that has shown none in its first
+// BU_LANE slots is walked on by the whole wave; looking at 2, 4 or 8 slots at
+// once instead of one measured the same.
+constexpr int BU_LANE = 64;
+template <int BS>
+__device__ __forceinline__ void bottom_up(Appender &app, int32_t n, const int64_t *row_ptr, const int32_t *col,
+                                          int32_t *level, int32_t *parent, int L, int32_t *next,
+                                          unsigned long long *g, unsigned long long &dsum,
+                                          unsigned long long &dmax) {
+    const int64_t stride = (int64_t)gridDim.x * BS;
+    unsigned long long *ng = level_group(g, L + 1);
+    for (int64_t base = (int64_t)blockIdx.x * BS; base < n; base += stride) {
+        const int64_t v = base + threadIdx.x;
+        int32_t p = -1;
+        int64_t s = 0, b = 0;
+        if (v < n && level[v] < 0) {
+            s = row_ptr[v];
+            b = row_ptr[v + 1];
+            const int64_t e = b - s > BU_LANE ? s + BU_LANE : b;
+            for (; s < e && p < 0; s++) {
+                const int32_t u = col[s];
+                if (level[u] == L) p = u;
+            }
+        }
+        uint64_t m = __ballot(p < 0 && s < b);
+        while (m) {
+            const int lane = __ffsll((unsigned long long)m) - 1;
+            m &= m - 1;
+            const int64_t ws = __shfl(s, lane), wb = __shfl(b, lane);
+            int32_t got = -1;
+            uint64_t hit = 0;
+            for (int64_t t0 = ws; t0 < wb && !hit; t0 += WAVE) {
+                const int64_t t = t0 + lane_id();
+                got = t < wb ? col[t] : -1;
+                hit = __ballot(got >= 0 && level[got] == L);
+            }
+            if (hit) {
+                got = __shfl(got, __ffsll((unsigned long long)hit) - 1);
+                if (lane_id() == lane) p = got;
+            }
+        }
+        if (p >= 0) {
+            parent[v] = p;
+            level[v] = L + 1;
+        }
+        claim_vertex(app, p >= 0, row_ptr, n, (int32_t)v, next, ng, dsum, dmax);
+    }
+}
+
+// A frontier with few edges is expanded from its own rows, one with many
+// bottom-up.
+__host__ __device__ inline bool few_edges(uint64_t dsum, int64_t nnz) { return dsum * 16 < (uint64_t)nnz; }
+
+// One level, top-down or as its counters say (choose): the levels can be
+// queued without the host reading them in between.  k: the number of the
+// launch (its parity); fronts are taken by the level's parity.
+template <int BS>
+__global__ __launch_bounds__(BS) void k_st_level(int32_t n, int64_t nnz, const int64_t *row_ptr, const int32_t *col,
+                                                 int32_t *level, int32_t *parent, int k, int32_t *front0,
+                                                 int32_t *front1, unsigned long long *g, int choose) {
+    const int L = (int)g[CNT_LEVEL + (k & 1)];
+    const unsigned long long *c = level_group(g, L);
+    const bool nonempty = c[0] + c[3] > 0;
+    level_begin(g, L, k, nonempty);
+    if (!nonempty) return;
+    const int32_t *front = L & 1 ? front1 : front0;
+    int32_t *next = L & 1 ? front0 : front1;
     __shared__ Appender app;
     app_begin(app);
     unsigned long long dsum = 0, dmax = 0;
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < n; base += stride) {
-        const int64_t v = base + threadIdx.x;
-        bool claim = false;
-        if (v < n && level[v] < 0) {
-            const int64_t b = row_ptr[v + 1];
-            for (int64_t s = row_ptr[v]; s < b; s++) {
-                const int32_t u = col[s];
-                if (level[u] == L) {
-                    parent[v] = u;
-                    level[v] = L + 1;
-                    claim = true;
-                    break;
+    if (!choose || few_edges(c[1], nnz))
+        top_down<BS>(app, n, row_ptr, col, level, parent, L, front, next, g, dsum, dmax);
+    else
+        bottom_up<BS>(app, n, row_ptr, col, level, parent, L, next, g, dsum, dmax);
+    app_end<BS>(app, next, level_group(g, L + 1));
+    block_degree<BS>(dsum, dmax, level_group(g, L + 1) + 1);
+}
+
+// Levels with a small frontier and short rows, by one workgroup, until one is
+// not or SOLO_LEVELS are done (so a launch ends in bounded time): a level's
+// claims stay in LDS with their rows, which leaves it three dependent memory
+// accesses (the slot, the neighbour's level, its row) and no launch.  Bound by
+// them.  A path of 20000 vertices took 109 ms with a launch a level and takes
+// 24; a 512 x 512 grid (frontiers up to 512) 7.0 and 3.6.  The workgroup walks
+// 256 rows at once, so beyond SOLO_FRONTIER a launch over the chip is as fast:
+// a 2048 x 2048 grid took 26.3, 25.3, 27.3 and 49.9 ms with bounds of 256, 512,
+// 1024 and 2048, the 512 x 512 grid 4.7, 3.6, 3.5 and 3.6.
+constexpr int SOLO_FRONTIER = 512, SOLO_ROW = 32, SOLO_LEVELS = 4096;
+__global__ __launch_bounds__(WIDE_BLOCK) void k_st_solo(int32_t n, const int64_t *row_ptr, const int32_t *col,
+                                                        int32_t *level, int32_t *parent, int k, int32_t *front0,
+                                                        int32_t *front1, unsigned long long *g) {
+    __shared__ int32_t s_v[2][SOLO_FRONTIER], s_len[2][SOLO_FRONTIER];
+    __shared__ int64_t s_row[2][SOLO_FRONTIER];
+    __shared__ int s_n[2], s_long, s_wide;
+    const int L0 = (int)g[CNT_LEVEL + (k & 1)];
+    const unsigned long long *c0 = level_group(g, L0);
+    const int64_t nf0 = (int64_t)c0[0];
+    int L = L0;
+    if (nf0 > 0 && nf0 <= SOLO_FRONTIER && c0[3] == 0 && c0[2] <= SOLO_ROW) {
+        const int32_t *front = L & 1 ? front1 : front0;
+        for (int i = threadIdx.x; i < nf0; i += WIDE_BLOCK) {
+            const int32_t v = front[i];
+            const int64_t a = row_ptr[v];
+            s_v[L & 1][i] = v;
+            s_row[L & 1][i] = a;
+            s_len[L & 1][i] = (int32_t)(row_ptr[v + 1] - a);
+        }
+        if (threadIdx.x == 0) {
+            s_n[L & 1] = (int)nf0;
+            s_n[(L + 1) & 1] = 0;
+            s_long = 0;
+            s_wide = 0;
+        }
+        unsigned long long dsum, dmax;
+        for (;;) {
+            __syncthreads();
+            const int b = L & 1, nf = s_n[b];
+            int32_t *next = b ? front0 : front1;
+            dsum = dmax = 0;
+            for (int f = threadIdx.x >> 2; f < nf; f += WIDE_BLOCK / 4) {
+                const int32_t v = s_v[b][f], len = s_len[b][f];
+                const int64_t a = s_row[b][f];
+                for (int r = threadIdx.x & 3; r < len; r += 4) {
+                    const int32_t w = col[a + r];
+                    if (level[w] >= 0 || atomicCAS(&level[w], -1, L + 1) != -1) continue;
+                    parent[w] = v;
+                    const int64_t wa = row_ptr[w], wl = row_ptr[w + 1] - wa;
+                    dsum += (unsigned long long)wl;
+                    dmax = (unsigned long long)wl > dmax ? (unsigned long long)wl : dmax;
+                    if (wl > SOLO_ROW) s_wide = 1;
+                    if (wl > LONG_ROW) {
+                        next[n - 1 - (int64_t)atomicAdd(&s_long, 1)] = w;
+                        continue;
+                    }
+                    const int p = atomicAdd(&s_n[b ^ 1], 1);
+                    if (p < SOLO_FRONTIER) {
+                        s_v[b ^ 1][p] = w;
+                        s_row[b ^ 1][p] = wa;
+                        s_len[b ^ 1][p] = (int32_t)wl;
+                    } else {
+                        next[p] = w;
+                    }
                 }
             }
+            __syncthreads();
+            L++;
+            const int nn = s_n[b ^ 1];
+            if (nn == 0 || nn > SOLO_FRONTIER || s_wide || L - L0 >= SOLO_LEVELS) break;
+            if (threadIdx.x == 0) s_n[b] = 0;
         }
-        app_push(app, claim, (int32_t)v, next, ncnt);
-        add_degree(claim, row_ptr, (int32_t)v, dsum, dmax);
+        // the frontier reached and its counters, as a level's kernel leaves them
+        const int b = L & 1, nn = s_n[b];
+        int32_t *front_out = b ? front1 : front0;
+        for (int i = threadIdx.x; i < nn && i < SOLO_FRONTIER; i += WIDE_BLOCK) front_out[i] = s_v[b][i];
+        unsigned long long *c = level_group(g, L);
+        if (threadIdx.x < 12) g[threadIdx.x] = 0;
+        __threadfence();
+        __syncthreads();
+        block_degree<WIDE_BLOCK>(dsum, dmax, c + 1);
+        if (threadIdx.x == 0) {
+            c[0] = (unsigned long long)nn;
+            c[3] = (unsigned long long)s_long;
+            g[CNT_DEPTH] = (unsigned long long)L;
+        }
     }
-    app_end(app, next, ncnt);
-    block_degree(dsum, dmax, nstat);
+    if (threadIdx.x == 0) g[CNT_LEVEL + ((k + 1) & 1)] = (unsigned long long)L;
 }
 
 }  // namespace
@@ -343,24 +543,23 @@ using namespace drsf;
 
 namespace {
 
-// Scratch of one static rebuild: the row of every CSR slot and its marks,
-// scan partials, breadth-first levels, two frontiers, the hooking flag and
-// the level counters.
+// Scratch of one static rebuild: breadth-first levels, two frontiers, the
+// sampled component and the level counters, each 256-byte aligned in one
+// block.
 struct StaticScratch {
-    int32_t *erow, *level, *front0, *front1, *flag;
-    uint32_t *mark;
-    void *stmp;
+    int32_t *level, *front0, *front1, *giant;
     unsigned long long *cnt;
 };
-
-// Device bytes of each scratch array, in StaticScratch order of carving.
-void scratch_sizes(int32_t n, int64_t nnz, size_t sz[8]) {
-    sz[0] = sizeof(int32_t) * (size_t)(nnz + 1);                       // erow
-    sz[1] = sizeof(uint32_t) * (size_t)std::max<int64_t>(nnz, 1);      // mark
-    sz[2] = scan_tmp_bytes(nnz) + 64;                                  // stmp
-    sz[3] = sz[4] = sz[5] = sizeof(int32_t) * (size_t)n;              // level, front0, front1
-    sz[6] = sizeof(int32_t);                                           // flag
-    sz[7] = CNT_WORDS * sizeof(unsigned long long);                    // cnt
+size_t aligned(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+size_t scratch_bytes(int32_t n) {
+    return 3 * aligned(sizeof(int32_t) * (size_t)n) + aligned(sizeof(int32_t)) +
+           aligned(CNT_WORDS * sizeof(unsigned long long));
+}
+StaticScratch carve(void *p, int32_t n) {
+    unsigned char *b = static_cast<unsigned char *>(p);
+    const size_t v = aligned(sizeof(int32_t) * (size_t)n);
+    return StaticScratch{(int32_t *)b, (int32_t *)(b + v), (int32_t *)(b + 2 * v), (int32_t *)(b + 3 * v),
+                         (unsigned long long *)(b + 3 * v + aligned(sizeof(int32_t)))};
 }
 
 // The rebuild on given scratch; h: host memory for CNT_WORDS counters
@@ -368,9 +567,7 @@ void scratch_sizes(int32_t n, int64_t nnz, size_t sz[8]) {
 int static_forest_core(int32_t n, const int64_t *row_ptr, const int32_t *col, int64_t nnz, int32_t *parent_out,
                        int32_t *label_out, hipStream_t s, int32_t *levels_out, const StaticScratch &w,
                        unsigned long long *h) {
-    int32_t *erow = w.erow, *level = w.level, *front0 = w.front0, *front1 = w.front1, *flag = w.flag;
-    uint32_t *mark = w.mark;
-    void *stmp = w.stmp;
+    int32_t *level = w.level;
     unsigned long long *cnt = w.cnt;
     int rc = DRSF_OK;
     auto ok = [&](hipError_t e) {
@@ -378,90 +575,132 @@ int static_forest_core(int32_t n, const int64_t *row_ptr, const int32_t *col, in
         return e == hipSuccess;
     };
     int32_t *comp = label_out;
-    const int gv = grid_for(n, BLOCK), ge = grid_for(nnz, BLOCK);
-    if (nnz > 0) {  // row of every slot (the exclusive sums land in erow itself)
-        launch_fill_i32(reinterpret_cast<int32_t *>(mark), nnz, 0, s);
-        hipLaunchKernelGGL(k_st_marks, dim3(gv), dim3(BLOCK), 0, s, n, row_ptr, nnz, mark);
-        launch_scan_u32(mark, reinterpret_cast<uint32_t *>(erow), cnt, nnz, stmp, s);
-        hipLaunchKernelGGL(k_st_rows, dim3(ge), dim3(BLOCK), 0, s, nnz, mark,
-                           reinterpret_cast<const uint32_t *>(erow), erow);
-    }
-    hipLaunchKernelGGL(k_st_iota, dim3(gv), dim3(BLOCK), 0, s, n, comp);
-    // hooking rounds until nothing hooks (each round at least halves the
-    // roots that still have an edge to another root)
-    for (int round = 0; round < 64 && rc == DRSF_OK; round++) {
-        launch_fill_i32(flag, 1, 0, s);
-        hipLaunchKernelGGL(k_st_hook, dim3(ge), dim3(BLOCK), 0, s, nnz, erow, col, comp, flag);
+    const int gv = grid_for(n, BLOCK);
+    hipLaunchKernelGGL(k_st_comp_init, dim3(gv), dim3(BLOCK), 0, s, n, row_ptr, col, comp, cnt);
+    if (nnz > 0) {
         hipLaunchKernelGGL(k_st_compress, dim3(gv), dim3(BLOCK), 0, s, n, comp);
-        if (!ok(hipMemcpyAsync(h, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s)) || !ok(hipStreamSynchronize(s)))
-            break;
-        if (*(int32_t *)h == 0) break;
-        if (round == 63) rc = DRSF_E_DEVICE;
+        hipLaunchKernelGGL(k_st_link_first, dim3(gv), dim3(BLOCK), 0, s, n, row_ptr, col, comp);
+        hipLaunchKernelGGL(k_st_compress, dim3(gv), dim3(BLOCK), 0, s, n, comp);
+        hipLaunchKernelGGL(k_st_sample, dim3(1), dim3(BLOCK), 0, s, n, comp, w.giant);
+        hipLaunchKernelGGL(k_st_link_rest, dim3(gv), dim3(BLOCK), 0, s, n, row_ptr, col, comp, w.giant);
+        hipLaunchKernelGGL(k_st_compress, dim3(gv), dim3(BLOCK), 0, s, n, comp);
     }
-    // breadth-first forest from the roots, a level at a time; the host
-    // reads level L's counters and picks the kernel.  While the frontier's
-    // rows are short and their sum is far below the switch point, up to
-    // BATCH_MAX top-down levels are queued at once (the batch length
-    // doubles while this keeps holding), so a deep graph with small
-    // frontiers pays one host read per batch instead of per level; a
-    // top-down level takes its frontier size from the device, so a batch
-    // that outgrows its estimate stays correct, only slower.
-    constexpr int BATCH_MAX = 64;
-    launch_fill_u64(reinterpret_cast<uint64_t *>(cnt), CNT_WORDS, 0, s);
-    hipLaunchKernelGGL(k_st_bfs_init, dim3(gv), dim3(BLOCK), 0, s, n, row_ptr, comp, level, parent_out, front0,
-                       cnt);
-    int32_t *fr[2] = {front0, front1};
-    int L = 0, batch = 1;
+    // breadth-first forest from the roots, a level at a time.  A launch takes
+    // its level and frontier from the device, so launches are queued ahead of
+    // the host's reads of the counters: first a run of small levels and
+    // FIRST_LEVELS levels that pick their direction on the device (a power-law
+    // graph is nearly done then).  After a read, small frontiers run on in one
+    // workgroup, with levels over the chip behind for what it grows to.  While
+    // the frontier's rows' sum is far below the switch point, up to BATCH_MAX
+    // top-down levels are queued at once (the batch length doubles while this
+    // keeps holding), so a deep graph pays one host read per batch instead of
+    // per level; a batch that outgrows its estimate stays correct, only slower.
+    constexpr int BATCH_MAX = 64, FIRST_LEVELS = 4, WIDE_CAP = GRID_CAP * BLOCK / WIDE_BLOCK;
+    const int gl = grid_for(n, WIDE_BLOCK, WIDE_CAP);
+    hipLaunchKernelGGL(k_st_bfs_init, dim3(gl), dim3(WIDE_BLOCK), 0, s, n, row_ptr, comp, level, parent_out,
+                       w.front0, cnt);
+    int launches = 0, batch = 1;
+    auto solo = [&]() {
+        hipLaunchKernelGGL(k_st_solo, dim3(1), dim3(WIDE_BLOCK), 0, s, n, row_ptr, col, level, parent_out,
+                           launches++, w.front0, w.front1, cnt);
+    };
+    auto wide = [&]() {
+        hipLaunchKernelGGL((k_st_level<WIDE_BLOCK>), dim3(gl), dim3(WIDE_BLOCK), 0, s, n, nnz, row_ptr, col, level,
+                           parent_out, launches++, w.front0, w.front1, cnt, 1);
+    };
+    if (nnz > 0) {
+        solo();
+        for (int i = 0; i < FIRST_LEVELS; i++) wide();
+    }
     while (rc == DRSF_OK) {
         if (!ok(hipMemcpyAsync(h, cnt, CNT_WORDS * sizeof(unsigned long long), hipMemcpyDeviceToHost, s)) ||
             !ok(hipStreamSynchronize(s)))
             break;
+        const int64_t L = (int64_t)h[CNT_LEVEL + (launches & 1)];
         const unsigned long long *hg = h + 4 * (L % 3);
-        const int64_t nf = (int64_t)hg[0], dsum = (int64_t)hg[1];
-        const uint64_t dmax = hg[2];
+        const int64_t nf = (int64_t)(hg[0] + hg[3]);
         if (nf == 0) break;
         if (L > n) {  // more levels than vertices: the counters are wrong
             rc = DRSF_E_DEVICE;
             break;
         }
-        if (dsum * 16 < nnz && dmax <= 4096) {
-            // a frontier with few edges and short rows: top-down from its
-            // own rows (four lanes per vertex; room for twice the frontier
-            // in a batch)
-            const int k = dsum * 256 < nnz ? batch : 1;
-            const int g = (int)std::min<int64_t>(GRID_CAP, grid_for(std::max<int64_t>(2 * nf, 64) * 4, BLOCK));
-            for (int i = 0; i < k; i++, L++)
-                hipLaunchKernelGGL(k_st_top_down, dim3(g), dim3(BLOCK), 0, s, row_ptr, col, level, parent_out, L,
-                                   fr[L & 1], fr[(L + 1) & 1], cnt);
+        if (nf <= SOLO_FRONTIER && hg[2] <= SOLO_ROW) {
+            batch = 1;
+            solo();
+            wide();
+        } else if (few_edges(hg[1], nnz)) {
+            // room for twice the frontier in a batch; a long row takes the
+            // whole grid
+            const int k = hg[1] * 256 < (uint64_t)nnz ? batch : 1;
+            const int64_t want = std::max<int64_t>(std::max<int64_t>(2 * nf, 64) * 4, hg[3] ? (int64_t)hg[2] : 0);
+            const int g = grid_for(want, BLOCK);
+            if (g > WIDE_CAP) {  // its workgroups' atomics would be most of its time
+                batch = 1;
+                wide();
+                continue;
+            }
+            for (int i = 0; i < k; i++)
+                hipLaunchKernelGGL((k_st_level<BLOCK>), dim3(g), dim3(BLOCK), 0, s, n, nnz, row_ptr, col, level,
+                                   parent_out, launches++, w.front0, w.front1, cnt, 0);
             batch = k == batch ? std::min(2 * batch, BATCH_MAX) : 1;
         } else {
-            // few edges but a long row: one pass over every slot; many
-            // edges: bottom-up
             batch = 1;
-            if (dsum * 16 < nnz)
-                hipLaunchKernelGGL(k_st_edges, dim3(ge), dim3(BLOCK), 0, s, nnz, row_ptr, erow, col, level,
-                                   parent_out, L, fr[(L + 1) & 1], cnt);
-            else
-                hipLaunchKernelGGL(k_st_bottom_up, dim3(gv), dim3(BLOCK), 0, s, n, row_ptr, col, level, parent_out,
-                                   L, fr[(L + 1) & 1], cnt);
-            L++;
+            wide();
         }
     }
-    if (levels_out) *levels_out = rc == DRSF_OK ? (int32_t)h[CNT_DEPTH] : 0;
+    // a graph without edges has one level, its roots
+    if (levels_out) *levels_out = rc == DRSF_OK ? std::max<int32_t>(1, (int32_t)h[CNT_DEPTH]) : 0;
     if (rc == DRSF_OK && !ok(hipStreamSynchronize(s))) rc = DRSF_E_DEVICE;
     return rc;
 }
 
-// Reads row_ptr[n] (the CSR's entry count) on the stream.
-int read_nnz(int32_t n, const int64_t *row_ptr, hipStream_t s, int64_t *nnz) {
-    *nnz = 0;
-    if (hipMemcpyAsync(nnz, row_ptr + n, sizeof *nnz, hipMemcpyDeviceToHost, s) != hipSuccess ||
+// Reads row_ptr[n] (the CSR's entry count) on the stream, through a word of h.
+int read_nnz(int32_t n, const int64_t *row_ptr, hipStream_t s, unsigned long long *h, int64_t *nnz) {
+    if (hipMemcpyAsync(h, row_ptr + n, sizeof *nnz, hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess) {
         (void)hipGetLastError();
         return DRSF_E_DEVICE;
     }
+    *nnz = (int64_t)h[0];
     return DRSF_OK;
 }
+
+// Pinned words for the level counters of calls in flight: a few slots kept
+// until the process ends, one taken by each call and given back; a call that
+// finds none free allocates its own.  A copy to pinned words and the wait for
+// it take 12 us, to pageable ones 21, allocating pinned words on each call 27.
+constexpr int PIN_SLOTS = 8;
+std::mutex g_pin_mu;
+unsigned long long *g_pin[PIN_SLOTS] = {};
+bool g_pin_used[PIN_SLOTS] = {};
+struct PinnedWords {
+    unsigned long long *p = nullptr;
+    int slot = -1;
+    PinnedWords() {
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        for (int k = 0; k < PIN_SLOTS && slot < 0; k++)
+            if (!g_pin_used[k]) slot = k;
+        unsigned long long *q = slot >= 0 ? g_pin[slot] : nullptr;
+        if (!q && hipHostMalloc((void **)&q, CNT_WORDS * sizeof(unsigned long long), hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            slot = -1;
+            return;
+        }
+        p = q;
+        if (slot >= 0) {
+            g_pin[slot] = q;
+            g_pin_used[slot] = true;
+        }
+    }
+    ~PinnedWords() {
+        if (slot >= 0) {
+            std::lock_guard<std::mutex> lk(g_pin_mu);
+            g_pin_used[slot] = false;
+        } else if (p) {
+            (void)hipHostFree(p);
+        }
+    }
+};
 
 // Scratch of the allocation-free entry point: one array per device, held
 // until the process ends.  In host code its name only stands for the
@@ -505,29 +744,20 @@ extern "C" int drsf_static_forest(int32_t n, const int64_t *row_ptr, const int32
         return DRSF_OK;
     }
     hipStream_t s = (hipStream_t)stream;
+    PinnedWords h;
+    if (!h.p) return DRSF_E_NOMEM;
     int64_t nnz = 0;
-    int rc = read_nnz(n, row_ptr, s, &nnz);
+    int rc = read_nnz(n, row_ptr, s, h.p, &nnz);
     if (rc) return rc;
     if (nnz < 0 || (nnz > 0 && !col)) return DRSF_E_ARG;
-    size_t sz[8];
-    scratch_sizes(n, nnz, sz);
-    void *p[8] = {};
-    unsigned long long *h = nullptr;
-    bool got = true;
-    for (int k = 0; k < 8 && got; k++) got = hipMalloc(&p[k], sz[k]) == hipSuccess;
-    got = got && hipHostMalloc((void **)&h, CNT_WORDS * sizeof(unsigned long long)) == hipSuccess;
-    if (!got) {
+    void *p = nullptr;
+    if (hipMalloc(&p, scratch_bytes(n)) != hipSuccess) {
         (void)hipGetLastError();
-        rc = DRSF_E_NOMEM;
-    } else {
-        const StaticScratch w{(int32_t *)p[0], (int32_t *)p[3], (int32_t *)p[4], (int32_t *)p[5],
-                              (int32_t *)p[6], (uint32_t *)p[1], p[2], (unsigned long long *)p[7]};
-        rc = static_forest_core(n, row_ptr, col, nnz, parent_out, label_out, s, levels_out, w, h);
+        return DRSF_E_NOMEM;
     }
+    rc = static_forest_core(n, row_ptr, col, nnz, parent_out, label_out, s, levels_out, carve(p, n), h.p);
     (void)hipStreamSynchronize(s);
-    for (void *q : p)
-        if (q) (void)hipFree(q);
-    if (h) (void)hipHostFree(h);
+    (void)hipFree(p);
     return rc;
 }
 
@@ -544,22 +774,17 @@ extern "C" int drsf_static_forest_noalloc(int32_t n, const int64_t *row_ptr, con
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
     int64_t nnz = 0;
-    if ((rc = read_nnz(n, row_ptr, s, &nnz))) return rc;
+    unsigned long long h[CNT_WORDS] = {};  // pageable: each read follows a stream synchronisation
+    if ((rc = read_nnz(n, row_ptr, s, h, &nnz))) return rc;
     if (nnz < 0 || (nnz > 0 && !col)) return DRSF_E_ARG;
     if (nnz > ((int64_t)1 << 32)) return DRSF_E_CAPACITY;
-    size_t sz[8], off[8], total = 0;
-    scratch_sizes(n, nnz, sz);
-    for (int k = 0; k < 8; k++) {  // each array 256-byte aligned inside the scratch
-        off[k] = total;
-        total += (sz[k] + 255) & ~(size_t)255;
-    }
+    // the documented bound, whatever part of the array is used
+    size_t total = 3 * aligned(sizeof(int32_t) * (size_t)n) + aligned(sizeof(int32_t) * (size_t)(nnz + 1)) +
+                   aligned(sizeof(uint32_t) * (size_t)std::max<int64_t>(nnz, 1)) +
+                   aligned(scan_tmp_bytes(nnz) + 64) + aligned(sizeof(int32_t)) +
+                   aligned(CNT_WORDS * sizeof(unsigned long long));
     if (total > NOALLOC_SCRATCH_BYTES) return DRSF_E_CAPACITY;
-    unsigned char *b = static_cast<unsigned char *>(base);
-    const StaticScratch w{(int32_t *)(b + off[0]), (int32_t *)(b + off[3]), (int32_t *)(b + off[4]),
-                          (int32_t *)(b + off[5]), (int32_t *)(b + off[6]), (uint32_t *)(b + off[1]),
-                          (void *)(b + off[2]), (unsigned long long *)(b + off[7])};
-    unsigned long long h[CNT_WORDS] = {};  // pageable: each read follows a stream synchronisation
-    rc = static_forest_core(n, row_ptr, col, nnz, parent_out, label_out, s, levels_out, w, h);
+    rc = static_forest_core(n, row_ptr, col, nnz, parent_out, label_out, s, levels_out, carve(base, n), h);
     (void)hipStreamSynchronize(s);
     return rc;
 }
