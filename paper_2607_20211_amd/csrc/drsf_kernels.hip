@@ -1517,10 +1517,10 @@ __global__ __launch_bounds__(BLOCK, 4) void k_key_edges(Dev d, int parts) {
 __device__ __forceinline__ uint64_t hook_pack(int r, int32_t other) {
     return ((uint64_t)(uint32_t)r << 32) | (uint32_t)other;
 }
-// Long chains are shortened on the way: an entry passed is made to point two
-// hooks up, with its own tag (any ancestor a concurrent reader sees will do).
-// On a grid, where pieces hook along whole rows, the edges' walks otherwise
-// repeat chains of hundreds of hooks.
+// Only a component's own thread writes its entry, here and in k_bor_flat: two
+// XCDs that store one word by plain stores in one launch can be left with L2
+// copies that differ beyond its end, and such a copy must not outlive the
+// entry's reset in the next update.
 __device__ __forceinline__ int32_t hook_to(uint64_t h) { return (int32_t)(uint32_t)h; }
 __device__ __forceinline__ bool hooked(uint64_t h, uint32_t r) { return (uint32_t)(h >> 32) < r; }
 // N pieces at once, their loads in flight together; entries that are not `on`
@@ -1544,7 +1544,6 @@ __device__ __forceinline__ void comp_roots(const Dev &d, const bool (&on)[N], in
             if (!go[k]) continue;
             const int32_t y = hook_to(h[k]);
             go[k] = hooked(h2[k], r);
-            if (go[k]) d.hook[x[k]] = (h[k] & 0xffffffff00000000ull) | (uint32_t)hook_to(h2[k]);
             x[k] = y;
             h[k] = h2[k];
             more |= go[k];
@@ -1721,6 +1720,37 @@ __global__ __launch_bounds__(BLOCK) void k_bor_select(Dev d, int r) {
         __syncthreads();  // obase is reused by the next unit
     }
     s_min.flush(best);
+}
+
+// After a delete's first hooks: every piece's entry, its tag kept, is made to
+// point to the end of its chain, by its own thread.  On a grid pieces hook
+// along whole rows, and without this the edges' walks repeat chains of hundreds
+// of hooks: 4096 x 4096, 1e5 deletes and inserts a step, 1325 us without and
+// 1150 with (the kernel 10); after the second round's hooks it gains nothing
+// more.  Below FLAT_BATCH updates there are too few pieces for it to pay for its
+// launch (R-MAT 20, 1e4 updates: 218 us without, 226 with).  The steps in between
+// are published, so that the walks of a long chain shorten each other.
+constexpr int FLAT_BATCH = 1 << 15;
+__global__ __launch_bounds__(BLOCK) void k_bor_flat(Dev d) {
+    if (stopped(d) || d.cnt[C_DONE_BOR]) return;
+    const int64_t np = (int64_t)d.cnt[C_NP];
+    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    for (int64_t p = (int64_t)blockIdx.x * BLOCK + threadIdx.x; p < np; p += stride) {
+        const uint64_t h = d.hook[p];
+        if (!hooked(h, 1u)) continue;
+        const uint64_t tag = h & 0xffffffff00000000ull;
+        uint64_t x = h;
+        for (int64_t steps = 0;; steps++) {
+            const uint64_t y = d.hook[hook_to(x)];
+            if (!hooked(y, 1u)) break;
+            x = y;
+            d.hook[p] = tag | (uint32_t)hook_to(x);
+            if (steps > np) {
+                atomicOr(d.status, ST_WALK_BOUND);
+                break;
+            }
+        }
+    }
 }
 
 // Super-trees oriented as they grow (Ctl::walk).  A component's pieces hang
@@ -2977,6 +3007,7 @@ void launch_boruvka(const Dev &d, int r0, int r1, int64_t units, bool ins, hipSt
         else if (ins)
             hipLaunchKernelGGL(k_bor_round0, dim3(grid_for(d.lb, BLOCK, EMIT_CAP)), dim3(BLOCK), 0, s, d);
         hipLaunchKernelGGL(k_bor_hook, dim3(gp), dim3(BLOCK), 0, s, d, r);
+        if (r == 0 && !ins && d.lb >= FLAT_BATCH) hipLaunchKernelGGL(k_bor_flat, dim3(gp), dim3(BLOCK), 0, s, d);
     }
     // the tail reads a dense list, which rounds from 2 on have
     if (r1 >= 2 && r1 > r0) hipLaunchKernelGGL(k_bor_tail, dim3(1), dim3(TAIL_THREADS), 0, s, d, r1);

@@ -49,6 +49,17 @@ def test_many_pieces_and_long_hook_chains(rows, cols, cuts, sweep_mode):
     _run(g, [(dl, drsf.DRSF_DELETE), (dl, drsf.DRSF_INSERT)], sweep_mode=sweep_mode)
 
 
+@pytest.mark.parametrize("rows,cols,cuts", [(2, 40001, 32767), (2, 40001, 32768), (1, 65537, 65536)])
+def test_chains_shortened_by_their_own_pieces(rows, cols, cuts):
+    """Batches around the one from which a pass after the first hooks shortens
+    their chains; in a path every hook fails to find an edge."""
+    drsf = _lib()
+    _case(f"grid {rows} x {cols}, {cuts} tree edges cut")
+    g = gen.make_graph("grid", rows * cols, gen.grid(rows, cols, 0, gen.seed(85, rows, gen.P_GRAPH)))
+    dl = gen.delete_batches(g.n, g.keys, g.parent, 1, cuts, cuts, gen.seed(85, rows, gen.P_DELETE))[0]
+    _run(g, [(dl, drsf.DRSF_DELETE), (dl, drsf.DRSF_INSERT), (dl[::2], drsf.DRSF_DELETE)])
+
+
 @pytest.mark.parametrize("leaves", [700, 5000])
 def test_one_piece_that_every_edge_touches(leaves):
     """Inserts and deletes of a star's rays: all edges meet the centre's piece."""
