@@ -270,6 +270,7 @@ struct drsf_ctx {
     // updated whole by one workgroup each, beside the chain, on stream s2
     int32_t nsg = 0, small_T = 0, small_threads = 512, small_grid = 0;
     std::vector<int32_t> g2s;            // graph -> small graph index, or -1
+    std::vector<int32_t> small_order;    // small graph indexes, larger graphs first
     std::vector<int32_t> sgid_h;
     std::vector<int64_t> scap_h, soff_h, svoff_h;
     int64_t pool_keys = 0, nsv = 0;
@@ -788,14 +789,21 @@ int setup_small(drsf_ctx *c) {
         (rc = dalloc(c, &c->spar, c->nsv)) || (rc = dalloc(c, &c->slab, c->nsv)) ||
         (rc = dalloc(c, &c->ser, c->nsv)) || (rc = dalloc(c, &c->bkeys, c->max_batch)) ||
         (rc = dalloc(c, &c->htab, 2 * c->max_batch + 4 * (int64_t)c->nsg)) || (rc = dalloc(c, &c->stasks, c->nsg)) ||
-        (rc = dalloc(c, &c->qhead, 1)))
+        (rc = dalloc(c, &c->qhead, 2)))
         return rc;
     if ((rc = halloc(c, &c->h_stasks, c->nsg))) return rc;
+    // the engine's queue holds the larger graphs first
+    c->small_order.resize((size_t)c->nsg);
+    for (int32_t k = 0; k < c->nsg; k++) c->small_order[k] = k;
+    std::stable_sort(c->small_order.begin(), c->small_order.end(), [c](int32_t a, int32_t b) {
+        const int32_t ga = c->sgid_h[a], gb = c->sgid_h[b];
+        return c->goff_h[ga + 1] - c->goff_h[ga] > c->goff_h[gb + 1] - c->goff_h[gb];
+    });
     HIPCHK(c, hipMemcpyAsync(c->sgid, c->sgid_h.data(), 4 * (size_t)c->nsg, hipMemcpyHostToDevice, s));
     HIPCHK(c, hipMemcpyAsync(c->soff, c->soff_h.data(), 8 * (size_t)c->nsg, hipMemcpyHostToDevice, s));
     HIPCHK(c, hipMemcpyAsync(c->scap, c->scap_h.data(), 8 * (size_t)c->nsg, hipMemcpyHostToDevice, s));
     HIPCHK(c, hipMemcpyAsync(c->svoff, c->svoff_h.data(), 8 * (size_t)c->nsg, hipMemcpyHostToDevice, s));
-    launch_fill_i32(reinterpret_cast<int32_t *>(c->qhead), 1, 0, s);
+    launch_fill_i32(reinterpret_cast<int32_t *>(c->qhead), 2, 0, s);
     launch_small_init(make_dev(c), make_small(c), s);
     HIPCHK(c, hipStreamSynchronize(s));  // the pageable metadata sources
     if (hipStreamCreateWithFlags(&c->s2, hipStreamNonBlocking) != hipSuccess ||
@@ -1157,22 +1165,21 @@ void enqueue_update(drsf_ctx *c, int kind, bool profile, const Ctl *kc) {
     }
     const bool small = c->nsg > 0;
     if (small && c->nsg == c->ngraph) {
-        // every graph is small: the engine alone, then its commit and the
-        // cleanup (no kernel sequence; its time counts as replacement edges)
+        // every graph is small: the engine alone, then the cleanup (no
+        // kernel sequence; its time counts as replacement edges)
         for (int i = 0; i < PH_N; i++)
             if (i != PH_REPL) mark(i, false);
         mark(PH_REPL);
-        if (launch_small_update(d, make_small(c), c->small_threads, c->small_grid, s))
+        if (launch_small_update(d, make_small(c), c->small_threads, c->small_grid, true, s))
             launch_fill_i32(c->status, 1, ST_ROUND_BOUND, s);
         mark(PH_N);
-        launch_small_commit(d, make_small(c), grid_for(c->nsg, 1, GRID_CAP), true, s);
         launch_cleanup(d, s);
         return;
     }
     if (small) {  // the small graphs' kernel on its own branch
         (void)hipEventRecord(c->ev_fork, s);
         (void)hipStreamWaitEvent(c->s2, c->ev_fork, 0);
-        if (launch_small_update(d, make_small(c), c->small_threads, c->small_grid, c->s2))
+        if (launch_small_update(d, make_small(c), c->small_threads, c->small_grid, false, c->s2))
             launch_fill_i32(c->status, 1, ST_ROUND_BOUND, c->s2);
         (void)hipEventRecord(c->ev_join, c->s2);
     }
@@ -1236,7 +1243,7 @@ void enqueue_update(drsf_ctx *c, int kind, bool profile, const Ctl *kc) {
     mark(PH_N);
     if (small) {
         (void)hipStreamWaitEvent(s, c->ev_join, 0);
-        launch_small_commit(d, make_small(c), grid_for(c->nsg, 1, GRID_CAP), false, s);
+        launch_small_commit(d, make_small(c), grid_for(c->nsg, 1, GRID_CAP), s);
     }
     launch_cleanup(d, s);  // also hands the results to the host
 }
@@ -1489,21 +1496,16 @@ void set_regions(drsf_ctx *c, Ctl &k) {
     }
 }
 
+// A host batch into the context.
 int stage_edges(drsf_ctx *c, const int32_t *edges, int64_t b, bool in_place) {
     if (b == 0) return DRSF_OK;
-    hipStream_t s = c->stream;
-    if (c->opts.inputs_on_device) {
-        HIPCHK(c, hipMemcpyAsync(c->bedges, edges, sizeof(int32_t) * 2 * (size_t)b,
-                                 hipMemcpyDeviceToDevice, s));
-    } else {
-        // the previous update has completed, so the pinned staging is free;
-        // a small batch is read from there by the first kernel (a copy costs
-        // the host about 10 us)
-        memcpy(c->h_edges, edges, sizeof(int32_t) * 2 * (size_t)b);
-        if (in_place && b <= PINNED_BATCH) return DRSF_OK;
-        HIPCHK(c, hipMemcpyAsync(c->bedges, c->h_edges, sizeof(int32_t) * 2 * (size_t)b,
-                                 hipMemcpyHostToDevice, s));
-    }
+    // the previous update has completed, so the pinned staging is free;
+    // a small batch is read from there by the first kernel (a copy costs
+    // the host about 10 us)
+    memcpy(c->h_edges, edges, sizeof(int32_t) * 2 * (size_t)b);
+    if (in_place && b <= PINNED_BATCH) return DRSF_OK;
+    HIPCHK(c, hipMemcpyAsync(c->bedges, c->h_edges, sizeof(int32_t) * 2 * (size_t)b, hipMemcpyHostToDevice,
+                             c->stream));
     return DRSF_OK;
 }
 
@@ -1952,7 +1954,11 @@ int drsf_multi_apply_async(drsf_ctx *c, const int32_t *edges, const int64_t *b_o
             }
         if (b_off[g + 1] == b_off[g]) continue;
         if (k < 0) (op[g] == DRSF_DELETE ? any_del : any_ins) = true;
-        else c->h_stasks[nsmall++] = make_int4(k, (int)b_off[g], (int)(b_off[g + 1] - b_off[g]), op[g]);
+    }
+    for (const int32_t k : c->small_order) {
+        const int32_t g = c->sgid_h[k];
+        if (b_off[g + 1] == b_off[g]) continue;
+        c->h_stasks[nsmall++] = make_int4(k, (int)b_off[g], (int)(b_off[g + 1] - b_off[g]), op[g]);
     }
     hipStream_t s = c->stream;
     // lists of -1: every vertex block and tile (one graph: the lists, only
@@ -1989,9 +1995,11 @@ int drsf_multi_apply_async(drsf_ctx *c, const int32_t *edges, const int64_t *b_o
         HIPCHK(c, hipMemcpyAsync(c->bop, c->h_bop, (size_t)b, hipMemcpyHostToDevice, s));
         HIPCHK(c, hipMemcpyAsync(c->bgid, c->h_bgid, sizeof(int32_t) * (size_t)b, hipMemcpyHostToDevice, s));
     }
-    if ((rc = stage_edges(c, edges, b, false))) return rc;
+    // a device batch is read in place, as drsf_apply's is
+    if (!c->opts.inputs_on_device && (rc = stage_edges(c, edges, b, false))) return rc;
     Ctl &k = *c->h_ctl;
     memset(&k, 0, sizeof k);
+    if (c->opts.inputs_on_device) k.edges = edges;
     k.b = b;
     k.op = 2;
     k.has_ins = any_ins;

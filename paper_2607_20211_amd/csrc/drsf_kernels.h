@@ -196,13 +196,13 @@ struct SmallDev {
     uint32_t *bkeys;         // [max_b] batch keys (a graph's batch range)
     uint32_t *htab;          // [2 max_b + 4 nsg] hash sets of batch keys too large for LDS
     const int4 *tasks;       // [nsmall] (small graph, batch start, batch length, op)
-    unsigned int *qhead;     // work queue: next task (reset by the commit kernel)
+    unsigned int *qhead;     // work queue: next task, workgroups done (the last one resets both)
 };
 size_t small_lds_bytes(int T);  // dynamic LDS of the small-graph kernel for T vertices
 size_t small_static_lds();      // and its static LDS
 int small_prepare(int T);  // allows the kernel its LDS (once, before any launch or capture)
-int launch_small_update(const Dev &d, const SmallDev &s, int threads, int grid, hipStream_t st);
-void launch_small_commit(const Dev &d, const SmallDev &s, int grid, bool alone, hipStream_t st);
+int launch_small_update(const Dev &d, const SmallDev &s, int threads, int grid, bool alone, hipStream_t st);
+void launch_small_commit(const Dev &d, const SmallDev &s, int grid, hipStream_t st);
 void launch_small_init(const Dev &d, const SmallDev &s, hipStream_t st);
 // pool growth: live keys to their new regions (new offsets noff[nsg])
 void launch_small_regrow(const Dev &d, const SmallDev &s, const int64_t *noff, uint32_t *npool, hipStream_t st);

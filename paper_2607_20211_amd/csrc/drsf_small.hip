@@ -9,7 +9,18 @@
 // (a separate branch of the captured update); results are staged and
 // written into parent/label by a commit kernel after both branches end,
 // since the chain's per-vertex kernels read the parents of every vertex in
-// the blocks they visit.
+// the blocks they visit.  Where every graph is small no chain runs, and the
+// workgroup writes them itself.  The queue holds the larger graphs first, so
+// that none of them is begun last.
+//
+// Bound by the block barriers and LDS latencies of the larger graphs: a step
+// has few edges per thread, so passes need one barrier each, a thread has
+// several loads in flight, the rounds run over the pieces instead of the
+// vertices, and the update's counters are added up per workgroup.  1024 graphs
+// of 100 to 3157 vertices, half inserting and half deleting 10 to 1000 edges:
+// 128 us and 11 for the commit before, 63 us now; a graph of 3157 vertices and
+// 12607 edges took 102 us and takes 47 (15 in the pass over its edges, 11 in
+// the rounds, 6 for the pieces).
 //
 // A small graph keeps its edges as an array of 32-bit keys (u << 16 | v,
 // u < v, local ids; n <= 16384, so bit 31 is free) in no particular order,
@@ -24,7 +35,9 @@
 //      over the edge array that also drops the deleted keys — a rejected
 //      batch changes nothing;
 //   3. deletes: cut (parent[c] = c for the child end of a deleted tree edge);
-//   4. pieces: roots of F-hat by pointer jumping in LDS;
+//   4. pieces: roots of F-hat by pointer jumping in LDS (before an insert the
+//      labels are the roots), and a list of them; a delete that cut no tree
+//      edge is done, and so is an insert that found no cross edge in 5;
 //   5-6. replacement edges: Boruvka rounds over components with LDS atomic
 //      minima of the edge keys (lowest key leaving each component; a mutual
 //      pair is recorded once), hooks applied after every selection, then
@@ -48,8 +61,7 @@ namespace drsf {
 namespace {
 
 constexpr uint32_t SK_INF = 0xffffffffu;
-constexpr int MAX_WAVES = 16;  // up to 1024 threads per workgroup
-constexpr int UNROLL = 8;      // edge-array loads a thread keeps in flight
+constexpr int UNROLL = 4;      // edge-array loads a thread keeps in flight
 constexpr int ER_REGS = 4;     // replacement edges a thread holds in registers during the level search
 
 __device__ __forceinline__ int nthreads() { return (int)blockDim.x; }
@@ -65,44 +77,61 @@ __host__ __device__ constexpr size_t lds_bytes_for(int T) { return 6 * (size_t)(
 
 struct Shared {
     int32_t err;  // a bound was exceeded (corrupt forest): the update fails
-    uint32_t wsum[MAX_WAVES];
     int32_t task;
     int32_t flag;
-    uint32_t word[4];
+    int32_t level[4];
+    uint32_t word[4];            // keys kept, live edges, edges chosen, pieces
+    int32_t cut;                 // a tree edge was deleted
+    uint32_t paths;
+    unsigned long long sum[3];   // of the workgroup's tasks: chosen edges, paths, cross edges
 };
-
-// Exclusive sum of one count per thread over the block, in thread order;
-// every thread calls it.  *total = the sum of all counts.
-__device__ uint32_t block_excl_sum(uint32_t x, Shared &sh, uint32_t *total) {
-    const int w = threadIdx.x / WAVE, nw = nthreads() / WAVE;
-    uint32_t inc = x;
-    for (int of = 1; of < WAVE; of <<= 1) {
-        const uint32_t y = __shfl_up(inc, of);
-        if (lane_id() >= of) inc += y;
-    }
-    if (lane_id() == WAVE - 1) sh.wsum[w] = inc;
-    __syncthreads();
-    uint32_t before = 0, tot = 0;
-    for (int q = 0; q < nw; q++) {
-        const uint32_t c = sh.wsum[q];
-        before += q < w ? c : 0;
-        tot += c;
-    }
-    __syncthreads();
-    *total = tot;
-    return before + inc - x;
-}
 
 // Appends the keys of this wave's lanes that have `keep` set to out at
 // positions claimed from the counter *cnt (one LDS atomic per wave), in no
 // particular order.
-__device__ __forceinline__ void wave_append(bool keep, uint32_t k, uint32_t *out, uint32_t *cnt) {
+template <class T>
+__device__ __forceinline__ void wave_append(bool keep, T k, T *out, uint32_t *cnt) {
     const uint64_t m = __ballot(keep);
     if (m == 0) return;
     uint32_t base = 0;
     if (lane_id() == 0) base = atomicAdd(cnt, (uint32_t)__popcll(m));
     base = __shfl(base, 0);
     if (keep) out[base + lanes_below(m)] = k;
+}
+
+// The same for N keys of every lane, with one LDS atomic for all of them.
+template <int N>
+__device__ __forceinline__ void wave_append(const bool (&keep)[N], const uint32_t (&k)[N], uint32_t *out,
+                                            uint32_t *cnt) {
+    uint64_t m[N];
+    uint32_t total = 0;
+#pragma unroll
+    for (int r = 0; r < N; r++) {
+        m[r] = __ballot(keep[r]);
+        total += (uint32_t)__popcll(m[r]);
+    }
+    if (total == 0) return;
+    uint32_t base = 0;
+    if (lane_id() == 0) base = atomicAdd(cnt, total);
+    base = __shfl(base, 0);
+#pragma unroll
+    for (int r = 0; r < N; r++) {
+        if (keep[r]) out[base + lanes_below(m[r])] = k[r];
+        base += (uint32_t)__popcll(m[r]);
+    }
+}
+
+// X[v] = src[v] - o for n vertices, UNROLL loads of a thread in flight
+__device__ __forceinline__ void load_local(int16_t *X, const int32_t *src, int32_t o, int n) {
+    const int nt = nthreads();
+    for (int v0 = threadIdx.x; v0 < n; v0 += nt * UNROLL) {
+        int32_t x[UNROLL];
+#pragma unroll
+        for (int r = 0; r < UNROLL; r++) x[r] = src[v0 + r * nt < n ? v0 + r * nt : v0];
+#pragma unroll
+        for (int r = 0; r < UNROLL; r++)
+            if (v0 + r * nt < n) X[v0 + r * nt] = (int16_t)(x[r] - o);
+    }
 }
 
 // Hash set of edge keys by open addressing over nch chunks of 4 slots
@@ -155,37 +184,40 @@ __device__ __forceinline__ int hs_find(const uint32_t *tab, uint32_t nch, uint32
     return at;
 }
 
-// Pointer jumping on X[0, n) until every entry is a root (X[X[v]] == X[v]);
-// a forest needs at most log2(n) + 1 rounds, so 40 bound it.
+// Pointer jumping on X[0, n) until every entry is a root (X[X[v]] == X[v]).
+// Only v's thread writes X[v], and any ancestor read meanwhile will do, so a
+// thread goes on until its own entries are done, with no barrier in between;
+// each turn takes an entry at least one step up, so n turns bound it.
 __device__ void jump_all(int16_t *X, int n, Shared &sh) {
-    for (int round = 0;; round++) {
-        if (round == 40) {
-            if (threadIdx.x == 0) sh.err = 1;
-            __syncthreads();
-            break;
-        }
-        if (threadIdx.x == 0) sh.flag = 0;
-        __syncthreads();
-        bool changed = false;
-        for (int v = threadIdx.x; v < n; v += nthreads()) {
-            const int16_t x = X[v], y = X[x];
-            if (x != y) {
-                X[v] = y;
-                changed = true;
+    constexpr int K = 4;  // entries a thread has in flight
+    for (int v0 = threadIdx.x; v0 < n; v0 += K * nthreads()) {
+        for (int turn = 0;; turn++) {
+            int16_t x[K], y[K];
+#pragma unroll
+            for (int k = 0; k < K; k++) x[k] = v0 + k * nthreads() < n ? X[v0 + k * nthreads()] : (int16_t)0;
+#pragma unroll
+            for (int k = 0; k < K; k++) y[k] = X[x[k]];
+            bool changed = false;
+#pragma unroll
+            for (int k = 0; k < K; k++)
+                if (v0 + k * nthreads() < n && x[k] != y[k]) {
+                    X[v0 + k * nthreads()] = y[k];
+                    changed = true;
+                }
+            if (!changed) break;
+            if (turn > n) {
+                sh.err = 1;
+                break;
             }
         }
-        if (changed) sh.flag = 1;
-        __syncthreads();
-        const int f = sh.flag;
-        __syncthreads();
-        if (!f) break;
     }
+    __syncthreads();
 }
 
 // One graph's update (see the file comment).  Every thread of the block
 // calls it.  tab_lds: 16-byte aligned LDS after P (lds_chunks chunks of 4
-// words), free until step 4; t: the task's position in the queue.
-__device__ void small_task(const Dev &d, const SmallDev &s, const int t, const int4 tk, Shared &sh, int16_t *P,
+// words), free until step 4; alone: the results go straight into the context.
+__device__ void small_task(const Dev &d, const SmallDev &s, const bool alone, const int4 tk, Shared &sh, int16_t *P,
                            int16_t *C, int16_t *H, uint32_t *B, uint32_t *tab_lds, uint32_t lds_chunks) {
     const int sidx = tk.x, op = tk.w;
     const int64_t bstart = tk.y;
@@ -206,12 +238,18 @@ __device__ void small_task(const Dev &d, const SmallDev &s, const int t, const i
     const int32_t *be = hc->edges ? hc->edges : d.bedges;
     uint32_t *ka = s.bkeys + bstart;
 
-    // 1. parents, batch keys, range checks
-    for (int v = threadIdx.x; v < n; v += nt) P[v] = (int16_t)(d.parent[o + v] - o);
+    // 1. parents (of an insert later, if it needs them), batch keys, range
+    // checks
+    if (op == 1) load_local(P, d.parent + o, o, n);
     if (threadIdx.x == 0) {
         sh.flag = 0;
         sh.err = 0;
-        sh.word[0] = 0;
+        sh.cut = 0;
+        sh.paths = 0;
+    }
+    if (threadIdx.x < 4) {
+        sh.word[threadIdx.x] = 0;
+        sh.level[threadIdx.x] = 0;
     }
     __syncthreads();
     int bad = 0;
@@ -248,17 +286,18 @@ __device__ void small_task(const Dev &d, const SmallDev &s, const int t, const i
             uint32_t kk[UNROLL];  // loads issued together, then used
 #pragma unroll
             for (int r = 0; r < UNROLL; r++) kk[r] = j0 + r * nt < m ? E[j0 + r * nt] : HS_EMPTY;
+            bool keep[UNROLL];
 #pragma unroll
             for (int r = 0; r < UNROLL; r++) {
                 const bool in = j0 + r * nt < m;
                 const int at = in ? hs_find(tab, nch, kk[r]) : -1;
-                if (op == 0) {
-                    if (at >= 0) bad2 |= ST_EXISTS;
-                } else {
-                    if (at >= 0) atomicOr(&tab[at], HS_FOUND);
-                    wave_append(in && at < 0, kk[r], E2, &sh.word[0]);
+                keep[r] = in && at < 0;
+                if (at >= 0) {
+                    if (op == 0) bad2 |= ST_EXISTS;
+                    else atomicOr(&tab[at], HS_FOUND);
                 }
             }
+            if (op == 1) wave_append(keep, kk, E2, &sh.word[0]);
         }
         if (bad2) atomicOr(&sh.flag, bad2);
         __syncthreads();
@@ -275,9 +314,9 @@ __device__ void small_task(const Dev &d, const SmallDev &s, const int t, const i
     if (sh.flag == 0 && blen > 0) {
         if (2 * (int64_t)blen <= 4 * (int64_t)lds_chunks) {
             validate(tab_lds, lds_chunks);
-        } else {  // words [2 bstart + 4 t, 2 (bstart + blen) + 4 (t + 1)) are the task's: tasks come in batch order
-            const int64_t w0 = (2 * bstart + 4 * (int64_t)t + 3) & ~(int64_t)3;  // 16-byte aligned
-            validate(s.htab + w0, (uint32_t)((2 * (bstart + blen) + 4 * ((int64_t)t + 1) - w0) / 4));
+        } else {  // words [2 bstart + 4 sidx, 2 (bstart + blen) + 4 (sidx + 1)) are the graph's: indexes go in batch order
+            const int64_t w0 = (2 * bstart + 4 * (int64_t)sidx + 3) & ~(int64_t)3;  // 16-byte aligned
+            validate(s.htab + w0, (uint32_t)((2 * (bstart + blen) + 4 * ((int64_t)sidx + 1) - w0) / 4));
         }
     }
     const int status = sh.flag;
@@ -307,128 +346,203 @@ __device__ void small_task(const Dev &d, const SmallDev &s, const int t, const i
 
     // 3. cut the deleted tree edges
     if (op == 1) {
+        bool cut = false;
         for (int i = threadIdx.x; i < blen; i += nt) {
             const int32_t u = sk_lo(ka[i]), v = sk_hi(ka[i]);
-            if (P[u] == v) P[u] = (int16_t)u;
-            else if (P[v] == u) P[v] = (int16_t)v;
+            if (P[u] == v) {
+                P[u] = (int16_t)u;
+                cut = true;
+            } else if (P[v] == u) {
+                P[v] = (int16_t)v;
+                cut = true;
+            }
         }
+        if (cut) sh.cut = 1;
+        __syncthreads();
     }
-    __syncthreads();
 
-    // 4. pieces: C = root of each vertex in F-hat
-    for (int v = threadIdx.x; v < n; v += nt) C[v] = P[v];
-    __syncthreads();
-    jump_all(C, n, sh);
-
-    // 5-6. replacement edges: Boruvka rounds (C holds component links,
-    // every entry a root at the start of a round; piece roots are the
-    // initial components).  A round reads list L, keeps the edges whose
-    // ends lie in different components (appended to `out`, the next
-    // round's L) and takes each component's lowest such key.
+    // 4. pieces: C = root of each vertex in F-hat (before an insert that is
+    // its label), R the roots in any order
+    int32_t *R = s.spar + vo;  // free until the results are staged
+    int32_t c0 = 0;            // this thread's first piece
+    int np = 0;
     uint32_t ner = 0, nx = 0;
+    if (op == 0 || sh.cut) {
+        const int nr = (n + nt - 1) / nt * nt;  // whole block rounds: the waves append together
+        if (op == 0) {
+            load_local(C, d.label + o, o, n);
+            __syncthreads();
+        } else {
+            for (int v = threadIdx.x; v < n; v += nt) C[v] = P[v];
+            __syncthreads();
+            jump_all(C, n, sh);
+        }
+        for (int v = threadIdx.x; v < nr; v += nt) {
+            const bool root = v < n && C[v] == v;
+            if (root) {
+                H[v] = (int16_t)v;
+                B[v] = SK_INF;
+            }
+            wave_append(root, v, R, &sh.word[3]);
+        }
+        __syncthreads();
+        np = (int)sh.word[3];
+        if ((int)threadIdx.x < np) c0 = R[threadIdx.x];
+    }
+    auto piece = [&](int i) { return i < nt ? c0 : R[i]; };
+
+    // 5-6. replacement edges: Boruvka rounds over the pieces (H holds
+    // component links, every piece's entry a root at the start of a round).
+    // A round reads list L, keeps the edges whose ends lie in different
+    // components (appended to `out`, the next round's L) and takes each
+    // component's lowest such key.
     const uint32_t *L = op == 0 ? ka : (flip ? E2 : E);
     int live = op == 0 ? blen : m2;
     uint32_t *out = X, *spare = Y;
-    for (int round = 0;; round++) {
-        // each round at least halves the components with a live edge; err is
-        // read by every thread before any can set it again
-        const int e = sh.err;
-        __syncthreads();
-        if (round == 40 || e) {
-            if (threadIdx.x == 0) sh.err = 1;
-            break;
-        }
-        for (int v = threadIdx.x; v < n; v += nt) B[v] = SK_INF;
-        if (threadIdx.x == 0) sh.word[1] = 0;
-        __syncthreads();
+    int32_t *TO = s.slab + vo;  // hooks of pieces beyond a thread's first (free until the labels are staged)
+    int32_t to0 = 0;
+    const int npr = (np + nt - 1) / nt * nt;
+    for (int round = 0; np > 0; round++) {
         const int span = nt * UNROLL;
         const int lr = (live + span - 1) / span * span;
         for (int j0 = threadIdx.x; j0 < lr; j0 += span) {
             uint32_t kk[UNROLL];
 #pragma unroll
             for (int r = 0; r < UNROLL; r++) kk[r] = j0 + r * nt < live ? L[j0 + r * nt] : 0u;
+            int32_t cu[UNROLL], cv[UNROLL];
 #pragma unroll
             for (int r = 0; r < UNROLL; r++) {
-                const uint32_t k = kk[r];
-                const int32_t cu = C[sk_lo(k)], cv = C[sk_hi(k)];
-                const bool keep = j0 + r * nt < live && cu != cv;
-                if (keep) {
-                    atomicMin(&B[cu], k);
-                    atomicMin(&B[cv], k);
-                }
-                wave_append(keep, k, out, &sh.word[1]);
+                cu[r] = C[sk_lo(kk[r])];
+                cv[r] = C[sk_hi(kk[r])];
             }
+            bool keep[UNROLL];
+            if (round > 0) {
+#pragma unroll
+                for (int r = 0; r < UNROLL; r++) {
+                    cu[r] = H[cu[r]];
+                    cv[r] = H[cv[r]];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < UNROLL; r++) {
+                keep[r] = j0 + r * nt < live && cu[r] != cv[r];
+                if (keep[r]) {
+                    atomicMin(&B[cu[r]], kk[r]);
+                    atomicMin(&B[cv[r]], kk[r]);
+                }
+            }
+            wave_append(keep, kk, out, &sh.word[1]);
         }
         __syncthreads();
         live = (int)sh.word[1];
         if (round == 0) nx = (uint32_t)live;
-        // select: H[c] = component c hooks onto (or c); record each chosen edge once
-        uint32_t got = 0;
-        for (int c = threadIdx.x; c < n; c += nt) {
-            H[c] = (int16_t)c;
-            const uint32_t k = B[c];
-            if (k == SK_INF || C[c] != c) continue;
-            const int32_t cx = C[sk_lo(k)], cy = C[sk_hi(k)];
-            const int32_t other = cx == c ? cy : cx;
-            const bool mutual = B[other] == k;
-            if (!mutual || c > other) H[c] = (int16_t)other;
-            if (!mutual || c < other) got++;
-        }
-        // ranks of this thread's recorded edges: record them in a second pass
-        uint32_t tot;
-        uint32_t before = block_excl_sum(got, sh, &tot);
-        for (int c = threadIdx.x; c < n; c += nt) {
-            const uint32_t k = B[c];
-            if (k == SK_INF || C[c] != c) continue;
-            const int32_t cx = C[sk_lo(k)], cy = C[sk_hi(k)];
-            const int32_t other = cx == c ? cy : cx;
-            if (!(B[other] == k) || c < other) ER[ner + before++] = make_int2(sk_lo(k), sk_hi(k));
+        // select: the component that c hooks onto (or c); each chosen edge is
+        // recorded once (in any order: they form a forest)
+        for (int i = threadIdx.x; i < npr; i += nt) {
+            bool mine = false;
+            uint32_t k = SK_INF;
+            if (i < np) {
+                const int32_t c = piece(i);
+                int32_t to = c;
+                k = B[c];
+                if (k != SK_INF && H[c] == c) {
+                    const int32_t cx = H[C[sk_lo(k)]], cy = H[C[sk_hi(k)]];
+                    const int32_t other = cx == c ? cy : cx;
+                    const bool mutual = B[other] == k;
+                    if (!mutual || c > other) to = other;
+                    mine = !mutual || c < other;
+                }
+                if (i < nt) to0 = to;
+                else TO[i] = to;
+            }
+            wave_append(mine, make_int2(sk_lo(k), sk_hi(k)), ER, &sh.word[2]);
         }
         __syncthreads();
-        if (tot == 0) break;
+        const uint32_t tot = sh.word[2] - ner;
+        if (tot == 0 || sh.err) break;  // the same for every thread: err is set before a barrier only
+        if (round == 40) {  // each round at least halves the components with a live edge
+            __syncthreads();
+            if (threadIdx.x == 0) sh.err = 1;
+            break;
+        }
         ner += tot;
-        for (int c = threadIdx.x; c < n; c += nt)
-            if (H[c] != c) C[c] = H[c];
+        for (int i = threadIdx.x; i < np; i += nt) {
+            const int32_t c = piece(i), to = i < nt ? to0 : TO[i];
+            if (to != c) H[c] = (int16_t)to;
+            B[c] = SK_INF;
+        }
+        if (threadIdx.x == 0) sh.word[1] = 0;
         __syncthreads();
-        jump_all(C, n, sh);
+        // links to the new roots, as in jump_all
+        for (int i = threadIdx.x; i < np; i += nt) {
+            const int32_t c = piece(i);
+            int32_t x = H[c];
+            for (int turn = 0;; turn++) {
+                const int32_t y = H[x];
+                if (x == y) break;
+                H[c] = (int16_t)y;
+                x = y;
+                if (turn > n) {
+                    sh.err = 1;
+                    break;
+                }
+            }
+        }
+        __syncthreads();
         L = out;
         out = spare;
         spare = const_cast<uint32_t *>(L);
     }
-
-    // 7. labels: smallest vertex of each final component (B[root])
-    for (int v = threadIdx.x; v < n; v += nt) B[v] = SK_INF;
     __syncthreads();
-    for (int v = threadIdx.x; v < n; v += nt) atomicMin(&B[C[v]], (uint32_t)v);
-    __syncthreads();
-    for (int v = threadIdx.x; v < n; v += nt) s.slab[vo + v] = (int32_t)B[C[v]] + o;
-
-    // 8. orientation, all in LDS.  H = piece root of each vertex (F-hat,
-    // unchanged by the hooking); a super-root piece (the piece holding its
-    // component's smallest vertex) is marked by H[root] = -root - 1.  Then B
-    // and C, no longer needed (the labels are staged), hold each piece
-    // root's search level and the replacement edge it was reached through.
-    for (int v = threadIdx.x; v < n; v += nt) H[v] = P[v];
-    __syncthreads();
-    jump_all(H, n, sh);
-    for (int v = threadIdx.x; v < n; v += nt)
-        if (C[v] == v) {  // a final component: its smallest vertex is B[v]
-            const int32_t sr = H[B[v]];
-            H[sr] = (int16_t)(-sr - 1);
+    // a forest that neither lost nor gained an edge stays as it is
+    const bool same = ner == 0 && !sh.cut && !sh.err;
+    if (same) {
+        __syncthreads();  // the flags are read
+        if (threadIdx.x == 0) {
+            s.sok[sidx] = 0;  // nothing to commit
+            s.sm[sidx] = m2;
+            s.sbuf[sidx] = flip ? 1 - cur : cur;
+            sh.sum[2] += nx;
         }
+        __syncthreads();
+        return;
+    }
+
+    // 7. labels: smallest vertex of each final component (B[root]); the first
+    // lane of a wave speaks for those with its component
+    if (op == 0) load_local(P, d.parent + o, o, n);
+    for (int i = threadIdx.x; i < np; i += nt) B[piece(i)] = SK_INF;
+    __syncthreads();
+    for (int v = threadIdx.x; v < (n + nt - 1) / nt * nt; v += nt) {
+        const int32_t root = v < n ? H[C[v]] : -1;
+        const int32_t first = __shfl(root, 0);
+        if (root >= 0 && (root != first || lane_id() == 0)) atomicMin(&B[root], (uint32_t)v);
+    }
+    __syncthreads();
+    for (int v = threadIdx.x; v < n; v += nt) s.slab[vo + v] = (int32_t)B[H[C[v]]] + o;
+    __syncthreads();
+
+    // 8. orientation, all in LDS.  A super-root piece (the piece holding its
+    // component's smallest vertex) is marked in H.  Then B and H, no longer
+    // needed (the labels are staged), hold each piece's search level and the
+    // replacement edge it was reached through.
+    for (int i = threadIdx.x; i < np; i += nt) {
+        const int32_t c = piece(i);
+        if (H[c] == c) H[C[B[c]]] = -1;  // a final component: only its own root tests true
+    }
     __syncthreads();
     int32_t *LV = reinterpret_cast<int32_t *>(B);
-    int16_t *PE = C;
-    for (int v = threadIdx.x; v < n; v += nt) LV[v] = H[v] < 0 ? 0 : -1;
+    int16_t *PE = H;
+    for (int i = threadIdx.x; i < np; i += nt) {
+        const int32_t c = piece(i);
+        LV[c] = H[c] == -1 ? 0 : -1;
+    }
     __syncthreads();
     // the piece pair of each of this thread's first ER_REGS replacement
     // edges, held in registers across the levels (0: used up)
     auto piece_pair = [&](int e) {
         const int2 xy = ER[e];
-        int32_t pa = H[xy.x], pb = H[xy.y];
-        if (pa < 0) pa = -pa - 1;
-        if (pb < 0) pb = -pb - 1;
-        return ((uint32_t)pa << 16) | (uint32_t)pb | 0x80000000u;
+        return ((uint32_t)C[xy.x] << 16) | (uint32_t)C[xy.y] | 0x80000000u;
     };
     uint32_t pp[ER_REGS];
 #pragma unroll
@@ -454,8 +568,9 @@ __device__ void small_task(const Dev &d, const SmallDev &s, const int t, const i
         return false;
     };
     for (int lvl = 0; lvl <= n; lvl++) {  // a super-tree has fewer levels than vertices
-        if (threadIdx.x == 0) sh.flag = 0;
-        __syncthreads();
+        // one barrier a level: the flag of the level after the next is
+        // cleared here, two barriers after it was last read
+        if (threadIdx.x == 0) sh.level[(lvl + 2) & 3] = 0;
         bool any = false;
 #pragma unroll
         for (int r = 0; r < ER_REGS; r++)
@@ -465,24 +580,23 @@ __device__ void small_task(const Dev &d, const SmallDev &s, const int t, const i
             }
         for (int e = threadIdx.x + ER_REGS * nt; e < (int)ner; e += nt)
             if (visit(piece_pair(e), e, lvl)) any = true;
-        if (any) sh.flag = 1;
+        if (any) sh.level[lvl & 3] = 1;
         __syncthreads();
-        const int f = sh.flag;
-        __syncthreads();
-        if (!f) break;
+        if (!sh.level[lvl & 3]) break;
     }
+    __syncthreads();
     // reversals: one thread per attached piece, plus the re-rooting of each
     // super-root piece whose root is not its component's smallest vertex
     uint32_t npaths = 0;
-    for (int v = threadIdx.x; v < n; v += nt) {
-        if (H[v] != v && H[v] != -v - 1) continue;  // v is a piece root
+    for (int i = threadIdx.x; i < np; i += nt) {
+        const int32_t v = piece(i);
         int32_t start, newpar;
         if (LV[v] > 0) {
             const int32_t pe = PE[v];
             const int2 xy = ER[pe >= 0 ? pe : -pe - 1];
             start = pe >= 0 ? xy.y : xy.x;
             newpar = pe >= 0 ? xy.x : xy.y;
-        } else if (H[v] < 0) {  // super-root piece: re-rooted at the component's smallest vertex
+        } else if (LV[v] == 0) {  // super-root piece: re-rooted at the component's smallest vertex
             start = s.slab[vo + v] - o;
             if (start == v) continue;
             newpar = start;
@@ -503,6 +617,7 @@ __device__ void small_task(const Dev &d, const SmallDev &s, const int t, const i
             x = nx2;
         }
     }
+    if (npaths) atomicAdd(&sh.paths, npaths);
     __syncthreads();
     if (sh.err) {  // a corrupt forest: the update fails (the graph is not committed)
         if (threadIdx.x == 0) {
@@ -512,21 +627,32 @@ __device__ void small_task(const Dev &d, const SmallDev &s, const int t, const i
         __syncthreads();
         return;
     }
-    for (int v = threadIdx.x; v < n; v += nt) s.spar[vo + v] = (int32_t)P[v] + o;
-    // counters of the update (all graphs of the context add up)
-    // (own counters: the chain running beside uses C_NER and C_NR as list lengths)
-    if (npaths) atomicAdd(&d.cnt[C_SNR], (unsigned long long)npaths);
+    if (alone) {
+        for (int v = threadIdx.x; v < n; v += nt) {
+            const int32_t lab = s.slab[vo + v];
+            d.parent[o + v] = (int32_t)P[v] + o;
+            d.label[o + v] = lab;
+            d.rep[o + v] = lab;
+        }
+    } else {
+        for (int v = threadIdx.x; v < n; v += nt) s.spar[vo + v] = (int32_t)P[v] + o;
+    }
     if (threadIdx.x == 0) {
         s.sok[sidx] = 1;
         s.sm[sidx] = m2;
         s.sbuf[sidx] = flip ? 1 - cur : cur;
-        atomicAdd(&d.cnt[C_SNER], (unsigned long long)ner);
-        atomicAdd(&d.cnt[C_SNCROSS], (unsigned long long)nx);
+        sh.sum[0] += ner;
+        sh.sum[1] += sh.paths;
+        sh.sum[2] += nx;
     }
     __syncthreads();
 }
 
-__global__ __launch_bounds__(1024) void k_small_update(Dev d, SmallDev s) {
+// alone: every graph of the context is small, so no kernel sequence runs: this
+// kernel also publishes the update's control block, clears the batch's
+// hash-slot marks and marks the update finished, as the sequence's kernels
+// would, for the cleanup.
+__global__ __launch_bounds__(1024) void k_small_update(Dev d, SmallDev s, int alone) {
     extern __shared__ unsigned char smem[];
     __shared__ Shared sh;
     const int T = s.T;
@@ -538,34 +664,40 @@ __global__ __launch_bounds__(1024) void k_small_update(Dev d, SmallDev s) {
     const size_t tab0 = (2 * (size_t)T + 15) & ~(size_t)15;
     uint32_t *tab = reinterpret_cast<uint32_t *>(smem + tab0);
     const uint32_t tab_chunks = (uint32_t)((lds_bytes_for(T) - tab0) / 16);
-    const int ntask = d.hctl->nsmall;
-    while (true) {
-        if (threadIdx.x == 0) sh.task = (int32_t)atomicAdd(s.qhead, 1u);
+    const Ctl *hc = d.hctl;
+    const int ntask = hc->nsmall;
+    if (alone) {
+        if (blockIdx.x == 0 && threadIdx.x < sizeof(Ctl) / 8)
+            reinterpret_cast<uint64_t *>(d.ctlw)[threadIdx.x] = reinterpret_cast<const uint64_t *>(hc)[threadIdx.x];
+        if (blockIdx.x == 0 && threadIdx.x == 0) d.cnt[C_ORIENTED] = 1;
+        for (int64_t i = (int64_t)blockIdx.x * nthreads() + threadIdx.x; i < hc->b; i += (int64_t)gridDim.x * nthreads())
+            d.bslot[i] = NONE;
+    }
+    if (threadIdx.x < 3) sh.sum[threadIdx.x] = 0;
+    // each workgroup's first task is its own, the queue holds the others
+    int t = blockIdx.x;
+    while (t < ntask) {
+        small_task(d, s, alone, s.tasks[t], sh, P, C, H, B, tab, tab_chunks);
+        if (threadIdx.x == 0) sh.task = (int32_t)(gridDim.x + atomicAdd(s.qhead, 1u));
         __syncthreads();
-        const int t = sh.task;
+        t = sh.task;
         __syncthreads();
-        if (t >= ntask) break;
-        small_task(d, s, t, s.tasks[t], sh, P, C, H, B, tab, tab_chunks);
+    }
+    // counters of the update, of all tasks at once (own counters: the chain
+    // running beside uses C_NER and C_NR as list lengths)
+    if (threadIdx.x < 3 && sh.sum[threadIdx.x])
+        atomicAdd(&d.cnt[threadIdx.x == 0 ? C_SNER : threadIdx.x == 1 ? C_SNR : C_SNCROSS], sh.sum[threadIdx.x]);
+    // the last workgroup out resets the queue for the next update
+    if (threadIdx.x == 0 && atomicAdd(&s.qhead[1], 1u) == gridDim.x - 1) {
+        atomicExch(&s.qhead[0], 0u);
+        atomicExch(&s.qhead[1], 0u);
     }
 }
 
 // After both branches: staged parents and labels of the updated small
-// graphs into the context's arrays (rep == label between updates), and the
-// work queue reset for the next update.  alone: every graph of the context
-// is small, so no kernel sequence ran: this kernel also publishes the
-// update's control block, clears the batch's hash-slot marks and marks the
-// update finished, as the sequence's kernels would, for the cleanup.
-__global__ __launch_bounds__(BLOCK) void k_small_commit(Dev d, SmallDev s, int alone) {
+// graphs into the context's arrays (rep == label between updates).
+__global__ __launch_bounds__(BLOCK) void k_small_commit(Dev d, SmallDev s) {
     const int ntask = d.hctl->nsmall;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *s.qhead = 0;
-    if (alone) {
-        const Ctl *hc = d.hctl;
-        if (blockIdx.x == 0 && threadIdx.x < sizeof(Ctl) / 8)
-            reinterpret_cast<uint64_t *>(d.ctlw)[threadIdx.x] = reinterpret_cast<const uint64_t *>(hc)[threadIdx.x];
-        if (blockIdx.x == 0 && threadIdx.x == 0) d.cnt[C_ORIENTED] = 1;
-        for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < hc->b; i += (int64_t)gridDim.x * BLOCK)
-            d.bslot[i] = NONE;
-    }
     for (int t = blockIdx.x; t < ntask; t += gridDim.x) {
         const int sidx = s.tasks[t].x;
         if (!s.sok[sidx]) continue;
@@ -632,12 +764,12 @@ int small_prepare(int T) {
                ? 0
                : -1;
 }
-int launch_small_update(const Dev &d, const SmallDev &s, int threads, int grid, hipStream_t st) {
-    hipLaunchKernelGGL(k_small_update, dim3(grid), dim3(threads), small_lds_bytes(s.T), st, d, s);
+int launch_small_update(const Dev &d, const SmallDev &s, int threads, int grid, bool alone, hipStream_t st) {
+    hipLaunchKernelGGL(k_small_update, dim3(grid), dim3(threads), small_lds_bytes(s.T), st, d, s, alone ? 1 : 0);
     return 0;
 }
-void launch_small_commit(const Dev &d, const SmallDev &s, int grid, bool alone, hipStream_t st) {
-    hipLaunchKernelGGL(k_small_commit, dim3(grid), dim3(BLOCK), 0, st, d, s, alone ? 1 : 0);
+void launch_small_commit(const Dev &d, const SmallDev &s, int grid, hipStream_t st) {
+    hipLaunchKernelGGL(k_small_commit, dim3(grid), dim3(BLOCK), 0, st, d, s);
 }
 void launch_small_regrow(const Dev &, const SmallDev &s, const int64_t *noff, uint32_t *npool, hipStream_t st) {
     hipLaunchKernelGGL(k_small_regrow, dim3(grid_for(s.nsg, 1, GRID_CAP)), dim3(BLOCK), 0, st, s, noff, npool);
