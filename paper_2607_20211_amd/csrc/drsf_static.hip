@@ -157,12 +157,14 @@ __device__ __forceinline__ void claim_vertex(Appender &app, bool take, const int
 // these kernels; three hooking rounds over every slot took 408 and the row of
 // every slot, which they read, 326.
 
-// A link only swaps roots, it does not shorten the path it walks.  Halving it
-// was slower (G(1e6, 5e6), first links: 117 us without, 552 from the ninth step
-// on): its stores race, so they have to be atomic ones.  By plain stores, two
-// XCDs that store one word in one launch can be left with L2 copies that differ
-// beyond its end; on a grid 2048 wide a few vertices, whose compression read
-// the copy of its own XCD, kept an ancestor as their label.
+// A link only swaps roots, it does not shorten the path it walks.  Several
+// threads halving one path store different ancestors into one word: a data
+// race, so the stores have to be atomic, and those were slower than longer walks
+// (G(1e6, 5e6), first links: 117 us without, 552 from the ninth step on).  Plain
+// stores are no choice: on a 2048 x 2048 grid 1 to 7 vertices of each call kept a
+// former ancestor as their label, with atomic stores or none no vertex did (how
+// the plain ones lead there is not known: a kernel of such stores alone, read
+// back from all XCDs, showed nothing).
 __device__ __forceinline__ void st_link(int32_t *comp, int32_t u, int32_t v) {
     int32_t a = comp[u], b = comp[v];
     while (a != b) {
