@@ -437,11 +437,12 @@ __global__ __launch_bounds__(BLOCK) void k_dedupe(Dev d) {
 // finding instead: rep <- parent over the listed vertex blocks, one wave per
 // block, four vertices per lane (16-byte accesses).  A cut child may be
 // copied before or after its cut; k_register then sets rep[c] = c.
+template <int NT>
 __device__ void rep_init(const Dev &d, int64_t nvl_list, int64_t bid, int64_t nblk) {
     typedef int v4i __attribute__((ext_vector_type(4)));
     const int64_t nb = (d.n + BLOCK - 1) / BLOCK;
     const int w = threadIdx.x / WAVE;
-    for (int64_t j = bid * (BLOCK / WAVE) + w;; j += nblk * (BLOCK / WAVE)) {
+    for (int64_t j = bid * (NT / WAVE) + w;; j += nblk * (NT / WAVE)) {
         const int64_t blk = list_block(d.vlist, nvl_list, j, nb);
         if (blk < 0) break;
         const int64_t v = blk * BLOCK + lane_id() * 4;
@@ -505,6 +506,7 @@ __device__ __forceinline__ void prepare_edges(const Dev &d, int64_t bid, int64_t
                 }
                 const int32_t la = d.label[key_lo(k)], lb = d.label[key_hi(k)];
                 if (la != lb) {
+                    d.bchild[i] = la;  // the later steps take an insert that joins trees from here
                     d.owner[la] = (int32_t)(2 * i);
                     d.owner[lb] = (int32_t)(2 * i + 1);
                 }
@@ -513,13 +515,14 @@ __device__ __forceinline__ void prepare_edges(const Dev &d, int64_t bid, int64_t
     }
 }
 
-__global__ __launch_bounds__(BLOCK) void k_prepare(Dev d, int gb) {
+template <int NT>
+__global__ __launch_bounds__(NT) void k_prepare(Dev d, int gb) {
     if (stopped(d)) return;
     if ((int)blockIdx.x >= gb) {
-        if (d.ctl->has_del) rep_init(d, d.ctl->nvl, (int64_t)blockIdx.x - gb, (int64_t)gridDim.x - gb);
+        if (d.ctl->has_del) rep_init<NT>(d, d.ctl->nvl, (int64_t)blockIdx.x - gb, (int64_t)gridDim.x - gb);
         return;
     }
-    prepare_edges<BLOCK>(d, blockIdx.x, gb);
+    prepare_edges<NT>(d, blockIdx.x, gb);
 }
 
 // The list's length and free positions after the update (one workgroup):
@@ -560,9 +563,11 @@ __device__ __forceinline__ void register_pieces(const Dev &d, int64_t bid, int64
                     d.rep[c] = c;  // the cut child roots its piece of F-hat
                 }
             } else {
-                const uint64_t k = d.bkey[i];
-                const int32_t la = d.label[key_lo(k)], lb = d.label[key_hi(k)];
-                if (la != lb) { a = la; c2 = lb; }
+                // inside one tree (most inserts into a graph with a large
+                // component): no gathers of labels (R-MAT 22, 1e6 inserts: 65 -> 62
+                // us here and 60 -> 45 in k_bor_round0, which does the same)
+                a = d.bchild[i];
+                if (a != NONE) c2 = d.label[key_hi(d.bkey[i])];
             }
         }
         const bool ga = a != NONE && d.owner[a] == (int32_t)(2 * i);
@@ -574,9 +579,10 @@ __device__ __forceinline__ void register_pieces(const Dev &d, int64_t bid, int64
     }
     if (bid == 0) settle_list<NT>(d);
 }
-__global__ __launch_bounds__(BLOCK) void k_register(Dev d) {
+template <int NT>
+__global__ __launch_bounds__(NT) void k_register(Dev d) {
     if (stopped(d)) return;
-    register_pieces<BLOCK>(d, blockIdx.x, gridDim.x);
+    register_pieces<NT>(d, blockIdx.x, gridDim.x);
 }
 
 // Live edges of each vertex: its entries in the store's two halves, less the
@@ -636,10 +642,12 @@ __device__ bool insert_emit_block(const Dev &d, int64_t t, Cross *e, int *total)
     uint64_t k = 0;
     int32_t la = 0, lb = 0;
     if (i < b && edge_op(d, i) == 0 && edge_ok(d, i)) {
-        k = d.bkey[i];
-        la = d.label[key_lo(k)];
-        lb = d.label[key_hi(k)];
-        cross = la != lb;
+        la = d.bchild[i];  // k_prepare's
+        cross = la != NONE;
+        if (cross) {
+            k = d.bkey[i];
+            lb = d.label[key_hi(k)];
+        }
     }
     const int off = block_excl_scan(cross ? 1 : 0, total);
     const int64_t reg = d.ctl->ibase + t;
@@ -1787,7 +1795,8 @@ __device__ __forceinline__ void hang_hooked(const Dev &d, int64_t slot, int32_t 
 // Distinct keys make the chosen edges a forest (Boruvka).  Round r >= 1 ends
 // the rounds when its select found no live edge.  Also clears the other
 // buffer of best[] for the next round's selection.
-__global__ __launch_bounds__(BLOCK) void k_bor_hook(Dev d, int r) {
+template <int NT>
+__global__ __launch_bounds__(NT) void k_bor_hook(Dev d, int r) {
     if (stopped(d) || d.cnt[C_DONE_BOR]) return;
     if (r >= 1) {
         const int64_t nout = (int64_t)d.cnt[(r & 1) ? C_NX1 : C_NX0];
@@ -1801,8 +1810,8 @@ __global__ __launch_bounds__(BLOCK) void k_bor_hook(Dev d, int r) {
     const bool walk = d.ctl->walk;
     const uint64_t *best = best_of(d, r);
     uint64_t *next = best_of(d, r + 1);
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < np; base += stride) {
+    const int64_t stride = (int64_t)gridDim.x * NT;
+    for (int64_t base = (int64_t)blockIdx.x * NT; base < np; base += stride) {
         const int64_t p = base + threadIdx.x;
         bool rec = false, from_x = false;
         int4 er = make_int4(0, 0, 0, 0);
@@ -1828,7 +1837,7 @@ __global__ __launch_bounds__(BLOCK) void k_bor_hook(Dev d, int r) {
                 }
             }
         }
-        const int64_t slot = block_append(rec ? 1 : 0, &d.cnt[C_NER]);
+        const int64_t slot = block_append<NT>(rec ? 1 : 0, &d.cnt[C_NER]);
         if (rec) {
             d.er[slot] = er;
             if (walk) hang_hooked(d, slot, er.z, er.w, from_x);
@@ -2060,18 +2069,19 @@ __device__ __forceinline__ void orient_piece(const Dev &d, int64_t p, int64_t np
 // piece's root and hangs that endpoint below a's other endpoint (Algorithm 1,
 // R and new parents).  A super-root piece whose root is not the component's
 // smallest vertex m is re-rooted at m; m is the component's new label.
-__global__ __launch_bounds__(BLOCK) void k_orient_bfs(Dev d, int levels) {
+template <int NT>
+__global__ __launch_bounds__(NT) void k_orient_bfs(Dev d, int levels) {
     if (stopped(d) || !d.cnt[C_DONE_BOR]) return;
     if (levels > 0 ? d.cnt[C_BFS_ROUND + levels - 1] != 0 : d.cnt[C_LONGTREE] != 0) return;
     const int64_t np = (int64_t)d.cnt[C_NP];
-    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    const int64_t stride = (int64_t)gridDim.x * NT;
     if (blockIdx.x == 0 && threadIdx.x == 0) d.cnt[C_ORIENTED] = 1;
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < np; base += stride) {
+    for (int64_t base = (int64_t)blockIdx.x * NT; base < np; base += stride) {
         const int64_t p = base + threadIdx.x;
         bool e1 = false, e2 = false;
         PathReq q1, q2;
         orient_piece(d, p, np, levels, &e1, &q1, &e2, &q2);
-        const int64_t s1 = block_append((e1 ? 1 : 0) + (e2 ? 1 : 0), &d.cnt[C_NR]);
+        const int64_t s1 = block_append<NT>((e1 ? 1 : 0) + (e2 ? 1 : 0), &d.cnt[C_NR]);
         const int64_t s2 = s1 + (e1 ? 1 : 0);
         if (e1) { if (s1 < d.pathcap) d.paths[s1] = q1; else atomicOr(d.status, ST_CAPACITY); }
         if (e2) { if (s2 < d.pathcap) d.paths[s2] = q2; else atomicOr(d.status, ST_CAPACITY); }
@@ -2952,13 +2962,33 @@ void launch_classify(const Dev &d, const Ctl *kc, hipStream_t s) {
 void launch_dedupe(const Dev &d, hipStream_t s) {
     hipLaunchKernelGGL(k_dedupe, dim3(grid_for(d.lb, BLOCK)), dim3(BLOCK), 0, s, d);
 }
+// Workgroups of the kernels that append to one counter of the update: of
+// WIDE_BLOCK threads from WIDE_BATCH entries on.  Each workgroup's atomic on
+// the counter waits for the others' (about 12 ns each), and wider workgroups
+// make fewer of them.  R-MAT 22, steps of 2 x 1e6 updates: 1263 us with
+// workgroups of 256 threads, 1162 of 512, 1168 of 1024 (k_register 62, 48, 46;
+// k_orient_bfs 22, 14, 12); of 2 x 1e5, where a workgroup's appends are few:
+// 363, 358 and 380.
+constexpr int WIDE_BLOCK = 512, WIDE_BATCH = 1 << 17;
+template <class F>
+void launch_wide(int64_t items, int cap, F f) {
+    if (items >= WIDE_BATCH)
+        f(std::integral_constant<int, WIDE_BLOCK>(), grid_for(items, WIDE_BLOCK, cap * BLOCK / WIDE_BLOCK));
+    else
+        f(std::integral_constant<int, BLOCK>(), grid_for(items, BLOCK, cap));
+}
 void launch_prepare(const Dev &d, bool del, hipStream_t s) {
-    const int gb = grid_for(d.lb, BLOCK);
-    const int gi = del ? grid_for(d.nvb, BLOCK / WAVE, COPY_CAP) : 0;
-    hipLaunchKernelGGL(k_prepare, dim3(gb + gi), dim3(BLOCK), 0, s, d, gb);
+    launch_wide(d.lb, GRID_CAP, [&](auto nt, int gb) {
+        constexpr int NT = decltype(nt)::value;
+        const int gi = del ? grid_for(d.nvb, NT / WAVE, COPY_CAP * BLOCK / NT) : 0;
+        hipLaunchKernelGGL((k_prepare<NT>), dim3(gb + gi), dim3(NT), 0, s, d, gb);
+    });
 }
 void launch_register(const Dev &d, hipStream_t s) {
-    hipLaunchKernelGGL(k_register, dim3(grid_for(d.lb, BLOCK)), dim3(BLOCK), 0, s, d);
+    launch_wide(d.lb, GRID_CAP, [&](auto nt, int g) {
+        constexpr int NT = decltype(nt)::value;
+        hipLaunchKernelGGL((k_register<NT>), dim3(g), dim3(NT), 0, s, d);
+    });
 }
 void launch_insert_emit(const Dev &d, hipStream_t s) {
     hipLaunchKernelGGL(k_insert_emit, dim3((unsigned)insert_regions(d.lb)), dim3(BLOCK), 0, s, d);
@@ -3007,14 +3037,17 @@ void launch_boruvka(const Dev &d, int r0, int r1, int64_t units, bool ins, hipSt
             hipLaunchKernelGGL(k_bor_select, dim3(r == 1 ? ge : gp), dim3(BLOCK), 0, s, d, r);
         else if (ins)
             hipLaunchKernelGGL(k_bor_round0, dim3(grid_for(d.lb, BLOCK, EMIT_CAP)), dim3(BLOCK), 0, s, d);
-        hipLaunchKernelGGL(k_bor_hook, dim3(gp), dim3(BLOCK), 0, s, d, r);
+        launch_bor_hook(d, r, s);
         if (r == 0 && !ins && d.lb >= FLAT_BATCH) hipLaunchKernelGGL(k_bor_flat, dim3(gp), dim3(BLOCK), 0, s, d);
     }
     // the tail reads a dense list, which rounds from 2 on have
     if (r1 >= 2 && r1 > r0) hipLaunchKernelGGL(k_bor_tail, dim3(1), dim3(TAIL_THREADS), 0, s, d, r1);
 }
 void launch_bor_hook(const Dev &d, int r, hipStream_t s) {
-    hipLaunchKernelGGL(k_bor_hook, dim3(grid_for(piece_bound(d), BLOCK, SMALL_CAP)), dim3(BLOCK), 0, s, d, r);
+    launch_wide(piece_bound(d), SMALL_CAP, [&](auto nt, int g) {
+        constexpr int NT = decltype(nt)::value;
+        hipLaunchKernelGGL((k_bor_hook<NT>), dim3(g), dim3(NT), 0, s, d, r);
+    });
 }
 void launch_solo_front(const Dev &d, const Ctl *kc, bool ins, int levels, hipStream_t s) {
     const Ctl none{};
@@ -3041,8 +3074,10 @@ void launch_sf_bfs(const Dev &d, int l0, int l1, hipStream_t s) {
 void launch_orient_bfs(const Dev &d, int levels, hipStream_t s) {
     if (levels == 0)
         hipLaunchKernelGGL(k_sf_reroot, dim3(grid_for(piece_bound(d), BLOCK, SMALL_CAP)), dim3(BLOCK), 0, s, d);
-    hipLaunchKernelGGL(k_orient_bfs, dim3(grid_for(piece_bound(d), BLOCK, SMALL_CAP)), dim3(BLOCK), 0, s, d,
-                       levels);
+    launch_wide(piece_bound(d), SMALL_CAP, [&](auto nt, int g) {
+        constexpr int NT = decltype(nt)::value;
+        hipLaunchKernelGGL((k_orient_bfs<NT>), dim3(g), dim3(NT), 0, s, d, levels);
+    });
 }
 void launch_superforest_lr(const Dev &d, int lr_rounds, int levels, hipStream_t s) {
     const int ga = grid_for(2 * d.ercap, BLOCK, SMALL_CAP);
@@ -3130,8 +3165,9 @@ int launch_et_reverse(const Dev &d, void *tmp, size_t tmp_bytes, hipStream_t s) 
 }
 void launch_cleanup(const Dev &d, hipStream_t s) {
     const int64_t m = std::max<int64_t>(piece_bound(d), d.lb);
-    // few workgroups: each arrives once on one counter (serialised atomics)
-    hipLaunchKernelGGL(k_cleanup, dim3(1 + grid_for(m, BLOCK, CLEANUP_CAP)), dim3(BLOCK), 0, s, d);
+    // few workgroups: each arrives once on one counter (serialised atomics);
+    // 1e6 entries: 27 us with 128, 19 with 256 or 512
+    hipLaunchKernelGGL(k_cleanup, dim3(1 + grid_for(m, BLOCK, m >= WIDE_BATCH ? 2 * CLEANUP_CAP : CLEANUP_CAP)), dim3(BLOCK), 0, s, d);
 }
 
 // ------------------------------------------------------ store rebuild

@@ -60,6 +60,17 @@ def test_chains_shortened_by_their_own_pieces(rows, cols, cuts):
     _run(g, [(dl, drsf.DRSF_DELETE), (dl, drsf.DRSF_INSERT), (dl[::2], drsf.DRSF_DELETE)])
 
 
+@pytest.mark.parametrize("b", [131071, 131072, 140001])
+def test_batches_around_the_wide_workgroups(b):
+    """Few edges per vertex, so that most entries cut or join trees."""
+    drsf = _lib()
+    _case(f"G(300000, 400000), batches of {b}")
+    g = gen.make_graph("gnm", 300000, gen.gnm(300000, 400000, gen.seed(86, 1, gen.P_GRAPH)))
+    cut = np.random.default_rng(b).choice(g.keys, b, replace=False)
+    pairs = np.stack([cut >> np.uint64(32), cut & np.uint64(0xffffffff)], 1).astype(np.int32)
+    _run(g, [(pairs, drsf.DRSF_DELETE), (pairs, drsf.DRSF_INSERT), (pairs[::-1], drsf.DRSF_DELETE)])
+
+
 @pytest.mark.parametrize("leaves", [700, 5000])
 def test_one_piece_that_every_edge_touches(leaves):
     """Inserts and deletes of a star's rays: all edges meet the centre's piece."""
