@@ -206,8 +206,7 @@ struct drsf_ctx {
     Ctl *ctl = nullptr;
     // pinned host staging
     int32_t *h_edges = nullptr;           // [2 max_batch]
-    int8_t *h_bop = nullptr;              // [max_batch]
-    int32_t *h_bgid = nullptr;            // [max_batch]
+    uint64_t *runs = nullptr, *h_runs = nullptr;  // [ngraph] several graphs: start << 8 | op of each one's batch
     int32_t *h_lists = nullptr;           // vlist | ilist | tlist
     // Two slots of control block and returned words: an update can be
     // queued while the one before it runs.  Queued updates alternate between
@@ -618,8 +617,6 @@ int alloc_state(drsf_ctx *c) {
     if ((rc = dalloc(c, &c->olist, n))) return rc;
     launch_fill_u64(c->wvol, orphan_words(c->nvb), 0, s);
     if ((rc = halloc(c, &c->h_edges, 2 * mb))) return rc;
-    if ((rc = halloc(c, &c->h_bop, mb))) return rc;
-    if ((rc = halloc(c, &c->h_bgid, mb))) return rc;
     if ((rc = halloc(c, &c->h_ctl_ring, 2))) return rc;
     select_slot(c, c->slot);
     launch_fill_i32(c->tidx, n, NONE, s);
@@ -650,7 +647,7 @@ void destroy_ctx(drsf_ctx *c) {
     drop_graphs(c);
     for (void *p : c->allocs) raw_dfree(c->opts, p);
     c->allocs.clear();
-    void *hosts[] = {c->h_edges, c->h_bop, c->h_bgid, c->h_lists, c->h_ctl_ring, c->h_ret_ring, c->h_stage};
+    void *hosts[] = {c->h_edges, c->h_runs, c->h_lists, c->h_ctl_ring, c->h_ret_ring, c->h_stage};
     for (void *p : hosts)
         if (p) (void)hipHostFree(p);
     for (auto &e : c->ev)
@@ -1639,6 +1636,7 @@ static int create_impl(int32_t G, const int32_t *n_off, int32_t n, const int64_t
     c->gstat = reinterpret_cast<int32_t *>(c->ctlmem + 1 + C_TOTAL);
     launch_fill_u64(c->ctlmem, c->ret_words, 0, c->stream);
     if ((rc = dalloc(c, &c->goff, (int64_t)G + 1))) return bail(rc);
+    if (n_off && ((rc = dalloc(c, &c->runs, G)) || (rc = halloc(c, &c->h_runs, G)))) return bail(rc);
     // every copy of create runs on the context's stream, after the work the
     // caller queued there (or, for a context-owned stream, on the null stream)
     if (hipMemcpyAsync(c->goff, c->goff_h.data(), sizeof(int32_t) * ((size_t)G + 1), hipMemcpyHostToDevice,
@@ -1936,8 +1934,9 @@ int drsf_multi_apply_async(drsf_ctx *c, const int32_t *edges, const int64_t *b_o
         keep_done(c, DRSF_OK);
         return DRSF_OK;
     }
-    // per-edge op and graph; vertex-block lists of the deleting and the
-    // inserting graphs and the base-store tiles of the deleting ones
+    // every graph's run of the batch (per-edge op and graph come from them on
+    // the device); vertex-block lists of the deleting and the inserting graphs
+    // and the base-store tiles of the deleting ones
     bool any_ins = false, any_del = false;
     int32_t nsmall = 0;
     // every graph small: the engine alone runs, which reads the tasks only
@@ -1946,12 +1945,7 @@ int drsf_multi_apply_async(drsf_ctx *c, const int32_t *edges, const int64_t *b_o
     for (int32_t g = 0; g < G; g++) {
         const int32_t k = c->nsg ? c->g2s[g] : -1;
         // op 2: the edge belongs to a small graph, whose own kernel takes it
-        const int8_t eo = k < 0 ? op[g] : (int8_t)2;
-        if (!alone)
-            for (int64_t i = b_off[g]; i < b_off[g + 1]; i++) {
-                c->h_bop[i] = eo;
-                c->h_bgid[i] = g;
-            }
+        c->h_runs[g] = (uint64_t)b_off[g] << 8 | (uint64_t)(k < 0 ? op[g] : 2);
         if (b_off[g + 1] == b_off[g]) continue;
         if (k < 0) (op[g] == DRSF_DELETE ? any_del : any_ins) = true;
     }
@@ -1992,8 +1986,8 @@ int drsf_multi_apply_async(drsf_ctx *c, const int32_t *edges, const int64_t *b_o
     if (nsmall)
         HIPCHK(c, hipMemcpyAsync(c->stasks, c->h_stasks, sizeof(int4) * (size_t)nsmall, hipMemcpyHostToDevice, s));
     if (!alone) {
-        HIPCHK(c, hipMemcpyAsync(c->bop, c->h_bop, (size_t)b, hipMemcpyHostToDevice, s));
-        HIPCHK(c, hipMemcpyAsync(c->bgid, c->h_bgid, sizeof(int32_t) * (size_t)b, hipMemcpyHostToDevice, s));
+        HIPCHK(c, hipMemcpyAsync(c->runs, c->h_runs, sizeof(uint64_t) * (size_t)G, hipMemcpyHostToDevice, s));
+        launch_batch_runs(b, G, c->runs, c->bop, c->bgid, s);
     }
     // a device batch is read in place, as drsf_apply's is
     if (!c->opts.inputs_on_device && (rc = stage_edges(c, edges, b, false))) return rc;

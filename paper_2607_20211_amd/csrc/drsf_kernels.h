@@ -341,6 +341,7 @@ void launch_key_edges(const Dev &d, int parts, hipStream_t s);
 // them (a delete's scans have made their selection)
 void launch_boruvka(const Dev &d, int r0, int r1, int64_t units, bool ins, hipStream_t s);
 void launch_bor_hook(const Dev &d, int r, hipStream_t s);
+void launch_batch_runs(int64_t b, int32_t G, const uint64_t *runs, int8_t *bop, int32_t *bgid, hipStream_t s);
 // small batches in one workgroup: up to the cut and the registration (an
 // insert: up to the orientation); and from an insert's cross edges, or a
 // delete's hooks of round r, to the orientation (levels 0: super-trees

@@ -381,6 +381,25 @@ __global__ __launch_bounds__(BLOCK) void k_classify(Dev d, Ctl kc, int from_arg)
     classify_edges(d, hd, (int64_t)blockIdx.x * BLOCK + threadIdx.x, (int64_t)gridDim.x * BLOCK);
 }
 
+// Graph and op of every entry of a batch for several graphs, from the graphs'
+// runs (first entry << 8 | op, ascending; graphs without entries share their
+// start with the next).  The host used to write both per entry and copy them:
+// 256 graphs, two calls of 131909 entries: 1140 us, now 1001.
+__global__ __launch_bounds__(BLOCK) void k_batch_runs(int64_t b, int32_t G, const uint64_t *runs, int8_t *bop,
+                                                      int32_t *bgid) {
+    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < b; i += stride) {
+        int32_t lo = 0, hi = G - 1;  // the last graph whose run starts at or before i
+        while (lo < hi) {
+            const int32_t mid = lo + ((hi - lo + 1) >> 1);
+            if ((int64_t)(runs[mid] >> 8) <= i) lo = mid;
+            else hi = mid - 1;
+        }
+        bop[i] = (int8_t)(runs[lo] & 0xff);
+        bgid[i] = lo;
+    }
+}
+
 // Repeated pairs inside the batch.  Equal keys hash to one slot and exactly
 // one of their stamps survives, so an edge that finds another edge's stamp
 // compares keys: equal is a repeat; different is a collision, and such edges
@@ -2958,6 +2977,9 @@ void launch_classify(const Dev &d, const Ctl *kc, hipStream_t s) {
     const Ctl none{};
     hipLaunchKernelGGL(k_classify, dim3(grid_for(d.lb, BLOCK)), dim3(BLOCK), 0, s, d, kc ? *kc : none,
                        kc ? 1 : 0);
+}
+void launch_batch_runs(int64_t b, int32_t G, const uint64_t *runs, int8_t *bop, int32_t *bgid, hipStream_t s) {
+    hipLaunchKernelGGL(k_batch_runs, dim3(grid_for(b, BLOCK)), dim3(BLOCK), 0, s, b, G, runs, bop, bgid);
 }
 void launch_dedupe(const Dev &d, hipStream_t s) {
     hipLaunchKernelGGL(k_dedupe, dim3(grid_for(d.lb, BLOCK)), dim3(BLOCK), 0, s, d);

@@ -90,3 +90,21 @@ def test_pieces_beyond_and_below_the_workgroup(kind, big, threads):
     ops = np.array([1, 0, 0, 1, 1, 1] + [1] * big, np.int8)
     pair.step([whole[0][::2], none, none, whole[3], whole[4][:900], whole[0][:1023:3]] + last, ops, "mixed")
     pair.gpu.close()
+
+
+@pytest.mark.parametrize("count", [1, 2, 257])
+def test_runs_of_many_graphs(count):
+    """Every entry finds its graph: one graph, empty runs at both ends and in a
+    row, no small-graph engine and with it."""
+    _case(f"runs of {count} graphs")
+    ns = [40 + 7 * (i % 50) for i in range(count)]
+    graphs = [gen.make_graph(f"g{i}", n, gen.gnm(n, 3 * n, i)) for i, n in enumerate(ns)]
+    for T in (0, 150):
+        pair = MultiPair(graphs, max_batch=1 << 15, small_graph_vertices=T)
+        for skip in (1, 3):
+            size = [0 if i % skip else 20 for i in range(count)]
+            size[0], size[-1] = (0, 0) if count > 2 else (size[0], size[-1])
+            cut = [_pairs(st[1])[:k] for st, k in zip(pair.state, size)]
+            pair.step(cut, np.ones(count, np.int8), "delete")
+            pair.step(cut, np.zeros(count, np.int8), "insert")
+        pair.gpu.close()
