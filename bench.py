@@ -59,7 +59,7 @@ def measured_traffic(kernel: str, workload: str):
     runs (profiles/*.counters.json), or None when the kernel's definition
     has changed since the counters were taken."""
     import glob
-    h = kernel_source_sha(kernel)
+    h = kernel_source_sha(kernel.split(" ")[0])
     for path in glob.glob(os.path.join(ROOT, "profiles", "*.counters.json")):
         c = json.load(open(path))
         if c.get("kernel") == kernel and c.get("workload") == workload and c.get("kernel_sha256_16") == h:
@@ -892,15 +892,15 @@ def main():
         "k_rep_chase": (pd["root_finding"] - ev_del, 12 * g.n + g.n // 8,
                         "root finding: read rep and label, write rep (4 B each per vertex), "
                         "orphan bitmap (1 bit per vertex)"),
-        "k_orph_scan": (pd["orphan_scan"] - ev_del,
+        "k_key_edges (orphans)": (pd["orphan_scan"] - ev_del,
                         int(4 * sd["orphan_slots"] + g.n // 8 + 40 * sd["num_orphans"]),
                         "orphan scan: 4-B column per adjacency slot, the orphan bitmap "
                         "(1 bit per vertex) once, one 40-B list entry per orphan (the piece of "
                         "orphan neighbours, read only for them, is not counted)"),
     }
     if sd["scan_orphans"] < 0.5:
-        kernels["k_sweep_base"] = (pd["store_sweep"] - ev_del, 4 * eb + 4 * (g.n + 1),
-                                   "store sweep: 4 B per stored edge slot + 4 B per row offset")
+        kernels["k_key_edges (store)"] = (pd["store_sweep"] - ev_del, 4 * eb + 4 * (g.n + 1),
+                                          "store sweep: 4 B per stored edge slot + 4 B per row offset")
     rooflines = {}
     for name, (ms, nbytes, what) in kernels.items():
         ach = nbytes / (ms * 1e-3) / 1e9 if ms > 0 else 0.0
@@ -914,8 +914,8 @@ def main():
     # per-launch medians beside the means (one heavy step can pull a mean up)
     med_del = {k: float(np.median([p[k] - p.get(drsf.EVENT_BRACKET, 0.0) for p in phases_del]))
                for k in phases_del[0]}
-    for name, ph in (("k_rep_chase", "root_finding"), ("k_orph_scan", "orphan_scan"),
-                     ("k_sweep_base", "store_sweep")):
+    for name, ph in (("k_rep_chase", "root_finding"), ("k_key_edges (orphans)", "orphan_scan"),
+                     ("k_key_edges (store)", "store_sweep")):
         if name in rooflines:
             rooflines[name]["median_launch_ms"] = round(med_del[ph], 4)
     dom = max(rooflines, key=lambda k: rooflines[k]["avg_launch_ms"])
