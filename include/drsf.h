@@ -88,7 +88,10 @@ typedef struct {
     int64_t delta_capacity;  /* inserted edges held in the inserted-edge list; an
                                 insert that would overflow it first merges the list
                                 into the base store (and drops deleted entries):
-                                O(|E|) work, amortised over the list; 0 = automatic
+                                O(|E|) work, amortised over the list; where few of
+                                its entries are live (deleted ones make room for
+                                later inserts) the list stays and only the vertices'
+                                edges are counted anew; 0 = automatic
                                 (max(4 max_batch, |E| / 8, 2^20)) */
     int sweep_mode;          /* delete key-edge scan: 0 (default) per batch, the
                                 orphans' adjacency (each orphan counted with 8
@@ -208,7 +211,8 @@ typedef struct {
     int64_t num_pieces;
     int64_t num_paths;
     int64_t num_orphans;      /* delete: vertices cut off from their old root */
-    int64_t orphan_slots;     /* delete: adjacency entries of those vertices */
+    int64_t orphan_slots;     /* delete: adjacency entries of those vertices, as of
+                                 the last merge of the inserted-edge list */
     int32_t scan_orphans;     /* delete: 1 if the key-edge scan covered only the
                                  orphans' adjacency, 0 if the whole store */
     int32_t host_finished;    /* 0 if the queued kernel sequence finished the
@@ -375,8 +379,8 @@ int drsf_static_forest(int32_t n, const int64_t *row_ptr, const int32_t *col, in
  * forbid allocation): it makes no device or host allocation.  Its scratch
  * is one array of 64 MiB in device memory that the library holds on each
  * device it runs on until the process ends; the graph must fit it:
- * 12 n + 8 nnz bytes plus about 1.5 KB, each of eight arrays rounded up to
- * 256 bytes (for example n = 10^6 with nnz = 6.8 * 10^6), else
+ * 12 n + 8 nnz bytes plus about 1.5 KB are taken as its need, in eight parts
+ * each rounded up to 256 bytes (for example n = 10^6 with nnz = 6.8 * 10^6), else
  * DRSF_E_CAPACITY and nothing is done.  Arguments, result and the other
  * errors are drsf_static_forest's.  Every call on a device uses that
  * device's one array, so calls that overlap on one device (from two host
@@ -430,7 +434,8 @@ int64_t drsf_num_edges(drsf_ctx *ctx);
 int drsf_export_edges(drsf_ctx *ctx, uint64_t *keys_host, int64_t capacity, int64_t *m_out);
 
 /* Device-side copy of the whole state; restore returns to it exactly.  A
- * snapshot taken before a store rebuild cannot be restored after it
+ * snapshot taken before a merge of the inserted-edge list (delta_capacity)
+ * or a growth of the small graphs' buffers cannot be restored after it
  * (DRSF_E_STATE). */
 typedef struct drsf_snapshot drsf_snapshot;
 int drsf_snapshot_take(drsf_ctx *ctx, drsf_snapshot **out);
