@@ -185,7 +185,8 @@ struct drsf_ctx {
     int jump_rounds = 0;
     // per update kind (bit kind), with levels left to the library (tuning 0):
     // super-trees oriented as they grow, set once an update of that kind
-    // needed more search levels than are queued; and the super-forest's Euler
+    // needed more search levels than are queued, or its launches for them
+    // were not worth it; and the super-forest's Euler
     // tour queued after the search (it skips itself when the search
     // sufficed), set once a walk of those was too long
     unsigned walk_kinds = 0, lr_kinds = 0;
@@ -2108,6 +2109,13 @@ int wait_oldest(drsf_ctx *c) {
     if (st != 0) {
         c->last_rc = fail(c, DRSF_E_DEVICE, "internal bound exceeded (status %d)", st);
     } else {
+        // the search sufficed: later updates of the kind do without its
+        // launches (R-MAT 20, 2 x 1e4 updates: 220 -> 204 us a step).  Not with
+        // another update queued, whose launches hold the search; and left
+        // alone where it costs no launches (one workgroup) or a graph would
+        // have to be captured again for it
+        if (c->npend == 0 && !c->solo && !graph_launch(c) && !(c->view.host_finished & 2) && k[C_NER] > 0)
+            c->walk_kinds |= 1u << c->kind;
         // the list as this update left it; of its inserts and deletes in the
         // store, those that did not go through the list changed base entries
         c->nd_known = (int64_t)k[C_NDELTA];

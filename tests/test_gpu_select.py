@@ -110,6 +110,30 @@ def test_super_trees_searched_then_oriented_as_they_grow(k, bits, launch_mode):
     pair.gpu.close()
 
 
+@pytest.mark.parametrize("k", [300, 16384])
+@pytest.mark.parametrize("launch_mode", [2, 1])
+def test_shallow_super_trees_first_then_deep_ones(k, launch_mode):
+    """A star's rays, for which the search suffices (a later update then does
+    without it), then the ruler chain above, its walks short or past their
+    bound, and both again."""
+    drsf = _lib()
+    _case(f"rays, then a ruler chain of {k} pieces, launch mode {launch_mode}")
+    weight = [((j + 1) & -(j + 1)).bit_length() for j in range(k)]
+    order = sorted(range(k), key=lambda j: (weight[j], j))
+    u = np.empty(k + 1, np.int64)
+    u[np.array(order)] = np.arange(k)
+    u[k] = 2 * k + 1
+    v = np.arange(k, 2 * k + 1, dtype=np.int64)
+    rays, c = 5000, 2 * k + 2
+    g = gen.make_graph("rays and ruler", 2 * k + 3 + rays, np.sort(gen.keys_of_edges(np.stack([u, v], 1))))
+    star = np.stack([np.full(rays, c), np.arange(c + 1, c + 1 + rays)], 1).astype(np.int32)
+    chain = np.stack([u[:k], v[1:k + 1]], axis=1).astype(np.int32)
+    both = np.concatenate([star, chain])
+    _run(g, [(star, drsf.DRSF_INSERT), (star, drsf.DRSF_DELETE), (star, drsf.DRSF_INSERT), (chain, drsf.DRSF_INSERT),
+             (both, drsf.DRSF_DELETE), (both, drsf.DRSF_INSERT), (both[::2], drsf.DRSF_DELETE)],
+         launch_mode=launch_mode)
+
+
 @pytest.mark.parametrize("device", [True, False])
 @pytest.mark.parametrize("b", [1, 2, 511, 512, 513, 4096, 4097, 8193])
 def test_batches_around_the_one_workgroup_bounds(b, device):
