@@ -108,8 +108,9 @@ typedef struct {
     int levels_queued;       /* super-forest search levels queued in the update's
                                 kernel sequence (max 12); 0 = chosen by the
                                 library: 4, until an update needed more (the
-                                host finishes it); later updates of its kind
-                                orient super-trees as they grow, without a
+                                host finishes it) or, launched kernel by
+                                kernel, found them enough; later updates of its
+                                kind orient super-trees as they grow, without a
                                 search, or, once that met too long a walk,
                                 queue the super-forest's Euler tour after 4
                                 levels (it skips itself when the search
