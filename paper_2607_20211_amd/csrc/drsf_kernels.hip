@@ -32,9 +32,12 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 // ignored), or -1; *raw receives the stored entry.  Each step loads
 // SEARCH_FAN evenly spaced entries at once and keeps the part of the run
 // that can hold v, so a run of length L takes about log_{FAN+1}(L)
-// dependent loads.
+// dependent loads.  A large batch is bound by the lines its probes touch, which
+// a wide fan adds to: k_classify on R-MAT 22, 1e6 entries, took 123, 124, 128,
+// 131 and 139 us with a fan of 1, 2, 3, 4 and 6; 1e5 entries 20 with each.
+// k_twin, 64e6 searches: 10.5 ms with a fan of 4, 8.4 with 2.
 #ifndef DRSF_SEARCH_FAN
-#define DRSF_SEARCH_FAN 4
+#define DRSF_SEARCH_FAN 2
 #endif
 constexpr int SEARCH_FAN = DRSF_SEARCH_FAN;
 __device__ __forceinline__ int64_t find_in_row(const int32_t *col, uint32_t lo, uint32_t hi,
