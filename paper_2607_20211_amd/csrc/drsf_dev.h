@@ -153,8 +153,10 @@ __device__ __forceinline__ void group_min_u64(bool active, int32_t target, uint6
 // The same merge over a workgroup's many (target, value) pairs: minima per
 // target in a small LDS table, then one global atomic per target met.  A
 // pair that finds no place within a few probes goes to memory by itself.
-// clear() once (with a barrier after it), then any number of add(), and
-// flush() by every thread of the workgroup, which leaves the table clear.
+// clear() once, then any number of add(), and flush(), which leaves the table
+// clear; every thread of the workgroup calls clear() and flush().  Both end in
+// a barrier: each wave clears a part of the table, and an add() to a part that
+// another wave has yet to clear would be lost.
 constexpr int MIN_SLOTS = 1024;
 constexpr int MIN_PROBES = 8;
 struct MinTable {
@@ -167,6 +169,7 @@ struct MinTable {
             id[s] = -1;
             val[s] = KEY_INF;
         }
+        __syncthreads();
     }
     __device__ __forceinline__ void add(int32_t target, uint64_t v, uint64_t *arr) {
         static_assert(MIN_SLOTS == 1 << 10, "the hash takes 10 bits");

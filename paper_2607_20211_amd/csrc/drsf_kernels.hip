@@ -1645,7 +1645,6 @@ __global__ __launch_bounds__(BLOCK) void k_bor_round0(Dev d) {
     if (stopped(d) || !d.ctl->has_ins) return;
     __shared__ MinTable s_min;
     s_min.clear();
-    __syncthreads();
     const int64_t total = (d.ctl->b + BLOCK - 1) / BLOCK;
     const int64_t per = (total + gridDim.x - 1) / gridDim.x;
     for (int64_t t = blockIdx.x * per; t < total && t < (blockIdx.x + 1) * per; t++) {
