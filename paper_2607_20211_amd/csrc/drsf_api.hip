@@ -207,7 +207,7 @@ struct drsf_ctx {
     Ctl *ctl = nullptr;
     // pinned host staging
     int32_t *h_edges = nullptr;           // [2 max_batch]
-    uint64_t *runs = nullptr, *h_runs = nullptr;  // [ngraph] several graphs: start << 8 | op of each one's batch
+    uint64_t *runs = nullptr, *h_runs = nullptr;  // [ngraph] drsf_multi_apply: start << 8 | op of each one's batch
     int32_t *h_lists = nullptr;           // vlist | ilist | tlist
     // Two slots of control block and returned words: an update can be
     // queued while the one before it runs.  Queued updates alternate between
@@ -1637,7 +1637,7 @@ static int create_impl(int32_t G, const int32_t *n_off, int32_t n, const int64_t
     c->gstat = reinterpret_cast<int32_t *>(c->ctlmem + 1 + C_TOTAL);
     launch_fill_u64(c->ctlmem, c->ret_words, 0, c->stream);
     if ((rc = dalloc(c, &c->goff, (int64_t)G + 1))) return bail(rc);
-    if (n_off && ((rc = dalloc(c, &c->runs, G)) || (rc = halloc(c, &c->h_runs, G)))) return bail(rc);
+    if ((rc = dalloc(c, &c->runs, G)) || (rc = halloc(c, &c->h_runs, G))) return bail(rc);
     // every copy of create runs on the context's stream, after the work the
     // caller queued there (or, for a context-owned stream, on the null stream)
     if (hipMemcpyAsync(c->goff, c->goff_h.data(), sizeof(int32_t) * ((size_t)G + 1), hipMemcpyHostToDevice,

@@ -3,6 +3,7 @@ and label arrays after each multi-graph update are bit-exact with the oracle
 run on that graph alone, in local ids."""
 from __future__ import annotations
 
+import ctypes
 import sys
 
 import numpy as np
@@ -208,4 +209,39 @@ def test_multi_context_with_one_graph():
         dl = gen.delete_batches(n, keys, par, 1, 400, min(200, trees), gen.seed(41, step, gen.P_DELETE))[0]
         pair.step([dl], np.array([drsf.DRSF_DELETE], np.int8), f"one graph delete {step}")
     pair.step([np.zeros((0, 2), np.int32)], np.array([drsf.DRSF_INSERT], np.int8), "one graph, empty")
+    pair.gpu.close()
+
+
+# one workgroup takes the whole front, only the rounds, or neither
+@pytest.mark.parametrize("b", [16, 1000, 6000])
+@pytest.mark.parametrize("device", [False, True])
+def test_multi_calls_on_a_one_graph_context(b, device):
+    """drsf_multi_apply takes a context that drsf_create made, as one graph:
+    the results are drsf_apply's."""
+    drsf = _lib()
+    from test_gpu_parity import Pair
+    _case(f"multi calls on a one-graph context: b {b}, device {device}")
+    n = 20001
+    g = gen.make_graph("one", n, gen.gnm(n, 2 * n, gen.seed(84, b, gen.P_GRAPH)))
+    pair = Pair(g, device=device, max_batch=8192)
+    apply = pair.gpu.apply
+    status = []
+
+    def apply_multi(edges, op):
+        st = drsf.drsf_multi_apply(pair.gpu.ctx, edges, [0, len(edges)], [op])
+        status.append(int(st[0]))
+        v = drsf.drsf_view()
+        assert drsf.load().drsf_get_view(pair.gpu.ctx, ctypes.byref(v)) == drsf.DRSF_OK
+        return pair.gpu._stats(v)
+
+    fresh = gen.insert_batches(n, g.keys, 1, b, gen.seed(84, b, gen.P_INSERT))[0]
+    rng = np.random.default_rng(84 + b)
+    k = rng.choice(g.keys, b, replace=False)
+    old = np.stack([k >> np.uint64(32), k & np.uint64(0xffffffff)], 1).astype(np.int32)
+    for step, (batch, op) in enumerate(((fresh, drsf.DRSF_INSERT), (old, drsf.DRSF_DELETE),
+                                        (old, drsf.DRSF_INSERT), (fresh, drsf.DRSF_DELETE))):
+        pair.gpu.apply = apply_multi if step % 3 else apply  # the two calls on one state
+        pair.step(np.ascontiguousarray(batch, np.int32), op, f"step {step}")
+    assert status == [drsf.DRSF_OK] * 2
+    assert np.array_equal(pair.gpu.edges(), pair.keys)
     pair.gpu.close()
