@@ -657,8 +657,10 @@ class MultiForest(Forest):
 
     def apply_multi_async(self, edges, b_off, op) -> None:
         edges, b_off, op = self._multi_args(edges, b_off, op)
-        self._pending_multi = edges
+        # the call waits for the update queued before, which may still be
+        # reading its batch: that batch is let go after it
         drsf_multi_apply_async(self.ctx, edges, b_off, op)
+        self._pending_multi = edges
 
     def wait_multi(self) -> np.ndarray:
         st = drsf_multi_wait(self.ctx, self.G)

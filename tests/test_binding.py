@@ -107,3 +107,25 @@ def test_multi_batch_offsets_are_checked():
     _refused(f.apply_multi, e, [0, 2], [0, 1])             # b_off too short
     _refused(f.apply_multi, e, [0, 2, 5], [0, 1])          # more edges than given
     _refused(f.apply_multi, torch.zeros((4, 2), dtype=torch.int64), [0, 2, 4], [0, 1])
+
+
+def test_queued_multi_batch_outlives_the_call_that_waits_for_it(monkeypatch):
+    """A device batch of several graphs is read in place.  The second call
+    waits for the first update inside the library: until then the first batch
+    must be alive, and the second until its own wait."""
+    import weakref
+    f = _ctx(drsf.MultiForest, on_device=True, G=2)
+    refs, alive = [], []
+
+    def call(ctx, edges, b_off, op):
+        alive.append([r() is not None for r in refs])
+        refs.append(weakref.ref(edges))
+
+    monkeypatch.setattr(drsf, "drsf_multi_apply_async", call)
+    monkeypatch.setattr(drsf, "drsf_multi_wait", lambda ctx, G: np.zeros(G, np.int32))
+    for _ in range(3):
+        f.apply_multi_async(FakeGpuTensor(n=8), [0, 2, 4], [0, 1])
+    assert alive == [[], [True], [False, True]]
+    assert refs[2]() is not None
+    f.wait_multi()
+    assert refs[2]() is None
