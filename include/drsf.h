@@ -89,9 +89,10 @@ typedef struct {
                                 insert that would overflow it first merges the list
                                 into the base store (and drops deleted entries):
                                 O(|E|) work, amortised over the list; where few of
-                                its entries are live (deleted ones make room for
-                                later inserts) the list stays and only the vertices'
-                                edges are counted anew; 0 = automatic
+                                its entries are live and few of the store's deleted
+                                (deleted ones make room for later inserts) the list
+                                keeps its live entries and the vertices' edges are
+                                counted anew; 0 = automatic
                                 (max(4 max_batch, |E| / 8, 2^20)) */
     int sweep_mode;          /* delete key-edge scan: 0 (default) per batch, the
                                 orphans' adjacency (each orphan counted with 8
@@ -390,6 +391,14 @@ int drsf_static_forest(int32_t n, const int64_t *row_ptr, const int32_t *col, in
  */
 int drsf_static_forest_noalloc(int32_t n, const int64_t *row_ptr, const int32_t *col, int32_t *parent_out,
                                int32_t *label_out, void *stream, int32_t *levels_out);
+
+/*
+ * The edge store of the context, host int64[4]: entries of its base (live and
+ * deleted), deleted ones among them, positions of the inserted-edge list that
+ * a delete reads, free ones among them (small graphs' edges are in neither).
+ * Errors: DRSF_E_ARG, or that of an update waited for.
+ */
+int drsf_store_figures(drsf_ctx *ctx, int64_t *out);
 
 /* Device bytes the context holds (its own allocations). */
 int64_t drsf_device_bytes(const drsf_ctx *ctx);

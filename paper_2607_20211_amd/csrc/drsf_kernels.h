@@ -326,6 +326,8 @@ void launch_insert_emit(const Dev &d, hipStream_t s);
 void launch_count_edges(const Dev &d, int32_t *adeg, unsigned long long *wdeg, int64_t list, hipStream_t s);
 // the list's hash index from its live entries (deleted keys leave it)
 void launch_rehash(const Dev &d, int64_t count, hipStream_t s);
+// the list's live entries to its front, no position free, its index with them
+void launch_list_compact(const Dev &d, int64_t count, hipStream_t s);
 // pointer-jumping rounds over rep before the chase (deep forests); a round
 // after one that changed nothing exits at once
 void launch_rep_jump(const Dev &d, int rounds, hipStream_t s);

@@ -653,6 +653,29 @@ __global__ __launch_bounds__(BLOCK) void k_rehash(Dev d) {
     }
 }
 
+// The list's live entries, packed (their order does not matter), then put at
+// its front: its length is their number and no position is free.  The packed
+// keys pass through the cross-edge scratch, which is unused between updates.
+__global__ __launch_bounds__(BLOCK) void k_list_pack(Dev d, uint64_t *packed) {
+    const int64_t nd = (int64_t)d.cnt[C_NDELTA];
+    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < nd; base += (int64_t)gridDim.x * BLOCK) {
+        const int64_t i = base + threadIdx.x;
+        const uint64_t k = i < nd ? d.dkey[i] : KEY_DEAD;
+        const int64_t at = block_append(k != KEY_DEAD ? 1 : 0, &d.cnt[C_LISTED]);
+        if (k != KEY_DEAD) packed[at] = k;
+    }
+}
+__global__ __launch_bounds__(BLOCK) void k_list_place(Dev d, const uint64_t *packed) {
+    const int64_t live = (int64_t)d.cnt[C_LISTED];
+    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < live; i += stride) d.dkey[i] = packed[i];
+}
+__global__ void k_list_close(Dev d) {
+    d.cnt[C_NDELTA] = d.cnt[C_LISTED];
+    d.cnt[C_NFREE] = 0;
+    d.cnt[C_LISTED] = 0;
+}
+
 // insert: key edges M = B; cross edges join two different trees (labels).
 // Batch entries [t * BLOCK, (t + 1) * BLOCK) go to region ibase + t of x0;
 // every thread of the workgroup calls it.  Returns the thread's edge (live
@@ -3025,6 +3048,14 @@ void launch_count_edges(const Dev &d, int32_t *adeg, unsigned long long *wdeg, i
 void launch_rehash(const Dev &d, int64_t count, hipStream_t s) {
     launch_fill_u64(d.dhash, (int64_t)d.dhmask + 1, HASH_EMPTY, s);
     hipLaunchKernelGGL(k_rehash, dim3(grid_for(count, BLOCK)), dim3(BLOCK), 0, s, d);
+}
+void launch_list_compact(const Dev &d, int64_t count, hipStream_t s) {
+    const dim3 grid(grid_for(count, BLOCK));
+    uint64_t *packed = reinterpret_cast<uint64_t *>(d.x1);
+    hipLaunchKernelGGL(k_list_pack, grid, dim3(BLOCK), 0, s, d, packed);
+    hipLaunchKernelGGL(k_list_place, grid, dim3(BLOCK), 0, s, d, packed);
+    hipLaunchKernelGGL(k_list_close, dim3(1), dim3(1), 0, s, d);
+    launch_rehash(d, count, s);
 }
 void launch_rep_jump(const Dev &d, int rounds, hipStream_t s) {
     for (int k = 0; k < std::min(rounds, MAX_JUMP); k++)

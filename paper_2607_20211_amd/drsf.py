@@ -79,7 +79,7 @@ class DrsfError(RuntimeError):
 
 # every symbol include/drsf.h declares
 EXPORTS = ("drsf_default_opts", "drsf_create", "drsf_apply", "drsf_apply_async", "drsf_wait",
-           "drsf_copy_out", "drsf_get_view", "drsf_num_edges", "drsf_export_edges",
+           "drsf_copy_out", "drsf_get_view", "drsf_store_figures", "drsf_num_edges", "drsf_export_edges",
            "drsf_snapshot_take", "drsf_snapshot_restore", "drsf_snapshot_free",
            "drsf_phase_times", "drsf_destroy", "drsf_last_error", "drsf_version",
            "drsf_multi_create", "drsf_multi_apply", "drsf_multi_apply_async", "drsf_multi_wait",
@@ -125,6 +125,8 @@ def load():
     lib.drsf_copy_out.restype = c_int
     lib.drsf_get_view.argtypes = [vp, ctypes.POINTER(drsf_view)]
     lib.drsf_get_view.restype = c_int
+    lib.drsf_store_figures.argtypes = [vp, vp]
+    lib.drsf_store_figures.restype = c_int
     lib.drsf_num_edges.argtypes = [vp]
     lib.drsf_num_edges.restype = i64
     lib.drsf_export_edges.argtypes = [vp, vp, i64, ctypes.POINTER(i64)]
@@ -420,6 +422,14 @@ def drsf_multi_num_edges(ctx, G: int) -> np.ndarray:
 
 def drsf_num_graphs(ctx) -> int:
     return int(load().drsf_num_graphs(ctx))
+
+
+def drsf_store_figures(ctx) -> dict:
+    """Entries of the base store and deleted ones among them, positions of the
+    inserted-edge list and free ones among them."""
+    x = np.zeros(4, dtype=np.int64)
+    _check(load().drsf_store_figures(ctx, _ptr(x)), ctx)
+    return dict(zip(("base", "deleted", "list", "free"), (int(v) for v in x)))
 
 
 def drsf_set_tuning(ctx, rounds_queued: int = 0, levels_queued: int = 0, sweep_mode: int = 0) -> None:

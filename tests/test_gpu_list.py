@@ -143,3 +143,64 @@ def test_snapshot_keeps_the_list():
         assert np.array_equal(pair.gpu.edges(), pair.keys)
     drsf.drsf_snapshot_free(snap)
     pair.gpu.close()
+
+
+# of 1500 inserted edges `stay` live on (the list keeps at most 187 at a merge point)
+@pytest.mark.parametrize("stay", [0, 1, 150])
+@pytest.mark.parametrize("launch_mode", [1, 2])
+def test_a_burst_that_went_away_leaves_a_short_list(stay, launch_mode):
+    """A list filled by edges that are deleted again is as short as its live
+    entries after the merge point, and they are found and deleted as before."""
+    drsf = _lib()
+    _case(f"a burst of inserted edges that goes away: {stay} stay, launch mode {launch_mode}")
+    n, dcap = 3001, 1500
+    g = gen.make_graph("burst", n, gen.gnm(n, 5003, gen.seed(85, 0, gen.P_GRAPH)))
+    pair = Pair(g, max_batch=500, delta_capacity=dcap, launch_mode=launch_mode)
+    fresh = gen.insert_batches(n, g.keys, 7, 500, gen.seed(85, 0, gen.P_INSERT))
+    burst = np.concatenate(fresh[:3])
+
+    def figures():
+        return drsf.drsf_store_figures(pair.gpu.ctx)
+
+    for b in fresh[:3]:
+        pair.step(b, drsf.DRSF_INSERT, "burst")
+    for k in range(stay, dcap, 500):
+        pair.step(burst[k:k + 500], drsf.DRSF_DELETE, "burst goes")
+    assert figures() == {"base": len(g.keys), "deleted": 0, "list": dcap, "free": dcap - stay}
+    for k in range(2):  # the second round takes and frees positions of the short list
+        pair.step(fresh[3 + k][:100], drsf.DRSF_INSERT, "after the merge point")
+        assert figures() == {"base": len(g.keys), "deleted": 0, "list": stay + 100, "free": 0}
+        assert np.array_equal(pair.gpu.edges(), pair.keys)
+        pair.step(fresh[3 + k][:100], drsf.DRSF_DELETE, "again")
+        assert figures()["free"] == 100
+    if stay:
+        pair.step(burst[:stay], drsf.DRSF_DELETE, "the rest of the burst")
+    assert np.array_equal(pair.gpu.edges(), g.keys)
+    pair.gpu.close()
+
+
+@pytest.mark.parametrize("gone", [625, 626, 2501])  # of 5003: an eighth, just over it, half
+def test_deleted_base_entries_are_dropped(gone):
+    """A merge point drops the base store's deleted entries once more than an
+    eighth of them are, also where the list's own entries would stay."""
+    drsf = _lib()
+    _case(f"deleted base entries at a merge point: {gone} of 5003")
+    n, dcap = 3001, 1500
+    g = gen.make_graph("shrunk", n, gen.gnm(n, 5003, gen.seed(86, 0, gen.P_GRAPH)))
+    pair = Pair(g, max_batch=2501, delta_capacity=dcap)
+    fresh = gen.insert_batches(n, g.keys, 4, 500, gen.seed(86, 0, gen.P_INSERT))
+    down = np.random.default_rng(86).choice(g.keys, gone, replace=False)
+    pair.step(_pairs(down), drsf.DRSF_DELETE, "shrink")
+    for b in fresh[:3]:
+        pair.step(b, drsf.DRSF_INSERT, "short-lived")
+        pair.step(b, drsf.DRSF_DELETE, "short-lived")
+    was = drsf.drsf_store_figures(pair.gpu.ctx)
+    assert was == {"base": 5003, "deleted": gone, "list": 500, "free": 500}
+    pair.step(fresh[3][:10], drsf.DRSF_INSERT, "merge point")
+    kept = 8 * gone <= 5003
+    assert drsf.drsf_store_figures(pair.gpu.ctx) == {
+        "base": 5003 if kept else 5003 - gone, "deleted": gone if kept else 0, "list": 10, "free": 0}
+    assert np.array_equal(pair.gpu.edges(), pair.keys)
+    pair.step(_pairs(down[:300]), drsf.DRSF_INSERT, "some come back")
+    assert np.array_equal(pair.gpu.edges(), pair.keys)
+    pair.gpu.close()
