@@ -115,7 +115,9 @@ typedef struct {
                                 search, or, once that met too long a walk,
                                 queue the super-forest's Euler tour after 4
                                 levels (it skips itself when the search
-                                sufficed) */
+                                sufficed) for 16 updates, then for twice as
+                                many each time (at most 1024) that a walk was
+                                too long again */
     int reverse_mode;        /* path reversal: 0 (default) one thread walks each
                                 path; 1: Euler tour of F-hat with list ranking,
                                 start/finish times and the interval test
@@ -414,8 +416,8 @@ int64_t drsf_footprint(int32_t n, int64_t nnz, const drsf_opts *opts);
  * Changes the tunables of drsf_opts (rounds_queued, levels_queued,
  * sweep_mode; 0 = default for the first two) on a live context (captured
  * update graphs are dropped).  Results do not depend on them (only the split
- * between queued and host-driven work does).  Used by the
- * autotuner.  Errors: DRSF_E_ARG.
+ * between queued and host-driven work does).  Counts left to the library
+ * start from its first choice again.  Used by the autotuner.  Errors: DRSF_E_ARG.
  */
 int drsf_set_tuning(drsf_ctx *ctx, int rounds_queued, int levels_queued, int sweep_mode);
 

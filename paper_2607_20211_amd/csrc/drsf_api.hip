@@ -190,10 +190,13 @@ struct drsf_ctx {
     // per update kind (bit kind), with levels left to the library (tuning 0):
     // super-trees oriented as they grow, set once an update of that kind
     // needed more search levels than are queued, or its launches for them
-    // were not worth it; and the super-forest's Euler
-    // tour queued after the search (it skips itself when the search
-    // sufficed), set once a walk of those was too long
+    // were not worth it; and the super-forest's Euler tour queued after the
+    // search (it skips itself when the search sufficed), set once a walk of
+    // those was too long, for lr_left further updates of the kind: then they
+    // grow oriented again, and the next time that fails the tour is queued for
+    // twice as many (lr_span)
     unsigned walk_kinds = 0, lr_kinds = 0;
+    int lr_left[4] = {}, lr_span[4] = {};
     // small batches run their rounds in one workgroup: a delete after
     // solo_from full-grid selections, one more for each time its list of live
     // edges was still too long for it (past SOLO_ROUND_MAX all rounds are
@@ -201,6 +204,7 @@ struct drsf_ctx {
     // does (its solo_from, or 0)
     int solo_from = 1;
     int solo = 0;
+    int levels = 0;  // search levels of the update waited for
     // status word, counters and per-graph batch status share one allocation
     // so that one copy returns them: status at word 0, counters from word 1,
     // gstat after the counters
@@ -239,6 +243,7 @@ struct drsf_ctx {
         int64_t b;
         int64_t nins;  // inserts into the edge store
         int solo;      // its rounds ran in one workgroup: after so many selections
+        int levels;    // search levels it was launched with
     } pend[2] = {};
     int npend = 0;
     // results of updates that a call of the library waited for on the
@@ -1137,9 +1142,33 @@ int sg_reduce(drsf_ctx *c, const Dev &d, hipStream_t s) {
 // of every piece the context can register.
 int tour_rounds(const drsf_ctx *c) { return std::min(ceil_log2(2 * c->pcap + 2) + 2, MAX_ROUNDS); }
 
+// Updates replay captured graphs (launch_mode 1, or 0 with several graphs)
+// rather than launching kernel by kernel.
+bool graph_launch(const drsf_ctx *c) {
+    return c->opts.launch_mode == 1 || (c->opts.launch_mode == 0 && c->ngraph > 1);
+}
+
 // Super-trees are oriented as they grow, without a search.
 bool walks(const drsf_ctx *c, int kind) {
     return c->opts.levels_queued <= 0 && (c->walk_kinds & ~c->lr_kinds & (1u << kind)) != 0;
+}
+// The tour was queued for updates of this kind long enough: they are oriented
+// as they grow again (without this one outlier would cost every later update
+// of a context the search, the tour's launches and the one-workgroup rounds).
+constexpr int LR_SPAN = 16, LR_SPAN_MAX = 1024;
+int leave_tour(drsf_ctx *c, int kind) {
+    if (!(c->lr_kinds & (1u << kind)) || c->lr_left[kind]-- > 0) return DRSF_OK;
+    if (graph_launch(c)) {
+        HIPCHK(c, hipStreamSynchronize(c->stream));  // a queued update may still run a graph
+        drop_graphs(c);
+    }
+    c->lr_kinds &= ~(1u << kind);
+    return DRSF_OK;
+}
+void enter_tour(drsf_ctx *c, int kind) {
+    c->lr_span[kind] = c->lr_span[kind] ? std::min(2 * c->lr_span[kind], LR_SPAN_MAX) : LR_SPAN;
+    c->lr_left[kind] = c->lr_span[kind];
+    c->lr_kinds |= 1u << kind;
 }
 // search levels queued
 int levels_of(const drsf_ctx *c, int kind) { return walks(c, kind) ? 0 : c->bfs_fast; }
@@ -1309,7 +1338,7 @@ int continue_update(drsf_ctx *c) {
     int how = 0;  // the bits of drsf_view.host_finished
     // profiled contexts time the continuation, host round trips included
     c->cont_timed = c->have_phases;
-    const int queued = levels_of(c, c->kind);  // search levels in the sequence
+    const int queued = c->levels;  // search levels in the sequence
     const int solo = c->solo;
     if (!oriented) {
         if ((rc = read_flags(queued))) return rc;
@@ -1378,7 +1407,7 @@ int continue_update(drsf_ctx *c) {
     // queued round that finds nothing costs one dispatch; bounded so that one
     // outlier cannot make every update slow).  If the search was too short,
     // they orient super-trees as they grow, and if that failed, they queue
-    // the tour
+    // the tour for a while
     if (!bad) {
         bool grew = false;
         if ((how & 1) && solo) {
@@ -1390,19 +1419,14 @@ int continue_update(drsf_ctx *c) {
             grew = true;
         }
         if ((how & 2) && c->opts.levels_queued <= 0) {
-            unsigned &kinds = queued == 0 ? c->lr_kinds : c->walk_kinds;
+            const unsigned kinds = queued == 0 ? c->lr_kinds : c->walk_kinds;
             grew |= !(kinds & (1u << c->kind));
-            kinds |= 1u << c->kind;
+            if (queued > 0) c->walk_kinds |= 1u << c->kind;
+            else if (!(kinds & (1u << c->kind))) enter_tour(c, c->kind);
         }
         if (grew) drop_graphs(c);
     }
     return DRSF_OK;
-}
-
-// Updates replay captured graphs (launch_mode 1, or 0 with several graphs)
-// rather than launching kernel by kernel.
-bool graph_launch(const drsf_ctx *c) {
-    return c->opts.launch_mode == 1 || (c->opts.launch_mode == 0 && c->ngraph > 1);
 }
 
 // Queues one update whose batch is in the device batch buffers and whose
@@ -1418,6 +1442,7 @@ int launch_update(drsf_ctx *c) {
     *(volatile unsigned long long *)(c->h_ret + c->ret_words + 7) = 0;
     c->kind = (c->h_ctl->has_ins ? 1 : 0) | (c->h_ctl->has_del ? 2 : 0);
     if (c->kind == 0) c->kind = 3;  // nothing but rejected or empty batches: run everything
+    if (const int rc = leave_tour(c, c->kind)) return rc;
     c->h_ctl->walk = walks(c, c->kind);
     // the supergraph reads sizes back between its kernels, so it is not
     // captured (the Euler-tour reversal, sort included, is a fixed sequence).
@@ -1435,7 +1460,8 @@ int launch_update(drsf_ctx *c) {
         HIPCHK(c, hipGraphLaunch(c->gexec[c->slot][c->kind], s));
     }
     HIPCHK(c, hipGetLastError());
-    c->pend[c->slot] = drsf_ctx::Pend{c->seq, c->kind, c->last_op, c->last_b, c->last_nins, c->solo};
+    c->pend[c->slot] = drsf_ctx::Pend{c->seq, c->kind, c->last_op, c->last_b, c->last_nins, c->solo,
+                                    levels_of(c, c->kind)};
     c->last_slot = c->slot;
     c->npend++;
     c->have_phases = prof;
@@ -1448,6 +1474,7 @@ int relaunch_update(drsf_ctx *c, int q) {
     select_slot(c, q);
     c->kind = c->pend[q].kind;
     c->h_ctl->walk = walks(c, c->kind);  // the host's continuation may have changed it
+    c->pend[q].levels = levels_of(c, c->kind);
     c->pend[q].solo = solo_update(c, c->kind, graph_launch(c) ? c->max_batch : std::max<int64_t>(c->h_ctl->b, 1));
     if (!graph_launch(c)) {
         enqueue_update(c, c->kind, false, c->h_ctl);
@@ -1795,6 +1822,10 @@ int drsf_set_tuning(drsf_ctx *c, int rounds_queued, int levels_queued, int sweep
     c->opts.rounds_queued = rounds_queued;
     c->opts.levels_queued = levels_queued;
     c->opts.sweep_mode = sweep_mode;
+    // what earlier updates taught the library goes with the old setting
+    c->walk_kinds = c->lr_kinds = 0;
+    std::fill(c->lr_span, c->lr_span + 4, 0);
+    c->solo_from = 1;
     // the captured sequences hold the old round counts
     HIPCHK(c, hipStreamSynchronize(c->stream));
     drop_graphs(c);
@@ -2045,6 +2076,7 @@ int wait_oldest(drsf_ctx *c) {
     c->last_b = c->pend[q].b;
     c->last_op = c->pend[q].op;
     c->solo = c->pend[q].solo;
+    c->levels = c->pend[q].levels;
     c->npend--;
     // the last kernel writes the completion word once the results in
     // h_ret are final: poll it (a stream synchronisation wakes up later),

@@ -134,6 +134,53 @@ def test_shallow_super_trees_first_then_deep_ones(k, launch_mode):
          launch_mode=launch_mode)
 
 
+@pytest.mark.parametrize("queued", [False, True])
+@pytest.mark.parametrize("launch_mode", [2, 1])
+def test_the_tour_is_queued_for_a_while(launch_mode, queued):
+    """The long ruler chain above, until the tour is queued; after sixteen
+    updates of the kind super-trees grow oriented again, so that the next long
+    walk is the host's once more, and shallow ones need neither."""
+    drsf = _lib()
+    k = 16384
+    _case(f"ruler chain of {k} pieces and rays, launch mode {launch_mode}, queued {queued}")
+    weight = [((j + 1) & -(j + 1)).bit_length() for j in range(k)]
+    order = sorted(range(k), key=lambda j: (weight[j], j))
+    u = np.empty(k + 1, np.int64)
+    u[np.array(order)] = np.arange(k)
+    u[k] = 2 * k + 1
+    v = np.arange(k, 2 * k + 1, dtype=np.int64)
+    c = 2 * k + 2
+    g = gen.make_graph("tour for a while", 2 * k + 43, np.sort(gen.keys_of_edges(np.stack([u, v], 1))))
+    star = np.stack([np.full(40, c), np.arange(c + 1, c + 41)], 1).astype(np.int32)
+    chain = np.stack([u[:k], v[1:k + 1]], axis=1).astype(np.int32)
+    pair = Pair(g, max_batch=k, launch_mode=launch_mode, device=queued)
+
+    def there_and_back(batch, what):
+        if not queued:
+            st, _ = pair.step(batch, drsf.DRSF_INSERT, what)
+            pair.step(batch, drsf.DRSF_DELETE, what)
+            return st["host_finished"] & 2
+        import torch
+        with torch.cuda.stream(pair.stream):
+            e = torch.from_numpy(batch).to(pair.dev)
+        for op in (drsf.DRSF_INSERT, drsf.DRSF_DELETE):
+            pair.gpu.apply_async(e, op)
+        st = pair.gpu.wait()
+        pair.gpu.wait()
+        for op in (oracle.INSERT, oracle.DELETE):
+            r = oracle.apply(pair.n, pair.keys, pair.parent, batch, op, label=pair.label)
+            pair.keys, pair.parent, pair.label = r.keys, r.parent, r.label
+        pair.check_equal(what)
+        return st["host_finished"] & 2
+
+    assert [there_and_back(chain, f"chain {i}") for i in range(3)] == [2, 2, 0]
+    assert [there_and_back(star, f"rays {i}") for i in range(16)] == [0] * 16
+    assert [there_and_back(chain, f"chain again {i}") for i in range(3)] == [2, 0, 0]
+    assert [there_and_back(star, f"rays again {i}") for i in range(29)] == [0] * 29
+    assert [there_and_back(chain, f"chain at last {i}") for i in range(3)] == [0, 2, 0]
+    pair.gpu.close()
+
+
 @pytest.mark.parametrize("device", [True, False])
 @pytest.mark.parametrize("b", [1, 2, 511, 512, 513, 4096, 4097, 8193])
 def test_batches_around_the_one_workgroup_bounds(b, device):
