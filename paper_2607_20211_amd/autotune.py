@@ -24,7 +24,10 @@ import json
 import os
 import time
 
-CANDIDATES = [(r, l, m) for r in (2, 3, 4, 6) for l in (2, 4, 6) for m in (0, 1)]
+# (0, 0) leaves both counts to the library, which follows its updates (super-trees
+# oriented as they grow, small batches in one workgroup) where set counts are kept to
+CANDIDATES = [(0, 0, m) for m in (0, 1)]
+CANDIDATES += [(r, l, m) for r in (2, 3, 4, 6) for l in (2, 4, 6) for m in (0, 1)]
 
 
 def cache_path() -> str:

@@ -85,3 +85,18 @@ def test_tune_batched_searches_threshold_schedule_and_rounds(monkeypatch):
     assert (ch["small_threads"], ch["small_workgroups"]) == (1024, 128) and f.small == (1024, 128)
     assert (ch["rounds_queued"], ch["levels_queued"], ch["sweep_mode"]) == (4, 2, 0)
     assert ch["small_graph_vertices"] == 2048
+
+
+def test_the_library_s_own_choice_can_be_kept(monkeypatch):
+    """Counts left to the library are among the candidates, so that a tuned
+    context is no slower than an untuned one."""
+    monkeypatch.setattr("paper_2607_20211_amd.drsf.drsf_snapshot_free", lambda s: None)
+    clock = [0.0]
+    monkeypatch.setattr(autotune.time, "perf_counter", lambda: clock[0])
+    f = FakeForest(lambda s: 1.0 if s[:2] == (0, 0) else 2.0)
+
+    def sample(fr):
+        clock[0] += fr.cost(fr.setting)
+
+    r = autotune.tune(f, sample, "k", use_cache=False)
+    assert (r["rounds_queued"], r["levels_queued"], r["sweep_mode"]) == (0, 0, 0) == f.setting
