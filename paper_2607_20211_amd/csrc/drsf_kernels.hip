@@ -289,13 +289,15 @@ __device__ __forceinline__ int64_t list_block(const int32_t *list, int64_t cnt, 
 // nothing but batch scratch is written.
 // The update's control block comes from pinned host memory (a captured
 // launch) or with the launch (a kernel-by-kernel one); the first workgroup
-// publishes it for what follows, which reads the device copy.
+// publishes it for what follows, which reads the device copy.  (kc by value: by
+// reference the compiler copies it to scratch memory first; R-MAT 22, b = 1e5:
+// k_classify 19.4 us, now 17.4; 16 edges: k_solo_front 16.0 and 14.7.)
 struct BatchHead {
     int64_t b;
     int op, revive;
     const int32_t *edges;
 };
-__device__ __forceinline__ BatchHead publish_ctl(const Dev &d, const Ctl &kc, int from_arg) {
+__device__ __forceinline__ BatchHead publish_ctl(const Dev &d, Ctl kc, int from_arg) {
     if (from_arg) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *d.ctlw = kc;
         return BatchHead{kc.b, kc.op, kc.revive, kc.edges};
