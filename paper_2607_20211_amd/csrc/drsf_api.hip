@@ -1045,11 +1045,14 @@ int rebuild_store(drsf_ctx *c) {
     c->bptr = c->lptr = nullptr;
     c->bcol = c->lcol = c->zrow = c->tile_k = nullptr;
     c->twin = c->ltwin = c->zptr = nullptr;
-    const int64_t old_tiles = c->ntiles;
+    const int64_t old_tiles = c->ntiles, m_live = c->m_live;
+    const std::vector<int64_t> gm = c->gm_h;
     rc = build_store(c, rowp, col, nnz, true);
     dfree(c, rowp);
     dfree(c, col);
     if (rc) return rc;
+    c->m_live = m_live;  // the store's own count leaves out the small graphs' edges
+    c->gm_h = gm;
     if (c->ntiles > old_tiles && (rc = alloc_tiles(c))) return rc;
     // empty inserted-edge list
     launch_fill_u64(c->cnt + C_NDELTA, 1, 0, s);

@@ -142,3 +142,33 @@ def test_every_graph_small_runs_the_engine_alone(profile):
             assert all(t[k] == 0.0 for k in ("validate", "update_graph", "root_finding", "orphan_scan",
                                               "superforest_rooting", "reversal_and_labels")), t
     pair.gpu.close()
+
+
+@pytest.mark.parametrize("launch_mode", [1, 2])
+def test_a_store_rebuild_leaves_the_small_graphs_counts(launch_mode):
+    """A rebuild of the edge store (the list of the graphs in it is full) keeps
+    the edge counts of the graphs that the one-workgroup engine holds: they are
+    reported, decide when a graph's buffers grow, and size the export."""
+    drsf = _lib()
+    _case(f"store rebuild beside small graphs, launch mode {launch_mode}")
+    ns = [120, 3000, 90, 2000]
+    graphs = [gen.make_graph(f"g{i}", n, gen.gnm(n, 3 * n, gen.seed(87, i, gen.P_GRAPH))) for i, n in enumerate(ns)]
+    pair = MultiPair(graphs, max_batch=8192, delta_capacity=8192, small_graph_vertices=200, launch_mode=launch_mode)
+    small = {i: gen.insert_batches(ns[i], graphs[i].keys, 3, per, gen.seed(87, i, gen.P_INSERT))
+             for i, per in ((0, 1500), (2, 1000))}
+    big = {i: gen.insert_batches(ns[i], graphs[i].keys, 3, 2500, gen.seed(88, i, gen.P_INSERT)) for i in (1, 3)}
+    none = np.zeros((0, 2), np.int32)
+
+    def step(batches, op, what):
+        pair.step(batches, [op] * 4, what)
+        want = np.sort(np.concatenate([gen.shift_keys(s[1], int(o)) for s, o in zip(pair.state, pair.mg.n_off)]))
+        assert np.array_equal(pair.gpu.edges(), want), what
+
+    ins, dl = drsf.DRSF_INSERT, drsf.DRSF_DELETE
+    step([small[0][0], big[1][0], small[2][0], big[3][0]], ins, "fill the list")
+    step([none, big[1][1], none, none], ins, "more")
+    step([small[0][1], none, small[2][1], big[3][1]], ins, "past the merge point")  # 10,000 inserts, most live
+    step([small[0][2], big[1][2], none, none], ins, "a small graph outgrows its buffers")  # 4,500 more than it had
+    old = np.stack([graphs[0].keys >> np.uint64(32), graphs[0].keys & np.uint64(0xffffffff)], 1).astype(np.int32)
+    step([old, none, small[2][0], none], dl, "delete")
+    pair.gpu.close()
