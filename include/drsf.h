@@ -397,7 +397,8 @@ int drsf_static_forest_noalloc(int32_t n, const int64_t *row_ptr, const int32_t 
 /*
  * The edge store of the context, host int64[4]: entries of its base (live and
  * deleted), deleted ones among them, positions of the inserted-edge list that
- * a delete reads, free ones among them (small graphs' edges are in neither).
+ * a delete reads, free ones among them.  Edges of small graphs are in neither;
+ * the places they had in the base at create count as deleted.
  * Errors: DRSF_E_ARG, or that of an update waited for.
  */
 int drsf_store_figures(drsf_ctx *ctx, int64_t *out);

@@ -115,10 +115,11 @@ struct drsf_ctx {
     // queued ones included: at most dcap.  The list's length after every
     // queued update, at most (its arrays hold lcap); its length and free
     // positions after the last update waited for; slots of its index that may
-    // not be empty; deleted entries of the base store
+    // not be empty; deleted entries of the base store; and its entries of
+    // small graphs, which hold nothing since they were moved out
     int64_t ndelta_bound = 0;
     int64_t lcap = 0, list_len = 0;
-    int64_t nd_known = 0, nfree_known = 0, hash_used = 0, ntomb = 0;
+    int64_t nd_known = 0, nfree_known = 0, hash_used = 0, ntomb = 0, nvoid = 0;
     uint64_t *dhash = nullptr;
     int32_t *dhpos = nullptr, *dfree = nullptr;
     int32_t *adeg = nullptr;
@@ -781,6 +782,7 @@ int setup_small(drsf_ctx *c) {
     for (int32_t k = 0; k < c->nsg; k++) {
         const int32_t g = c->sgid_h[k];
         const int64_t m = c->gm_h[g];
+        c->nvoid += m;
         c->scap_h[k] = std::max<int64_t>(2 * m, m + 4096);  // room for inserts before the pool grows
         c->soff_h[k] = off;
         off += 2 * c->scap_h[k];
@@ -1058,7 +1060,7 @@ int rebuild_store(drsf_ctx *c) {
     launch_fill_u64(c->cnt + C_NDELTA, 1, 0, s);
     launch_fill_u64(c->cnt + C_NFREE, 1, 0, s);
     launch_fill_u64(c->dhash, (int64_t)c->dhmask + 1, HASH_EMPTY, s);
-    c->nd_known = c->nfree_known = c->list_len = c->hash_used = c->ntomb = 0;
+    c->nd_known = c->nfree_known = c->list_len = c->hash_used = c->ntomb = c->nvoid = 0;
     c->adeg_on = false;
     HIPCHK(c, hipStreamSynchronize(s));
     c->broken = false;
@@ -1079,7 +1081,7 @@ int rebuild_store(drsf_ctx *c) {
 // refused after either.
 int merge_list(drsf_ctx *c) {
     int rc;
-    if (c->nd_known - c->nfree_known > c->dcap / LIST_KEEP || c->ntomb > c->eb / TOMB_KEEP) {
+    if (c->nd_known - c->nfree_known > c->dcap / LIST_KEEP || c->ntomb + c->nvoid > c->eb / TOMB_KEEP) {
         if ((rc = rebuild_store(c))) return rc;
     } else {
         if (!c->osum && (rc = dalloc(c, &c->osum, FINISH_CAP))) return rc;
@@ -2288,7 +2290,7 @@ int drsf_store_figures(drsf_ctx *c, int64_t *out) {
     const int rc = finish_pending(c);
     if (rc) return rc;
     out[0] = c->eb;
-    out[1] = c->ntomb;
+    out[1] = c->ntomb + c->nvoid;
     out[2] = c->nd_known;
     out[3] = c->nfree_known;
     return DRSF_OK;

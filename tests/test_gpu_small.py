@@ -172,3 +172,22 @@ def test_a_store_rebuild_leaves_the_small_graphs_counts(launch_mode):
     old = np.stack([graphs[0].keys >> np.uint64(32), graphs[0].keys & np.uint64(0xffffffff)], 1).astype(np.int32)
     step([old, none, small[2][0], none], dl, "delete")
     pair.gpu.close()
+
+
+def test_the_small_graphs_places_in_the_store_are_dropped():
+    """The entries that small graphs leave behind in the edge store go at the
+    first merge point, also where few edges of the list are live."""
+    drsf = _lib()
+    _case("places of small graphs in the edge store")
+    ns = [900, 800, 1000, 2000]
+    graphs = _graphs(ns, 9)
+    pair = MultiPair(graphs, max_batch=2048, delta_capacity=2048, small_graph_vertices=1000)
+    fresh = gen.insert_batches(2000, graphs[3].keys, 3, 1024, gen.seed(89, 3, gen.P_INSERT))
+    none = np.zeros((0, 2), np.int32)
+    m = [len(g.keys) for g in graphs]
+    assert drsf.drsf_store_figures(pair.gpu.ctx) == {"base": sum(m), "deleted": sum(m[:3]), "list": 0, "free": 0}
+    for k in range(3):
+        pair.step([none, none, none, fresh[k]], [drsf.DRSF_INSERT] * 4, f"insert {k}")
+        pair.step([none, none, none, fresh[k]], [drsf.DRSF_DELETE] * 4, f"delete {k}")
+    assert drsf.drsf_store_figures(pair.gpu.ctx) == {"base": m[3], "deleted": 0, "list": 1024, "free": 1024}
+    pair.gpu.close()
