@@ -1912,7 +1912,6 @@ int drsf_apply_async(drsf_ctx *c, const int32_t *edges, int64_t b, int op) {
     k.has_ins = op == DRSF_INSERT;
     k.has_del = op == DRSF_DELETE;
     k.ngraph = 1;
-    k.lfast = c->bfs_fast;
     k.smode = c->opts.sweep_mode;
     k.nvl = k.nil = k.ntl = -1;
     c->last_nins = op == DRSF_INSERT ? b : 0;
@@ -2051,7 +2050,6 @@ int drsf_multi_apply_async(drsf_ctx *c, const int32_t *edges, const int64_t *b_o
     k.has_ins = any_ins;
     k.has_del = any_del;
     k.ngraph = G;
-    k.lfast = c->bfs_fast;
     k.smode = c->opts.sweep_mode;
     k.nvl = nvl;
     k.nil = nil;

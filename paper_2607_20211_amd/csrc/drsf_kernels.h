@@ -19,13 +19,11 @@ struct Ctl {
     int32_t has_ins;  // some edge inserts
     int32_t has_del;  // some edge deletes
     int32_t ngraph;   // graphs in this context (per-graph batch status)
-    int32_t lfast;    // search levels queued before the orientation step
     int32_t smode;    // delete sweep: 0 chosen per batch, 1 always the full store
     const int32_t *edges;  // the batch in the caller's device memory, or null: staged copy
     uint64_t seq;          // update number, written to the completion word when done
     int32_t nsmall;        // small graphs with a batch in this update (SmallDev::tasks)
     int32_t walk;          // super-trees are oriented as they grow instead of searched
-    int32_t pad;
     int32_t revive;        // inserts look for their deleted base entry also without validation
 };
 
