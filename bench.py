@@ -36,9 +36,14 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 
 
+# parts of one kernel, each a launch of its own in the profiled pass: the
+# function that does the part
+KERNEL_PARTS = {"k_key_edges (orphans)": "orphan_scan", "k_key_edges (store)": "sweep_base"}
+
+
 def kernel_source_sha(kernel: str) -> str:
     """sha256[:16] of the kernel's own definition in drsf_kernels.hip (from
-    its __global__ line to its closing brace)."""
+    its first line to its closing brace)."""
     import hashlib
     src = open(os.path.join(ROOT, "paper_2607_20211_amd", "csrc", "drsf_kernels.hip")).read()
     i = src.find(f" void {kernel}(")
@@ -59,7 +64,7 @@ def measured_traffic(kernel: str, workload: str):
     runs (profiles/*.counters.json), or None when the kernel's definition
     has changed since the counters were taken."""
     import glob
-    h = kernel_source_sha(kernel.split(" ")[0])
+    h = kernel_source_sha(KERNEL_PARTS.get(kernel, kernel))
     for path in glob.glob(os.path.join(ROOT, "profiles", "*.counters.json")):
         c = json.load(open(path))
         if c.get("kernel") == kernel and c.get("workload") == workload and c.get("kernel_sha256_16") == h:
