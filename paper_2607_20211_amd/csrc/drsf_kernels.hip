@@ -34,7 +34,8 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 // that can hold v, so a run of length L takes about log_{FAN+1}(L)
 // dependent loads.  A large batch is bound by the lines its probes touch, which
 // a wide fan adds to: k_classify on R-MAT 22, 1e6 entries, took 123, 124, 128,
-// 131 and 139 us with a fan of 1, 2, 3, 4 and 6; 1e5 entries 20 with each.
+// 131 and 139 us with a fan of 1, 2, 3, 4 and 6 (113 now with 2, at 1.33 GB of
+// traffic for two launches); 1e5 entries the same with each (17 now).
 // k_twin, 64e6 searches: 10.5 ms with a fan of 4, 8.4 with 2.
 #ifndef DRSF_SEARCH_FAN
 #define DRSF_SEARCH_FAN 2
